@@ -49,6 +49,50 @@ struct NmGroup {
     int iters;         // iterations taken (set when the task stops)
 };
 
+// Run the trajectory theta_k, k = 0..T-1, sample by sample, calling sink(k, dtheta, theta_eq)
+// with theta_k = dtheta + theta_eq.  kmin/kmax: wave-uniform bounds of the
+// lanes' pulse-end samples; samples below kmin are pulse for every lane and
+// samples above kmax post for every lane, so only [kmin, kmax] branches.
+template <int UNROLL, class RT, class Sink>
+__device__ __forceinline__ void run_steps(const PlantT<RT>& pl, int T, RT dt, int k0, RT frac,
+                                               int kmin, int kmax, Sink& sink)
+{
+    RT d[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) d[i] = pl.d0[i];
+    RT theq = pl.th1;
+    if (k0 < 0) {  // PW <= 0: no pulse, the step acts from t = 0
+#pragma unroll
+        for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
+        theq = pl.amp;
+    }
+    int k = 0;
+    const int ka = min(kmin, T);
+#pragma unroll UNROLL
+    for (; k < ka; ++k) {
+        sink(k, d[0], theq);
+        step<0>(pl, d);
+    }
+    const int kb = min(kmax, T - 1);
+#pragma unroll 1
+    for (; k <= kb; ++k) {
+        sink(k, d[0], theq);
+        if (k < k0) {
+            step<0>(pl, d);
+        } else if (k == k0) {
+            split_step(pl, frac, dt, d);
+            theq = pl.amp;
+        } else {
+            step<1>(pl, d);
+        }
+    }
+#pragma unroll UNROLL
+    for (; k < T; ++k) {
+        sink(k, d[0], theq);
+        step<1>(pl, d);
+    }
+}
+
 struct SseSinkNm {
     const R* r;
     double sse;
@@ -78,7 +122,7 @@ __device__ double nm_eval(const NmGroup& g, const R* r, const double* x, bool va
     int kmin = __builtin_amdgcn_readfirstlane(wave_min(valid ? k0 : 0x7FFFFFFF));
     int kmax = __builtin_amdgcn_readfirstlane(wave_max(valid ? k0 : -0x7FFFFFFF));
     SseSinkNm sink{r, 0.0};
-    if (valid) run_trajectory<2>(pl, sd.T, (R)dt, k0, frac, kmin, kmax, sink);
+    if (valid) run_steps<2>(pl, sd.T, (R)dt, k0, frac, kmin, kmax, sink);
     double rm = sqrt((sink.sse + q) / ((double)sd.T * sd.C));
     return (rm >= 0.0 && rm <= 1.7976931348623157e308) ? rm : INFINITY;
 }

@@ -181,7 +181,7 @@ __global__ void refine_kernel(int S, const SacDev* __restrict__ sacs, int round,
 }
 
 // ---------------------------------------------------------------------------
-// Sinks for run_trajectory
+// Sinks for run_blocks
 // ---------------------------------------------------------------------------
 
 template <class RT>
@@ -189,26 +189,25 @@ struct SseSinkT {  // squared residual against the projected trace in LDS, summe
     using A = typename Prec<RT>::acc;
     const RT* r;
     A sse;
-    __device__ __forceinline__ void operator()(int k, RT dth, RT theq)
-    {
-        RT e = (r[k] - theq) - dth;
-        sse = fmr((A)e, (A)e, sse);
-    }
+    __device__ __forceinline__ RT begin(int k, RT u) const { return r[k] - u; }
+    __device__ __forceinline__ void end(int, RT e) { sse = fmr((A)e, (A)e, sse); }
 };
 using SseSink = SseSinkT<R>;
 
 struct TrajSink {  // theta_k to global memory
     float* out;
-    __device__ __forceinline__ void operator()(int k, R dth, R theq) { out[k] = (float)(dth + theq); }
+    __device__ __forceinline__ R begin(int, R u) const { return -u; }
+    __device__ __forceinline__ void end(int k, R e) { out[k] = (float)-e; }
 };
 
 struct Cost2dSink {  // both channels, FP64 accumulation (reporting only)
     const float* pos;
     int C;
     double cphi, sphi, sq, ab;
-    __device__ __forceinline__ void operator()(int k, R dth, R theq)
+    __device__ __forceinline__ R begin(int, R u) const { return -u; }
+    __device__ __forceinline__ void end(int k, R e)
     {
-        double th = (double)(dth + theq);
+        const double th = -(double)e;
         double e0 = (double)pos[(int64_t)k * C] - th * cphi;
         sq += e0 * e0;
         ab += fabs(e0);
@@ -257,7 +256,7 @@ struct TileSmem {
 // its index in the tile (low word), or all ones for a slot past the saccade's candidates.  tmin
 // (with costs): at [tile_base + t], the bits of the tile's least FP32 sum, 0 if one is NaN, +inf
 // if the tile holds no candidate.
-template <int TPB, int PASSES, int UNROLL, class RT = R>
+template <int TPB, int PASSES, class RT = R>
 __device__ __forceinline__ uint64_t process_tile(TileSmem<TPB, PASSES, RT>& sm, const SacDev& sd, int s, int t,
                                                  int round, float dt, const float* __restrict__ proj,
                                                  const float* centre, const float* hw, const float* lo,
@@ -333,14 +332,10 @@ __device__ __forceinline__ uint64_t process_tile(TileSmem<TPB, PASSES, RT>& sm, 
         PlantT<RT> pl;
         plant_setup(p, sd.amp, dt, pl);
         RT frac;
-        int k0 = pulse_end_sample(pl.pwd, T, frac);
-        int kmin = wave_min(valid ? k0 : 0x7FFFFFFF);
-        int kmax = wave_max(valid ? k0 : -0x7FFFFFFF);
-        kmin = __builtin_amdgcn_readfirstlane(kmin);
-        kmax = __builtin_amdgcn_readfirstlane(kmax);
+        const int k0 = pulse_end_sample(pl.pwd, T, frac);
         SseSinkT<RT> sink{sm.r, 0.0};
         if (valid) {
-            run_trajectory<UNROLL>(pl, T, (RT)dt, k0, frac, kmin, kmax, sink);
+            run_blocks(pl, T, (RT)dt, k0, frac, sink);
             uint64_t key = cost_key(sink.sse, idx);
             best = key < best ? key : best;
         }
@@ -416,7 +411,7 @@ __device__ __forceinline__ int saccade_of_tile(const SacDev* __restrict__ sacs, 
 // One round over a batch: round >= 0 puts every saccade at that round with keys
 // [round][key_stride]; round < 0 takes each saccade's own round (sd.round) and
 // keys [slot] (saccades admitted at different times, see the server).
-template <int TPB, int PASSES, int UNROLL>
+template <int TPB, int PASSES>
 __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_round_kernel(const SacDev* __restrict__ sacs, int S, int round,
                                                         int key_stride, float dt, const float* __restrict__ proj,
                                                         const float* centre, const float* hw,
@@ -437,7 +432,7 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_round_kernel(const Sa
     if (status[sd.slot] & OPMM_ST_NONFINITE_INPUT) return;
     const int t = blockIdx.x - sd.tile_base;
     const int r = round >= 0 ? round : sd.round;
-    uint64_t best = process_tile<TPB, PASSES, UNROLL>(sm, sd, s, t, r, dt, proj, centre, hw, lo, hi);
+    uint64_t best = process_tile<TPB, PASSES>(sm, sd, s, t, r, dt, proj, centre, hw, lo, hi);
     if (threadIdx.x == 0 && best != ~0ull)
         atomicMin((unsigned long long*)&keys[(int64_t)(round >= 0 ? r : 0) * key_stride + sd.slot],
                   (unsigned long long)best);
@@ -445,12 +440,14 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_round_kernel(const Sa
 
 // Screened round, first pass: the round's tiles with the recurrence in FP32.  Every candidate's
 // squared-residual sum goes to costs; each saccade's FP32 best key to smin[slot].
-// With its FP32 setup and the scaled Horner transition the FP32 pass needs 125 registers, so 4
-// waves fit per SIMD; the bound only caps it at 168 (3 waves).  A 5-wave bound spills 23 registers.
+// Bound by VALU issue: the pass needs 128 registers (4 waves per SIMD) with no scratch.  The block
+// recurrence (run_blocks) took it from 0.841 to 0.708 ms per round of 256 x 65536 candidates (mean T 57),
+// 2.3 against 2.9 thousand instructions per candidate; without the pins of square_dform the post
+// piece's columns sink behind the pulse and it needs 166 registers: 3 waves, 0.820 ms.
 #ifndef OPMM_SCREEN_MIN_WAVES
-#define OPMM_SCREEN_MIN_WAVES 3
+#define OPMM_SCREEN_MIN_WAVES 4
 #endif
-template <int TPB, int PASSES, int UNROLL>
+template <int TPB, int PASSES>
 __global__ __launch_bounds__(TPB, OPMM_SCREEN_MIN_WAVES) void fit_screen_kernel(const SacDev* __restrict__ sacs, int S,
                                                          int round, float dt, const float* __restrict__ proj,
                                                          const float* centre, const float* hw, const float* lo,
@@ -470,7 +467,7 @@ __global__ __launch_bounds__(TPB, OPMM_SCREEN_MIN_WAVES) void fit_screen_kernel(
     if (status[sd.slot] & OPMM_ST_NONFINITE_INPUT) return;
     const int t = blockIdx.x - sd.tile_base;
     const uint64_t best =
-        process_tile<TPB, PASSES, UNROLL, float>(sm, sd, s_s, t, round, dt, proj, centre, hw, lo, hi, costs, tmin);
+        process_tile<TPB, PASSES, float>(sm, sd, s_s, t, round, dt, proj, centre, hw, lo, hi, costs, tmin);
     if (threadIdx.x == 0 && best != ~0ull) atomicMin((unsigned long long*)&smin[sd.slot], (unsigned long long)best);
 }
 
@@ -511,7 +508,7 @@ __global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restr
     R frac;
     const int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
     SseSink sink{r, 0.0};
-    run_trajectory<1>(pl, sd.T, (R)dt, k0, frac, k0, k0, sink);
+    run_blocks(pl, sd.T, (R)dt, k0, frac, sink);
     const double n = (double)sd.T * sd.C, q = qorth[slot];
     const double rm = sqrt((sink.sse + q) / n) + 0.5 * (double)tau;
     thr[slot] = rm <= 1e300 ? rm * rm * n - q : __builtin_inf();  // a non-finite anchor verifies all
@@ -534,7 +531,7 @@ struct VerifySmem {
 // longest trace), so that short traces leave room for more waves per CU.
 extern __shared__ R verify_trace[];
 
-template <int TILE, int UNROLL>
+template <int TILE>
 __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
     const SacDev* __restrict__ sacs, int S, int round, int key_stride, float dt, const float* __restrict__ proj,
     const float* centre, const float* hw, const float* lo, const float* hi, const int32_t* __restrict__ status,
@@ -588,14 +585,10 @@ __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
         Plant pl;
         plant_setup(p, sd.amp, dt, pl);
         R frac;
-        int k0 = pulse_end_sample(pl.pwd, T, frac);
-        int kmin = wave_min(valid ? k0 : 0x7FFFFFFF);
-        int kmax = wave_max(valid ? k0 : -0x7FFFFFFF);
-        kmin = __builtin_amdgcn_readfirstlane(kmin);
-        kmax = __builtin_amdgcn_readfirstlane(kmax);
+        const int k0 = pulse_end_sample(pl.pwd, T, frac);
         SseSink sink{r, 0.0};
         if (valid) {
-            run_trajectory<UNROLL>(pl, T, (R)dt, k0, frac, kmin, kmax, sink);
+            run_blocks(pl, T, (R)dt, k0, frac, sink);
             const uint64_t key = cost_key(sink.sse, idx);
             best = key < best ? key : best;
         }
@@ -614,7 +607,7 @@ __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
 // search its tile, marks the saccade OPMM_ST_WAIT_TIMEOUT and counts the
 // give-up in *errflag, and still counts the tile as done, so the queue drains
 // and every block exits.
-template <int TPB, int PASSES, int UNROLL>
+template <int TPB, int PASSES>
 __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_persistent_kernel(
     const SacDev* __restrict__ sacs, int S, int R, int tiles_per_round, float dt, float shrink,
     const float* __restrict__ proj, float* centre, float* hw, const float* lo, const float* hi,
@@ -664,7 +657,7 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_persistent_kernel(
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
             uint64_t best = ~0ull;
-            if (!s_gaveup) best = process_tile<TPB, PASSES, UNROLL>(sm, sd, s, t, r, dt, proj, centre, hw, lo, hi);
+            if (!s_gaveup) best = process_tile<TPB, PASSES>(sm, sd, s, t, r, dt, proj, centre, hw, lo, hi);
             if (threadIdx.x == 0) {
                 if (best != ~0ull)
                     atomicMin((unsigned long long*)&keys[(int64_t)r * S + s], (unsigned long long)best);
@@ -714,9 +707,9 @@ __global__ __launch_bounds__(64) void report_kernel(int S, const SacDev* __restr
     Plant pl;
     plant_setup(p, sd.amp, dt, pl);
     R frac;
-    int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
+    const int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
     Cost2dSink sink{tr, sd.C, sd.cphi, sd.sphi, 0.0, 0.0};
-    run_trajectory<1>(pl, sd.T, (R)dt, k0, frac, k0, k0, sink);
+    run_blocks(pl, sd.T, (R)dt, k0, frac, sink);
     if (threadIdx.x != 0) return;
     const int32_t st = status[sd.slot];
     const bool bad = (st & OPMM_ST_NONFINITE_INPUT) != 0;
@@ -744,11 +737,10 @@ __global__ __launch_bounds__(256, OPMM_MIN_WAVES) void simulate_kernel(int64_t n
     Plant pl;
     plant_setup(p, amp[ii], dt, pl);
     R frac;
-    int k0 = pulse_end_sample(pl.pwd, T, frac);
-    int kmin = wave_min(valid ? k0 : 0x7FFFFFFF), kmax = wave_max(valid ? k0 : -0x7FFFFFFF);
+    const int k0 = pulse_end_sample(pl.pwd, T, frac);
     if (!valid) return;
     TrajSink sink{traj + ii * T};
-    run_trajectory<2>(pl, T, (R)dt, k0, frac, kmin, kmax, sink);
+    run_blocks(pl, T, (R)dt, k0, frac, sink);
 }
 
 // RMSE of n candidates against one saccade, with the recurrence of precision RT (FP64: the search's
@@ -770,11 +762,10 @@ __global__ __launch_bounds__(256, OPMM_MIN_WAVES) void score_kernel(int64_t n, c
     PlantT<RT> pl;
     plant_setup(p, amp, dt, pl);
     RT frac;
-    int k0 = pulse_end_sample(pl.pwd, T, frac);
-    int kmin = wave_min(valid ? k0 : 0x7FFFFFFF), kmax = wave_max(valid ? k0 : -0x7FFFFFFF);
+    const int k0 = pulse_end_sample(pl.pwd, T, frac);
     if (!valid) return;
     SseSinkT<RT> sink{r, 0.0};
-    run_trajectory<2>(pl, T, (RT)dt, k0, frac, kmin, kmax, sink);
+    run_blocks(pl, T, (RT)dt, k0, frac, sink);
     double tot = ((double)sink.sse + qorth[0]) / ((double)T * C);
     float v = (float)sqrt(tot);
     rmse[i] = (v >= 0.0f && v <= 3.402823466e38f) ? v : __int_as_float(0x7F800000);
@@ -802,24 +793,27 @@ __global__ void candidates_kernel(uint64_t seed, uint32_t round, uint32_t idx0, 
 // Kernel shapes
 // ---------------------------------------------------------------------------
 
+// A shape is threads per block and candidates per thread.  The last number of a name told shapes apart
+// by the unroll factor of the sample-by-sample recurrence; the block recurrence has none, so
+// shapes that differ in it alone run one kernel (names and indices stay: tuner files hold them).
 struct Shape {
-    int tpb, passes, unroll;
+    int tpb, passes;
     const char* name;
 };
 const Shape kShapes[] = {
-    {256, 4, 1, "tpb256_pass4_unroll1"},
-    {256, 2, 1, "tpb256_pass2_unroll1"},
-    {256, 8, 1, "tpb256_pass8_unroll1"},
-    {128, 8, 1, "tpb128_pass8_unroll1"},
-    {256, 4, 2, "tpb256_pass4_unroll2"},
-    {256, 4, 4, "tpb256_pass4_unroll4"},
-    {64, 16, 1, "tpb64_pass16_unroll1"},
-    {256, 16, 1, "tpb256_pass16_unroll1"},
-    {128, 32, 1, "tpb128_pass32_unroll1"},
-    {256, 8, 4, "tpb256_pass8_unroll4"},
-    {256, 4, 8, "tpb256_pass4_unroll8"},
-    {64, 16, 4, "tpb64_pass16_unroll4"},
-    {128, 8, 4, "tpb128_pass8_unroll4"},
+    {256, 4, "tpb256_pass4_unroll1"},
+    {256, 2, "tpb256_pass2_unroll1"},
+    {256, 8, "tpb256_pass8_unroll1"},
+    {128, 8, "tpb128_pass8_unroll1"},
+    {256, 4, "tpb256_pass4_unroll2"},
+    {256, 4, "tpb256_pass4_unroll4"},
+    {64, 16, "tpb64_pass16_unroll1"},
+    {256, 16, "tpb256_pass16_unroll1"},
+    {128, 32, "tpb128_pass32_unroll1"},
+    {256, 8, "tpb256_pass8_unroll4"},
+    {256, 4, "tpb256_pass4_unroll8"},
+    {64, 16, "tpb64_pass16_unroll4"},
+    {128, 8, "tpb128_pass8_unroll4"},
 };
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 constexpr int kDefaultShape = 9;  // fastest per-round shape on the full-estimation workload (sweep)
@@ -863,29 +857,29 @@ struct TimedLaunch {
     }
 };
 
-template <int TPB, int PASSES, int UNROLL>
+template <int TPB, int PASSES>
 hipError_t launch_shape(const FitLaunch& L, bool persistent, int round, hipStream_t st)
 {
     TimedLaunch tl(L.timer, persistent ? OPMM_KERNEL_PERSISTENT : OPMM_KERNEL_ROUND, st);
     if (persistent) {
-        hipLaunchKernelGGL((fit_persistent_kernel<TPB, PASSES, UNROLL>), dim3(L.grid_persistent), dim3(TPB), 0,
+        hipLaunchKernelGGL((fit_persistent_kernel<TPB, PASSES>), dim3(L.grid_persistent), dim3(TPB), 0,
                            st, L.sacs, L.S, L.R, L.tiles_per_round, L.dt, L.shrink, L.proj, L.centre, L.hw,
                            L.lo, L.hi, L.status, L.keys, L.head, L.done, L.ready, L.errflag, L.ord, L.obase,
                            L.wait_limit);
     } else {
-        hipLaunchKernelGGL((fit_round_kernel<TPB, PASSES, UNROLL>), dim3(L.tiles_per_round), dim3(TPB), 0, st,
+        hipLaunchKernelGGL((fit_round_kernel<TPB, PASSES>), dim3(L.tiles_per_round), dim3(TPB), 0, st,
                            L.sacs, L.S, round, L.key_stride, L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status,
                            L.keys, L.ord, L.obase);
     }
     return hipGetLastError();
 }
 
-template <int TPB, int PASSES, int UNROLL>
+template <int TPB, int PASSES>
 hipError_t launch_screened(const FitLaunch& L, int round, hipStream_t st)
 {
     {
         TimedLaunch tl(L.timer, OPMM_KERNEL_SCREEN, st);
-        hipLaunchKernelGGL((fit_screen_kernel<TPB, PASSES, UNROLL>), dim3(L.tiles_per_round), dim3(TPB), 0, st,
+        hipLaunchKernelGGL((fit_screen_kernel<TPB, PASSES>), dim3(L.tiles_per_round), dim3(TPB), 0, st,
                            L.sacs, L.S, round, L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status, L.ord, L.obase,
                            L.costs, L.tmin, L.smin);
     }
@@ -894,7 +888,7 @@ hipError_t launch_screened(const FitLaunch& L, int round, hipStream_t st)
                        L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status, L.qorth, L.smin, L.tau, max_T, L.vthr);
     {
         TimedLaunch tl(L.timer, OPMM_KERNEL_VERIFY, st);
-        hipLaunchKernelGGL((fit_verify_kernel<TPB * PASSES, UNROLL>), dim3(L.tiles_per_round), dim3(64),
+        hipLaunchKernelGGL(fit_verify_kernel<TPB * PASSES>, dim3(L.tiles_per_round), dim3(64),
                            sizeof(R) * (size_t)max_T, st, L.sacs, L.S, round, L.key_stride, L.dt, L.proj, L.centre,
                            L.hw, L.lo, L.hi, L.status, L.keys, L.ord, L.obase, L.costs, L.tmin, L.vthr, max_T);
     }
@@ -905,46 +899,40 @@ hipError_t launch_screened(const FitLaunch& L, int round, hipStream_t st)
 hipError_t launch_screened_round(int shape, const FitLaunch& L, int round, hipStream_t st)
 {
     switch (shape) {
-    case 0: return launch_screened<256, 4, 1>(L, round, st);
-    case 1: return launch_screened<256, 2, 1>(L, round, st);
-    case 2: return launch_screened<256, 8, 1>(L, round, st);
-    case 3: return launch_screened<128, 8, 1>(L, round, st);
-    case 4: return launch_screened<256, 4, 2>(L, round, st);
-    case 5: return launch_screened<256, 4, 4>(L, round, st);
-    case 6: return launch_screened<64, 16, 1>(L, round, st);
-    case 7: return launch_screened<256, 16, 1>(L, round, st);
-    case 8: return launch_screened<128, 32, 1>(L, round, st);
-    case 9: return launch_screened<256, 8, 4>(L, round, st);
-    case 10: return launch_screened<256, 4, 8>(L, round, st);
-    case 11: return launch_screened<64, 16, 4>(L, round, st);
-    default: return launch_screened<128, 8, 4>(L, round, st);
+    case 1: return launch_screened<256, 2>(L, round, st);
+    case 2:
+    case 9: return launch_screened<256, 8>(L, round, st);
+    case 3:
+    case 12: return launch_screened<128, 8>(L, round, st);
+    case 6:
+    case 11: return launch_screened<64, 16>(L, round, st);
+    case 7: return launch_screened<256, 16>(L, round, st);
+    case 8: return launch_screened<128, 32>(L, round, st);
+    default: return launch_screened<256, 4>(L, round, st);  // 0, 4, 5, 10
     }
 }
 
 hipError_t launch_fit_kernel(int shape, const FitLaunch& L, bool persistent, int round, hipStream_t st)
 {
     switch (shape) {
-    case 0: return launch_shape<256, 4, 1>(L, persistent, round, st);
-    case 1: return launch_shape<256, 2, 1>(L, persistent, round, st);
-    case 2: return launch_shape<256, 8, 1>(L, persistent, round, st);
-    case 3: return launch_shape<128, 8, 1>(L, persistent, round, st);
-    case 4: return launch_shape<256, 4, 2>(L, persistent, round, st);
-    case 5: return launch_shape<256, 4, 4>(L, persistent, round, st);
-    case 6: return launch_shape<64, 16, 1>(L, persistent, round, st);
-    case 7: return launch_shape<256, 16, 1>(L, persistent, round, st);
-    case 8: return launch_shape<128, 32, 1>(L, persistent, round, st);
-    case 9: return launch_shape<256, 8, 4>(L, persistent, round, st);
-    case 10: return launch_shape<256, 4, 8>(L, persistent, round, st);
-    case 11: return launch_shape<64, 16, 4>(L, persistent, round, st);
-    default: return launch_shape<128, 8, 4>(L, persistent, round, st);
+    case 1: return launch_shape<256, 2>(L, persistent, round, st);
+    case 2:
+    case 9: return launch_shape<256, 8>(L, persistent, round, st);
+    case 3:
+    case 12: return launch_shape<128, 8>(L, persistent, round, st);
+    case 6:
+    case 11: return launch_shape<64, 16>(L, persistent, round, st);
+    case 7: return launch_shape<256, 16>(L, persistent, round, st);
+    case 8: return launch_shape<128, 32>(L, persistent, round, st);
+    default: return launch_shape<256, 4>(L, persistent, round, st);  // 0, 4, 5, 10
     }
 }
 
-template <int TPB, int PASSES, int UNROLL>
+template <int TPB, int PASSES>
 int persistent_blocks_per_cu()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fit_persistent_kernel<TPB, PASSES, UNROLL>, TPB, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fit_persistent_kernel<TPB, PASSES>, TPB, 0) !=
         hipSuccess)
         return 1;
     return nb > 0 ? nb : 1;
@@ -953,19 +941,16 @@ int persistent_blocks_per_cu()
 int shape_blocks_per_cu(int shape)
 {
     switch (shape) {
-    case 0: return persistent_blocks_per_cu<256, 4, 1>();
-    case 1: return persistent_blocks_per_cu<256, 2, 1>();
-    case 2: return persistent_blocks_per_cu<256, 8, 1>();
-    case 3: return persistent_blocks_per_cu<128, 8, 1>();
-    case 4: return persistent_blocks_per_cu<256, 4, 2>();
-    case 5: return persistent_blocks_per_cu<256, 4, 4>();
-    case 6: return persistent_blocks_per_cu<64, 16, 1>();
-    case 7: return persistent_blocks_per_cu<256, 16, 1>();
-    case 8: return persistent_blocks_per_cu<128, 32, 1>();
-    case 9: return persistent_blocks_per_cu<256, 8, 4>();
-    case 10: return persistent_blocks_per_cu<256, 4, 8>();
-    case 11: return persistent_blocks_per_cu<64, 16, 4>();
-    default: return persistent_blocks_per_cu<128, 8, 4>();
+    case 1: return persistent_blocks_per_cu<256, 2>();
+    case 2:
+    case 9: return persistent_blocks_per_cu<256, 8>();
+    case 3:
+    case 12: return persistent_blocks_per_cu<128, 8>();
+    case 6:
+    case 11: return persistent_blocks_per_cu<64, 16>();
+    case 7: return persistent_blocks_per_cu<256, 16>();
+    case 8: return persistent_blocks_per_cu<128, 32>();
+    default: return persistent_blocks_per_cu<256, 4>();  // 0, 4, 5, 10
     }
 }
 

@@ -8,8 +8,9 @@
 // time-invariant on each piece of the pulse-step control (pulse on [0, PW)
 // with the activation time constants, step afterwards with the deactivation
 // time constants), so one sample period dt advances the deviation from the
-// piece's equilibrium by a fixed matrix: d_{k+1} = Phi d_k.  Phi = exp(A dt) is
-// formed once per candidate in "D-form" (D = Phi - I, Taylor polynomial by
+// piece's equilibrium by a fixed matrix: d_{k+1} = Phi d_k (run_blocks advances
+// four samples at a time, with Phi^4 and the theta rows of Phi^1..Phi^3).
+// Phi = exp(A dt) is formed once per candidate in "D-form" (D = Phi - I, Taylor polynomial by
 // Horner's rule, then squarings): storing Phi - I keeps the slow modes
 // (|1 - mu| ~ 0.02 per ms) at full relative precision.  The recurrence type R
 // is FP64 by default (FP32 stays buildable); candidates are FP32.  The sample
@@ -188,8 +189,8 @@ struct PlantT {
     RT q1a, q1n, q2a, q2n;      // F rows: -1/tau, pulse (activation) and post (deactivation)
     // one-sample transition in D-form (Phi - I)
     RT m[4][4];                 // mechanical block
-    RT x1[4][2], x2[4][2];      // coupling to (F_ag, F_ant), pulse and post pieces
-    RT e1[2], e2[2];            // F decay factor minus one, pulse and post pieces
+    RT x[4][4];                 // coupling to F: pulse (ag, ant), then post (ag, ant)
+    RT e[4];                    // F decay factor minus one: pulse (ag, ant), then post (ag, ant)
     // equilibria and switching
     RT th1;                     // theta at the pulse equilibrium
     RT amp;                     // theta at the post equilibrium (= amplitude)
@@ -232,6 +233,60 @@ template <> struct LitT<float> { using type = float; };
         o2 = fmr(s22, V2, fmr(s20, V0, i2));                                               \
         o3 = fmr(s33, V3, fmr(s30, V0, i3));                                               \
     } while (0)
+
+// OPMM_KEEP(x): x is computed here.  Without it the compiler sinks what only the post piece reads (its
+// coupling columns and rows) behind the pulse loop and keeps the columns of every doubling live until
+// then: 166 registers instead of 128 in the FP32 pass, 95 spilled instead of none in the FP64 kernels
+// (FP64 round 2.32 ms against 1.42 per round of 256 x 65536 candidates).
+#ifdef __HIP_DEVICE_COMPILE__
+#define OPMM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+#define OPMM_KEEP(x) asm volatile("" : "+v"(x))
+#else
+#define OPMM_SCHED_FENCE() ((void)0)
+#define OPMM_KEEP(x) ((void)0)
+#endif
+
+// One doubling of the step in D-form, D_2h = D_h^2 + 2 D_h, of the mechanical block pm, the coupling
+// columns px and the active-state factors minus one pd.
+template <class RT>
+__device__ __forceinline__ void square_dform(RT (&pm)[4][4], RT (&px)[4][4], RT (&pd)[4])
+{
+    // the coupling columns first, one at a time and in place, then the block: at most 16 temporaries
+    // live (the scheduling barriers keep the columns apart)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        RT nx[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            RT b = px[i][c] * (pd[c] + RT(2));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b = fmr(pm[i][k], px[k][c], b);
+            nx[i] = b;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { px[i][c] = nx[i]; OPMM_KEEP(px[i][c]); }
+        pd[c] = pd[c] * (pd[c] + RT(2));
+        OPMM_KEEP(pd[c]);
+        OPMM_SCHED_FENCE();
+    }
+    RT nm[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            RT a = pm[i][c] + pm[i][c];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a = fmr(pm[i][k], pm[k][c], a);
+            nm[i][c] = a;
+        }
+    }
+    OPMM_SCHED_FENCE();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) pm[i][c] = nm[i][c];
+    }
+}
 
 // Horner evaluation of D = sum_{k=1..M} (hA)^k / k! for the augmented block
 // matrix [[Mech, G1, G2], [0, Q1, 0], [0, 0, Q2]] whose off-diagonal blocks
@@ -312,38 +367,13 @@ __device__ __forceinline__ void transition_dform(PlantT<RT>& pl, RT hfull)
         }
     }
 #pragma unroll
-    for (int q = 0; q < SQ; ++q) {
-        RT nm[4][4], nx[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                RT a = pm[i][c] + pm[i][c];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) a = fmr(pm[i][k], pm[k][c], a);
-                nm[i][c] = a;
-                RT b = px[i][c] * (pd[c] + RT(2));
-#pragma unroll
-                for (int k = 0; k < 4; ++k) b = fmr(pm[i][k], px[k][c], b);
-                nx[i][c] = b;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { pm[i][c] = nm[i][c]; px[i][c] = nx[i][c]; }
-            pd[i] = pd[i] * (pd[i] + RT(2));
-        }
-    }
+    for (int q = 0; q < SQ; ++q) square_dform(pm, px, pd);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) pl.m[i][c] = pm[i][c];
-        pl.x1[i][0] = px[i][0]; pl.x1[i][1] = px[i][1];
-        pl.x2[i][0] = px[i][2]; pl.x2[i][1] = px[i][3];
+        for (int c = 0; c < 4; ++c) { pl.m[i][c] = pm[i][c]; pl.x[i][c] = px[i][c]; }
+        pl.e[i] = pd[i];
     }
-    pl.e1[0] = pd[0]; pl.e1[1] = pd[1];
-    pl.e2[0] = pd[2]; pl.e2[1] = pd[3];
 }
 
 
@@ -437,9 +467,9 @@ __device__ __forceinline__ void plant_setup(const float p[P], float amp, float d
     pl.pwd = (double)p[17] * rcp64((double)dt);
 }
 
-// d <- Phi d for one sample (D-form: d + D d)
-template <class RT>
-__device__ __forceinline__ void step(const PlantT<RT>& pl, const RT (&x)[4][2], const RT (&e)[2], RT d[6])
+// d <- Phi d for one step of pl's transition (D-form: d + D d) in the pulse (PIECE 0) or post (1) piece
+template <int PIECE, class RT>
+__device__ __forceinline__ void step(const PlantT<RT>& pl, RT d[6])
 {
     RT n[4];
     // the row's own state is the addend of the first fma
@@ -452,11 +482,11 @@ __device__ __forceinline__ void step(const PlantT<RT>& pl, const RT (&x)[4][2], 
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             if (c != i) n[i] = fmr(pl.m[i][c], d[c], n[i]);
-        n[i] = fmr(x[i][0], d[4], n[i]);
-        n[i] = fmr(x[i][1], d[5], n[i]);
+        n[i] = fmr(pl.x[i][2 * PIECE], d[4], n[i]);
+        n[i] = fmr(pl.x[i][2 * PIECE + 1], d[5], n[i]);
     }
-    d[4] = fmr(e[0], d[4], d[4]);
-    d[5] = fmr(e[1], d[5], d[5]);
+    d[4] = fmr(pl.e[2 * PIECE], d[4], d[4]);
+    d[5] = fmr(pl.e[2 * PIECE + 1], d[5], d[5]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) d[i] = n[i];
 }
@@ -524,13 +554,53 @@ __device__ __forceinline__ int pulse_end_sample(double pw, int T, RT& frac)
     return k0;
 }
 
-// Run the trajectory theta_k, k = 0..T-1, calling sink(k, dtheta, theta_eq)
-// with theta_k = dtheta + theta_eq.  kmin/kmax: wave-uniform bounds of the
-// lanes' pulse-end samples; samples below kmin are pulse for every lane and
-// samples above kmax post for every lane, so only [kmin, kmax] branches.
-template <int UNROLL, class RT, class Sink>
-__device__ __forceinline__ void run_trajectory(const PlantT<RT>& pl, int T, RT dt, int k0, RT frac,
-                                               int kmin, int kmax, Sink& sink)
+// Samples advanced per step of the block recurrence (run_blocks).
+constexpr int BLOCK = 4;
+
+// Theta rows of the transitions over 1, 2 and 3 samples in D-form: theta_{k+j} = theta_k + row_j . d_k.
+template <class RT>
+struct ThetaRows {
+    RT m[BLOCK - 1][4];  // theta, omega, x_ag, x_ant
+    RT x[BLOCK - 1][4];  // F_ag, F_ant in the pulse piece, then in the post piece
+};
+
+// sink.begin(k, u), minus row_j . d, handed to sink.end: one sample of a block at offset j >= 1.
+template <int PIECE, class RT, class Sink>
+__device__ __forceinline__ void row_sample(const ThetaRows<RT>& rw, int j, int k, RT u, const RT d[6], Sink& sink)
+{
+    RT t = sink.begin(k, u);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t = fmr(-rw.m[j - 1][c], d[c], t);
+    t = fmr(-rw.x[j - 1][2 * PIECE], d[4], t);
+    t = fmr(-rw.x[j - 1][2 * PIECE + 1], d[5], t);
+    sink.end(k, t);
+}
+
+// One block: samples k .. k+3 from the state d at sample k, then d at sample k+4.
+template <int PIECE, class RT, class Sink>
+__device__ __forceinline__ void block_step(const PlantT<RT>& pl, const ThetaRows<RT>& rw, int k, RT theq, RT d[6],
+                                           Sink& sink)
+{
+    const RT u = d[0] + theq;
+    sink.end(k, sink.begin(k, u));
+#pragma unroll
+    for (int j = 1; j < BLOCK; ++j) row_sample<PIECE>(rw, j, k + j, u, d, sink);
+    step<PIECE>(pl, d);
+}
+
+// Run the trajectory theta_k, k = 0..T-1: for each sample, t = sink.begin(k, u) and sink.end(k, t - v)
+// with theta_k = u + v.  pl holds the one-sample transition on entry and that of a block on exit.
+//
+// Bound by VALU issue.  A block of four samples costs one step of the four-sample transition (26
+// multiply-adds) and three rows (6 each) instead of four one-sample steps: 53 operations per block with a
+// squared residual instead of 116, for the two doublings that form the block's transition (~350
+// operations, paid back from ~25 samples on).  Measured on a round of 256 x 65536 candidates (mean T 57):
+// FP32 0.841 -> 0.708 ms, FP64 1.724 -> 1.425 ms.  Blocks of two save less on long traces (18 operations
+// per sample), blocks of eight need 42 more row coefficients in registers.  The lane's blocks end at its own pulse-end sample (the first k0 mod 4
+// samples are single steps), so a candidate's arithmetic depends on the candidate alone; lanes of a
+// wave whose pulse ends differ by a block mask a block each.
+template <class RT, class Sink>
+__device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, RT dt, int k0, RT frac, Sink& sink)
 {
     RT d[6];
 #pragma unroll
@@ -541,30 +611,50 @@ __device__ __forceinline__ void run_trajectory(const PlantT<RT>& pl, int T, RT d
         for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
         theq = pl.amp;
     }
+    ThetaRows<RT> rw;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { rw.m[0][c] = pl.m[0][c]; rw.x[0][c] = pl.x[0][c]; }
+    const int np = max(k0, 0);  // samples before the pulse end (k0 <= T)
     int k = 0;
-    const int ka = min(kmin, T);
-#pragma unroll UNROLL
-    for (; k < ka; ++k) {
-        sink(k, d[0], theq);
-        step(pl, pl.x1, pl.e1, d);
-    }
-    const int kb = min(kmax, T - 1);
 #pragma unroll 1
-    for (; k <= kb; ++k) {
-        sink(k, d[0], theq);
-        if (k < k0) {
-            step(pl, pl.x1, pl.e1, d);
-        } else if (k == k0) {
-            split_step(pl, frac, dt, d);
-            theq = pl.amp;
-        } else {
-            step(pl, pl.x2, pl.e2, d);
-        }
+    for (const int head = np % BLOCK; k < head; ++k) {
+        sink.end(k, sink.begin(k, d[0] + theq));
+        step<0>(pl, d);
     }
-#pragma unroll UNROLL
-    for (; k < T; ++k) {
-        sink(k, d[0], theq);
-        step(pl, pl.x2, pl.e2, d);
+    square_dform(pl.m, pl.x, pl.e);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        rw.m[1][c] = pl.m[0][c];
+        rw.x[1][c] = pl.x[0][c];
+        // three samples: D_1 + D_2 + D_1 D_2, its theta row
+        RT a = rw.m[0][c] + rw.m[1][c], b = fmr(rw.x[0][c], pl.e[c], rw.x[0][c] + rw.x[1][c]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a = fmr(rw.m[0][i], pl.m[i][c], a);
+            b = fmr(rw.m[0][i], pl.x[i][c], b);
+        }
+        rw.m[2][c] = a;
+        rw.x[2][c] = b;
+        OPMM_KEEP(rw.x[2][c]);
+    }
+    square_dform(pl.m, pl.x, pl.e);
+#pragma unroll 1
+    for (; k < np; k += BLOCK) block_step<0>(pl, rw, k, theq, d, sink);
+    if (k0 >= 0 && k0 < T) {
+        sink.end(k, sink.begin(k, d[0] + theq));
+        split_step(pl, frac, dt, d);
+        theq = pl.amp;
+        ++k;
+    }
+#pragma unroll 1
+    for (; k + BLOCK <= T; k += BLOCK) block_step<1>(pl, rw, k, theq, d, sink);
+    // the last samples need no further state: their rows alone
+    if (k < T) {
+        const RT u = d[0] + theq;
+        sink.end(k, sink.begin(k, u));
+#pragma unroll
+        for (int j = 1; j < BLOCK - 1; ++j)
+            if (k + j < T) row_sample<1>(rw, j, k + j, u, d, sink);
     }
 }
 

@@ -678,7 +678,8 @@ __global__ __launch_bounds__(64) void features_kernel(int S, const opmm_rt::SacD
 // write the normalised target.  One sample per lane, keyed by (seed, step, i).
 struct GenSink {
     float* out;
-    __device__ __forceinline__ void operator()(int k, R dth, R theq) { out[k] = (float)(dth + theq); }
+    __device__ __forceinline__ R begin(int, R u) const { return -u; }
+    __device__ __forceinline__ void end(int k, R e) { out[k] = (float)-e; }
 };
 
 __global__ __launch_bounds__(64) void gen_batch_kernel(int B, uint64_t seed, const uint64_t* __restrict__ counter,
@@ -715,7 +716,7 @@ __global__ __launch_bounds__(64) void gen_batch_kernel(int B, uint64_t seed, con
     float* tr = trace + (int64_t)ii * MAX_T_GEN;
     GenSink sink{tr};
     if (!valid) return;
-    run_trajectory<1>(pl, T, (R)1.0, k0, frac, k0, k0, sink);
+    run_blocks(pl, T, (R)1.0, k0, frac, sink);
     for (int k = 0; k < T; k += 2) {  // Box-Muller pairs
         float u1 = fmaxf(uni(32 + k), 0x1p-25f), u2 = uni(33 + k);
         float rad = sqrtf(-2.0f * logf(u1));
