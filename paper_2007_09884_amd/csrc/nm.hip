@@ -49,18 +49,229 @@ struct NmGroup {
     int iters;         // iterations taken (set when the task stops)
 };
 
-// Run the trajectory theta_k, k = 0..T-1, sample by sample, calling sink(k, dtheta, theta_eq)
+// The simplex's iterates depend on every rounding of its costs, so this file keeps the sample-by-sample
+// evaluation its results are defined by: the transition by Horner's rule on matrices and one step per
+// sample (run_blocks in plant.hpp gives the same trajectories to ~1e-14 deg).
+struct NmPlant {
+    R a10, a11, a12, a13;       // per ms; omega row: theta, omega, x_ag, x_ant
+    R a20, a22, g2;             // x_ag row: theta, x_ag, F_ag
+    R a30, a33, g3;             // x_ant row: theta, x_ant, F_ant
+    R q1a, q1n, q2a, q2n;       // F rows: -1/tau, pulse (activation) and post (deactivation)
+    R m[4][4], x1[4][2], x2[4][2], e1[2], e2[2];  // one-sample transition in D-form (Phi - I), both pieces
+    R th1, amp, sh[6], d0[6];   // equilibria (theta), pulse minus post, rest minus pulse
+    double pwd;                 // PW in sample periods
+};
+
+// mechanical rows of (s*A) V, plus `acc` on the diagonal of column `diag` (-1: none)
+#define OPMM_MV(s10, s11, s12, s13, s20, s22, s30, s33, sv, V0, V1, V2, V3, o0, o1, o2, o3, i0, i1, i2, i3) \
+    do {                                                                                               \
+        o0 = fmr(sv, V1, i0);                                                                    \
+        o1 = fmr(s13, V3, fmr(s12, V2, fmr(s11, V1, fmr(s10, V0, i1))));       \
+        o2 = fmr(s22, V2, fmr(s20, V0, i2));                                               \
+        o3 = fmr(s33, V3, fmr(s30, V0, i3));                                               \
+    } while (0)
+
+// Horner evaluation of D = sum_{k=1..M} (hA)^k / k! for the augmented block
+// matrix [[Mech, G1, G2], [0, Q1, 0], [0, 0, Q2]] whose off-diagonal blocks
+// give the pulse-piece and post-piece coupling columns at once, on the step
+// h/2^SQ, then SQ squarings in D-form: D_2h = D_h^2 + 2 D_h.  The Horner
+// iterates P_k = I + (B/k) P_{k+1} (B = hA) are carried scaled, Q_k = c_k P_k
+// with c_M = M and c_k = k c_{k+1}: then Q_M = M I + B, Q_k = c_k I + B Q_{k+1}
+// and D = B Q_2 / M!, so the entries of B are formed once instead of once per
+// step (fewer instructions and fewer live registers).
+__device__ __forceinline__ void transition_dform(NmPlant& pl, R hfull)
+{
+    constexpr int M = Prec<R>::taylor_m, SQ = Prec<R>::taylor_sq;
+    const R h = hfull * (R(1) / R(1 << SQ));
+    const R qv[4] = {pl.q1a, pl.q1n, pl.q2a, pl.q2n};
+    const R s10 = pl.a10 * h, s11 = pl.a11 * h, s12 = pl.a12 * h, s13 = pl.a13 * h;
+    const R s20 = pl.a20 * h, s22 = pl.a22 * h, s30 = pl.a30 * h, s33 = pl.a33 * h;
+    const R sg2 = pl.g2 * h, sg3 = pl.g3 * h;
+    R sq[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sq[c] = qv[c] * h;
+    R pm[4][4], px[4][4], pd[4];
+    {   // Q_M = M I + B
+        const R m = R(M);
+        pm[0][0] = m;   pm[0][1] = h;      pm[0][2] = R(0);    pm[0][3] = R(0);
+        pm[1][0] = s10; pm[1][1] = m + s11; pm[1][2] = s12;     pm[1][3] = s13;
+        pm[2][0] = s20; pm[2][1] = R(0);  pm[2][2] = m + s22;  pm[2][3] = R(0);
+        pm[3][0] = s30; pm[3][1] = R(0);  pm[3][2] = R(0);    pm[3][3] = m + s33;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            px[0][c] = R(0); px[1][c] = R(0);
+            px[2][c] = (c & 1) ? R(0) : sg2;
+            px[3][c] = (c & 1) ? sg3 : R(0);
+            pd[c] = m + sq[c];
+        }
+    }
+    R ck = R(M);
+#pragma unroll
+    for (int k = M - 1; k >= 1; --k) {
+        // k >= 2: Q_k = c_k I + B Q_{k+1};  k == 1: D = (B / M!) Q_2
+        R one, t10, t11, t12, t13, t20, t22, t30, t33, tv, tg2, tg3, tq[4];
+        if (k >= 2) {
+            ck = ck * R(k);
+            one = ck;
+            t10 = s10; t11 = s11; t12 = s12; t13 = s13; t20 = s20; t22 = s22; t30 = s30; t33 = s33;
+            tv = h; tg2 = sg2; tg3 = sg3;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) tq[c] = sq[c];
+        } else {
+            const R f = R(1) / ck;  // 1 / M!, rounded once
+            one = R(0);
+            t10 = s10 * f; t11 = s11 * f; t12 = s12 * f; t13 = s13 * f;
+            t20 = s20 * f; t22 = s22 * f; t30 = s30 * f; t33 = s33 * f;
+            tv = h * f; tg2 = sg2 * f; tg3 = sg3 * f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) tq[c] = sq[c] * f;
+        }
+        R nm[4][4], nx[4][4], nd[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            OPMM_MV(t10, t11, t12, t13, t20, t22, t30, t33, tv, pm[0][c], pm[1][c], pm[2][c], pm[3][c],
+                    nm[0][c], nm[1][c], nm[2][c], nm[3][c],
+                    c == 0 ? one : R(0), c == 1 ? one : R(0), c == 2 ? one : R(0), c == 3 ? one : R(0));
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const R ga = (c & 1) ? R(0) : tg2 * pd[c];
+            const R gn = (c & 1) ? tg3 * pd[c] : R(0);
+            OPMM_MV(t10, t11, t12, t13, t20, t22, t30, t33, tv, px[0][c], px[1][c], px[2][c], px[3][c],
+                    nx[0][c], nx[1][c], nx[2][c], nx[3][c], R(0), R(0), ga, gn);
+            nd[c] = fmr(tq[c], pd[c], one);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { pm[i][c] = nm[i][c]; px[i][c] = nx[i][c]; }
+            pd[i] = nd[i];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < SQ; ++q) {
+        R nm[4][4], nx[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                R a = pm[i][c] + pm[i][c];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) a = fmr(pm[i][k], pm[k][c], a);
+                nm[i][c] = a;
+                R b = px[i][c] * (pd[c] + R(2));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) b = fmr(pm[i][k], px[k][c], b);
+                nx[i][c] = b;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { pm[i][c] = nm[i][c]; px[i][c] = nx[i][c]; }
+            pd[i] = pd[i] * (pd[i] + R(2));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) pl.m[i][c] = pm[i][c];
+        pl.x1[i][0] = px[i][0]; pl.x1[i][1] = px[i][1];
+        pl.x2[i][0] = px[i][2]; pl.x2[i][1] = px[i][3];
+    }
+    pl.e1[0] = pd[0]; pl.e1[1] = pd[1];
+    pl.e2[0] = pd[2]; pl.e2[1] = pd[3];
+}
+
+
+__device__ __forceinline__ void nm_setup(const float p[P], float amp, float dt, NmPlant& pl)
+{
+    double pd[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) pd[j] = p[j];
+    PlantScalars<double> c;
+    plant_scalars(pd, (double)amp, c);
+    pl.a10 = c.a10; pl.a11 = c.a11; pl.a12 = c.a12; pl.a13 = c.a13;
+    pl.a20 = c.a20; pl.a22 = c.a22; pl.g2 = c.g2;
+    pl.a30 = c.a30; pl.a33 = c.a33; pl.g3 = c.g3;
+    pl.q1a = c.q1a; pl.q1n = c.q1n; pl.q2a = c.q2a; pl.q2n = c.q2n;
+    transition_dform(pl, (R)dt);
+    pl.th1 = c.th1;
+    pl.amp = amp;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) { pl.d0[i] = c.d0[i]; pl.sh[i] = c.sh[i]; }
+    pl.pwd = (double)p[17] * rcp64((double)dt);
+}
+
+// d <- Phi d for one sample (D-form: d + D d)
+__device__ __forceinline__ void step(const NmPlant& pl, const R (&x)[4][2], const R (&e)[2], R d[6])
+{
+    R n[4];
+    // the row's own state is the addend of the first fma
+    n[0] = fmr(pl.m[0][0], d[0], d[0]);
+    n[1] = fmr(pl.m[1][1], d[1], d[1]);
+    n[2] = fmr(pl.m[2][2], d[2], d[2]);
+    n[3] = fmr(pl.m[3][3], d[3], d[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (c != i) n[i] = fmr(pl.m[i][c], d[c], n[i]);
+        n[i] = fmr(x[i][0], d[4], n[i]);
+        n[i] = fmr(x[i][1], d[5], n[i]);
+    }
+    d[4] = fmr(e[0], d[4], d[4]);
+    d[5] = fmr(e[1], d[5], d[5]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = n[i];
+}
+
+// v <- exp(A t) v by a Taylor polynomial (degree Prec::expmv_m) in Horner form (t <= dt).
+__device__ __forceinline__ void expmv(const NmPlant& pl, R qa, R qn, R t, R v[6])
+{
+    R w[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[i] = v[i];
+#pragma unroll
+    for (int k = Prec<R>::expmv_m; k >= 1; --k) {
+        R s = t * (R(1) / R(k));
+        asm volatile("" : "+v"(s));
+        R aw[6];
+        aw[0] = w[1];
+        aw[1] = fmr(pl.a13, w[3], fmr(pl.a12, w[2], fmr(pl.a11, w[1], pl.a10 * w[0])));
+        aw[2] = fmr(pl.g2, w[4], fmr(pl.a22, w[2], pl.a20 * w[0]));
+        aw[3] = fmr(pl.g3, w[5], fmr(pl.a33, w[3], pl.a30 * w[0]));
+        aw[4] = qa * w[4];
+        aw[5] = qn * w[5];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) w[i] = fmr(s, aw[i], v[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) v[i] = w[i];
+}
+
+// The sample that contains the pulse end: pulse dynamics for frac*dt, switch
+// to the post piece's coordinates, post dynamics for the rest of the sample.
+__device__ __forceinline__ void split_step(const NmPlant& pl, R frac, R dt, R d[6])
+{
+    expmv(pl, pl.q1a, pl.q1n, frac * dt, d);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
+    expmv(pl, pl.q2a, pl.q2n, (R(1) - frac) * dt, d);
+}
+
+// Run the trajectory theta_k, k = 0..T-1, calling sink(k, dtheta, theta_eq)
 // with theta_k = dtheta + theta_eq.  kmin/kmax: wave-uniform bounds of the
 // lanes' pulse-end samples; samples below kmin are pulse for every lane and
 // samples above kmax post for every lane, so only [kmin, kmax] branches.
-template <int UNROLL, class RT, class Sink>
-__device__ __forceinline__ void run_steps(const PlantT<RT>& pl, int T, RT dt, int k0, RT frac,
+template <int UNROLL, class Sink>
+__device__ __forceinline__ void run_steps(const NmPlant& pl, int T, R dt, int k0, R frac,
                                                int kmin, int kmax, Sink& sink)
 {
-    RT d[6];
+    R d[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) d[i] = pl.d0[i];
-    RT theq = pl.th1;
+    R theq = pl.th1;
     if (k0 < 0) {  // PW <= 0: no pulse, the step acts from t = 0
 #pragma unroll
         for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
@@ -71,25 +282,25 @@ __device__ __forceinline__ void run_steps(const PlantT<RT>& pl, int T, RT dt, in
 #pragma unroll UNROLL
     for (; k < ka; ++k) {
         sink(k, d[0], theq);
-        step<0>(pl, d);
+        step(pl, pl.x1, pl.e1, d);
     }
     const int kb = min(kmax, T - 1);
 #pragma unroll 1
     for (; k <= kb; ++k) {
         sink(k, d[0], theq);
         if (k < k0) {
-            step<0>(pl, d);
+            step(pl, pl.x1, pl.e1, d);
         } else if (k == k0) {
             split_step(pl, frac, dt, d);
             theq = pl.amp;
         } else {
-            step<1>(pl, d);
+            step(pl, pl.x2, pl.e2, d);
         }
     }
 #pragma unroll UNROLL
     for (; k < T; ++k) {
         sink(k, d[0], theq);
-        step<1>(pl, d);
+        step(pl, pl.x2, pl.e2, d);
     }
 }
 
@@ -115,8 +326,8 @@ __device__ double nm_eval(const NmGroup& g, const R* r, const double* x, bool va
         v = fmin(fmax(v, lo), hi);
         p[j] = (float)(v * g.nom[j]);
     }
-    Plant pl;
-    plant_setup(p, sd.amp, dt, pl);
+    NmPlant pl;
+    nm_setup(p, sd.amp, dt, pl);
     R frac;
     int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
     int kmin = __builtin_amdgcn_readfirstlane(wave_min(valid ? k0 : 0x7FFFFFFF));

@@ -335,7 +335,7 @@ __device__ __forceinline__ uint64_t process_tile(TileSmem<TPB, PASSES, RT>& sm, 
         const int k0 = pulse_end_sample(pl.pwd, T, frac);
         SseSinkT<RT> sink{sm.r, 0.0};
         if (valid) {
-            run_blocks(pl, T, (RT)dt, k0, frac, sink);
+            run_blocks(pl, T, k0, frac, sink);
             uint64_t key = cost_key(sink.sse, idx);
             best = key < best ? key : best;
         }
@@ -440,10 +440,8 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_round_kernel(const Sa
 
 // Screened round, first pass: the round's tiles with the recurrence in FP32.  Every candidate's
 // squared-residual sum goes to costs; each saccade's FP32 best key to smin[slot].
-// Bound by VALU issue: the pass needs 128 registers (4 waves per SIMD) with no scratch.  The block
-// recurrence (run_blocks) took it from 0.841 to 0.708 ms per round of 256 x 65536 candidates (mean T 57),
-// 2.3 against 2.9 thousand instructions per candidate; without the pins of square_dform the post
-// piece's columns sink behind the pulse and it needs 166 registers: 3 waves, 0.820 ms.
+// Bound by VALU issue at 4 waves per SIMD: 128 registers, 8 spilled around the setup; a 3-wave bound
+// spills none and is 2 % slower over a fit (7.91 against 8.06 ms for 256 x 65536 x 10).
 #ifndef OPMM_SCREEN_MIN_WAVES
 #define OPMM_SCREEN_MIN_WAVES 4
 #endif
@@ -508,7 +506,7 @@ __global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restr
     R frac;
     const int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
     SseSink sink{r, 0.0};
-    run_blocks(pl, sd.T, (R)dt, k0, frac, sink);
+    run_blocks(pl, sd.T, k0, frac, sink);
     const double n = (double)sd.T * sd.C, q = qorth[slot];
     const double rm = sqrt((sink.sse + q) / n) + 0.5 * (double)tau;
     thr[slot] = rm <= 1e300 ? rm * rm * n - q : __builtin_inf();  // a non-finite anchor verifies all
@@ -588,7 +586,7 @@ __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
         const int k0 = pulse_end_sample(pl.pwd, T, frac);
         SseSink sink{r, 0.0};
         if (valid) {
-            run_blocks(pl, T, (R)dt, k0, frac, sink);
+            run_blocks(pl, T, k0, frac, sink);
             const uint64_t key = cost_key(sink.sse, idx);
             best = key < best ? key : best;
         }
@@ -709,7 +707,7 @@ __global__ __launch_bounds__(64) void report_kernel(int S, const SacDev* __restr
     R frac;
     const int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
     Cost2dSink sink{tr, sd.C, sd.cphi, sd.sphi, 0.0, 0.0};
-    run_blocks(pl, sd.T, (R)dt, k0, frac, sink);
+    run_blocks(pl, sd.T, k0, frac, sink);
     if (threadIdx.x != 0) return;
     const int32_t st = status[sd.slot];
     const bool bad = (st & OPMM_ST_NONFINITE_INPUT) != 0;
@@ -740,7 +738,7 @@ __global__ __launch_bounds__(256, OPMM_MIN_WAVES) void simulate_kernel(int64_t n
     const int k0 = pulse_end_sample(pl.pwd, T, frac);
     if (!valid) return;
     TrajSink sink{traj + ii * T};
-    run_blocks(pl, T, (R)dt, k0, frac, sink);
+    run_blocks(pl, T, k0, frac, sink);
 }
 
 // RMSE of n candidates against one saccade, with the recurrence of precision RT (FP64: the search's
@@ -765,7 +763,7 @@ __global__ __launch_bounds__(256, OPMM_MIN_WAVES) void score_kernel(int64_t n, c
     const int k0 = pulse_end_sample(pl.pwd, T, frac);
     if (!valid) return;
     SseSinkT<RT> sink{r, 0.0};
-    run_blocks(pl, T, (RT)dt, k0, frac, sink);
+    run_blocks(pl, T, k0, frac, sink);
     double tot = ((double)sink.sse + qorth[0]) / ((double)T * C);
     float v = (float)sqrt(tot);
     rmse[i] = (v >= 0.0f && v <= 3.402823466e38f) ? v : __int_as_float(0x7F800000);

@@ -10,9 +10,10 @@
 // time constants), so one sample period dt advances the deviation from the
 // piece's equilibrium by a fixed matrix: d_{k+1} = Phi d_k (run_blocks advances
 // four samples at a time, with Phi^4 and the theta rows of Phi^1..Phi^3).
-// Phi = exp(A dt) is formed once per candidate in "D-form" (D = Phi - I, Taylor polynomial by
-// Horner's rule, then squarings): storing Phi - I keeps the slow modes
-// (|1 - mu| ~ 0.02 per ms) at full relative precision.  The recurrence type R
+// Phi = exp(A dt) is a Taylor polynomial of A on a fraction of the sample, doubled
+// up to it, carried as a polynomial of degree 3 in A ("Transitions as
+// polynomials" below) in "D-form", D = Phi - I: storing Phi - I keeps the slow
+// modes (|1 - mu| ~ 0.02 per ms) at full relative precision.  The recurrence type R
 // is FP64 by default (FP32 stays buildable); candidates are FP32.  The sample
 // that contains the pulse end is split exactly at PW with two Taylor
 // exponential-vector products.
@@ -23,6 +24,16 @@
 namespace opmm {
 
 constexpr int P = 18;
+
+// OPMM_KEEP(x): x is computed here.  Without it the compiler sinks what only the post piece reads (its
+// coupling columns and rows) behind the pulse loop and keeps their operands live until then (with
+// the doublings on matrices: 166 registers instead of 128 in the FP32 pass, 95 spilled instead of none
+// in the FP64 kernels, an FP64 round of 256 x 65536 candidates 2.32 ms instead of 1.42).
+#ifdef __HIP_DEVICE_COMPILE__
+#define OPMM_KEEP(x) asm volatile("" : "+v"(x))
+#else
+#define OPMM_KEEP(x) ((void)0)
+#endif
 
 // Precision of the per-sample recurrence and of the transition matrix.
 #ifndef OPMM_REC_T
@@ -151,9 +162,11 @@ __device__ __forceinline__ void draw_candidate(uint64_t seed, uint32_t round, ui
 {
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        uint64_t z = splitmix64(seed, stream_counter(round, idx, k));
+        const uint64_t z = splitmix64(seed, stream_counter(round, idx, k));
         uint32_t ua = (uint32_t)(z >> 40);
-        uint32_t ub = (uint32_t)(z >> 16) & 0xFFFFFFu;
+        // seen as a shifted 64-bit value, ua would be converted to float as one (five more instructions a draw)
+        OPMM_KEEP(ua);
+        const uint32_t ub = (uint32_t)(z >> 16) & 0xFFFFFFu;
         p[2 * k] = box_draw(ua, b.c[2 * k], b.w[2 * k], b.lo[2 * k], b.hi[2 * k]);
         p[2 * k + 1] = box_draw(ub, b.c[2 * k + 1], b.w[2 * k + 1], b.lo[2 * k + 1], b.hi[2 * k + 1]);
     }
@@ -182,12 +195,12 @@ __device__ __forceinline__ float draw_pw(uint64_t seed, uint32_t round, uint32_t
 
 template <class RT>
 struct PlantT {
-    // continuous-time system matrix entries (per ms); theta' = omega is implicit
+    // system matrix entries per base step, omega per base step; theta' = omega is implicit
     RT a10, a11, a12, a13;      // omega row: theta, omega, x_ag, x_ant
     RT a20, a22, g2;            // x_ag row: theta, x_ag, F_ag
     RT a30, a33, g3;            // x_ant row: theta, x_ant, F_ant
-    RT q1a, q1n, q2a, q2n;      // F rows: -1/tau, pulse (activation) and post (deactivation)
-    // one-sample transition in D-form (Phi - I)
+    RT q[4];                    // F rows: -1/tau; pulse (ag, ant: activation), then post (deactivation)
+    // transition of a number of samples in D-form (Phi - I), see run_blocks
     RT m[4][4];                 // mechanical block
     RT x[4][4];                 // coupling to F: pulse (ag, ant), then post (ag, ant)
     RT e[4];                    // F decay factor minus one: pulse (ag, ant), then post (ag, ant)
@@ -224,158 +237,6 @@ __device__ __forceinline__ float rcp64(float x)
 // types, FP64 for the dual numbers of the sensitivity pass.
 template <class S> struct LitT { using type = double; };
 template <> struct LitT<float> { using type = float; };
-
-// mechanical rows of (s*A) V, plus `acc` on the diagonal of column `diag` (-1: none)
-#define OPMM_MV(s10, s11, s12, s13, s20, s22, s30, s33, sv, V0, V1, V2, V3, o0, o1, o2, o3, i0, i1, i2, i3) \
-    do {                                                                                               \
-        o0 = fmr(sv, V1, i0);                                                                    \
-        o1 = fmr(s13, V3, fmr(s12, V2, fmr(s11, V1, fmr(s10, V0, i1))));       \
-        o2 = fmr(s22, V2, fmr(s20, V0, i2));                                               \
-        o3 = fmr(s33, V3, fmr(s30, V0, i3));                                               \
-    } while (0)
-
-// OPMM_KEEP(x): x is computed here.  Without it the compiler sinks what only the post piece reads (its
-// coupling columns and rows) behind the pulse loop and keeps the columns of every doubling live until
-// then: 166 registers instead of 128 in the FP32 pass, 95 spilled instead of none in the FP64 kernels
-// (FP64 round 2.32 ms against 1.42 per round of 256 x 65536 candidates).
-#ifdef __HIP_DEVICE_COMPILE__
-#define OPMM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
-#define OPMM_KEEP(x) asm volatile("" : "+v"(x))
-#else
-#define OPMM_SCHED_FENCE() ((void)0)
-#define OPMM_KEEP(x) ((void)0)
-#endif
-
-// One doubling of the step in D-form, D_2h = D_h^2 + 2 D_h, of the mechanical block pm, the coupling
-// columns px and the active-state factors minus one pd.
-template <class RT>
-__device__ __forceinline__ void square_dform(RT (&pm)[4][4], RT (&px)[4][4], RT (&pd)[4])
-{
-    // the coupling columns first, one at a time and in place, then the block: at most 16 temporaries
-    // live (the scheduling barriers keep the columns apart)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        RT nx[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            RT b = px[i][c] * (pd[c] + RT(2));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) b = fmr(pm[i][k], px[k][c], b);
-            nx[i] = b;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { px[i][c] = nx[i]; OPMM_KEEP(px[i][c]); }
-        pd[c] = pd[c] * (pd[c] + RT(2));
-        OPMM_KEEP(pd[c]);
-        OPMM_SCHED_FENCE();
-    }
-    RT nm[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            RT a = pm[i][c] + pm[i][c];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a = fmr(pm[i][k], pm[k][c], a);
-            nm[i][c] = a;
-        }
-    }
-    OPMM_SCHED_FENCE();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) pm[i][c] = nm[i][c];
-    }
-}
-
-// Horner evaluation of D = sum_{k=1..M} (hA)^k / k! for the augmented block
-// matrix [[Mech, G1, G2], [0, Q1, 0], [0, 0, Q2]] whose off-diagonal blocks
-// give the pulse-piece and post-piece coupling columns at once, on the step
-// h/2^SQ, then SQ squarings in D-form: D_2h = D_h^2 + 2 D_h.  The Horner
-// iterates P_k = I + (B/k) P_{k+1} (B = hA) are carried scaled, Q_k = c_k P_k
-// with c_M = M and c_k = k c_{k+1}: then Q_M = M I + B, Q_k = c_k I + B Q_{k+1}
-// and D = B Q_2 / M!, so the entries of B are formed once instead of once per
-// step (fewer instructions and fewer live registers).
-template <class RT>
-__device__ __forceinline__ void transition_dform(PlantT<RT>& pl, RT hfull)
-{
-    constexpr int M = Prec<RT>::taylor_m, SQ = Prec<RT>::taylor_sq;
-    const RT h = hfull * (RT(1) / RT(1 << SQ));
-    const RT qv[4] = {pl.q1a, pl.q1n, pl.q2a, pl.q2n};
-    const RT s10 = pl.a10 * h, s11 = pl.a11 * h, s12 = pl.a12 * h, s13 = pl.a13 * h;
-    const RT s20 = pl.a20 * h, s22 = pl.a22 * h, s30 = pl.a30 * h, s33 = pl.a33 * h;
-    const RT sg2 = pl.g2 * h, sg3 = pl.g3 * h;
-    RT sq[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) sq[c] = qv[c] * h;
-    RT pm[4][4], px[4][4], pd[4];
-    {   // Q_M = M I + B
-        const RT m = RT(M);
-        pm[0][0] = m;   pm[0][1] = h;      pm[0][2] = RT(0);    pm[0][3] = RT(0);
-        pm[1][0] = s10; pm[1][1] = m + s11; pm[1][2] = s12;     pm[1][3] = s13;
-        pm[2][0] = s20; pm[2][1] = RT(0);  pm[2][2] = m + s22;  pm[2][3] = RT(0);
-        pm[3][0] = s30; pm[3][1] = RT(0);  pm[3][2] = RT(0);    pm[3][3] = m + s33;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            px[0][c] = RT(0); px[1][c] = RT(0);
-            px[2][c] = (c & 1) ? RT(0) : sg2;
-            px[3][c] = (c & 1) ? sg3 : RT(0);
-            pd[c] = m + sq[c];
-        }
-    }
-    RT ck = RT(M);
-#pragma unroll
-    for (int k = M - 1; k >= 1; --k) {
-        // k >= 2: Q_k = c_k I + B Q_{k+1};  k == 1: D = (B / M!) Q_2
-        RT one, t10, t11, t12, t13, t20, t22, t30, t33, tv, tg2, tg3, tq[4];
-        if (k >= 2) {
-            ck = ck * RT(k);
-            one = ck;
-            t10 = s10; t11 = s11; t12 = s12; t13 = s13; t20 = s20; t22 = s22; t30 = s30; t33 = s33;
-            tv = h; tg2 = sg2; tg3 = sg3;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) tq[c] = sq[c];
-        } else {
-            const RT f = RT(1) / ck;  // 1 / M!, rounded once
-            one = RT(0);
-            t10 = s10 * f; t11 = s11 * f; t12 = s12 * f; t13 = s13 * f;
-            t20 = s20 * f; t22 = s22 * f; t30 = s30 * f; t33 = s33 * f;
-            tv = h * f; tg2 = sg2 * f; tg3 = sg3 * f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) tq[c] = sq[c] * f;
-        }
-        RT nm[4][4], nx[4][4], nd[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            OPMM_MV(t10, t11, t12, t13, t20, t22, t30, t33, tv, pm[0][c], pm[1][c], pm[2][c], pm[3][c],
-                    nm[0][c], nm[1][c], nm[2][c], nm[3][c],
-                    c == 0 ? one : RT(0), c == 1 ? one : RT(0), c == 2 ? one : RT(0), c == 3 ? one : RT(0));
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const RT ga = (c & 1) ? RT(0) : tg2 * pd[c];
-            const RT gn = (c & 1) ? tg3 * pd[c] : RT(0);
-            OPMM_MV(t10, t11, t12, t13, t20, t22, t30, t33, tv, px[0][c], px[1][c], px[2][c], px[3][c],
-                    nx[0][c], nx[1][c], nx[2][c], nx[3][c], RT(0), RT(0), ga, gn);
-            nd[c] = fmr(tq[c], pd[c], one);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { pm[i][c] = nm[i][c]; px[i][c] = nx[i][c]; }
-            pd[i] = nd[i];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < SQ; ++q) square_dform(pm, px, pd);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) { pl.m[i][c] = pm[i][c]; pl.x[i][c] = px[i][c]; }
-        pl.e[i] = pd[i];
-    }
-}
-
 
 // Continuous-time coefficients (per ms) and the statics of candidate p for a
 // saccade of amplitude amp (deg): the matrix entries of the mechanical block,
@@ -441,8 +302,9 @@ __device__ __forceinline__ void plant_scalars(const S p[P], S amp, PlantScalars<
     o.sh[4] = ns_a - fa2; o.sh[5] = ns_n - fn2;
 }
 
-// Coefficients, transition and equilibria of candidate p for a saccade of
-// amplitude amp (deg), sample period dt (ms).  The scalar part is formed in ST
+// Coefficients and equilibria of candidate p for a saccade of amplitude amp
+// (deg), sample period dt (ms), in units of the base step dt / 2^taylor_sq
+// (omega included: rest and equilibria have none, so no state is rescaled).  The scalar part is formed in ST
 // and rounded once to RT.  FP32 chains of reciprocals shift the equilibria by
 // a few ulps of ~10 deg, i.e. ~1e-6 deg on every sample: below the FP32
 // recurrence's own error, and a bias the FP64 recurrence does not take.
@@ -454,17 +316,222 @@ __device__ __forceinline__ void plant_setup(const float p[P], float amp, float d
     for (int j = 0; j < P; ++j) pd[j] = p[j];
     PlantScalars<ST> c;
     plant_scalars(pd, (ST)amp, c);
-    pl.a10 = (RT)c.a10; pl.a11 = (RT)c.a11; pl.a12 = (RT)c.a12; pl.a13 = (RT)c.a13;
-    pl.a20 = (RT)c.a20; pl.a22 = (RT)c.a22; pl.g2 = (RT)c.g2;
-    pl.a30 = (RT)c.a30; pl.a33 = (RT)c.a33; pl.g3 = (RT)c.g3;
-    pl.q1a = (RT)c.q1a; pl.q1n = (RT)c.q1n; pl.q2a = (RT)c.q2a; pl.q2n = (RT)c.q2n;
-    transition_dform(pl, (RT)dt);
+    const RT h = (RT)dt * (RT(1) / RT(1 << Prec<RT>::taylor_sq));
+    pl.a10 = (RT)c.a10 * (h * h); pl.a11 = (RT)c.a11 * h; pl.a12 = (RT)c.a12 * (h * h); pl.a13 = (RT)c.a13 * (h * h);
+    pl.a20 = (RT)c.a20 * h; pl.a22 = (RT)c.a22 * h; pl.g2 = (RT)c.g2 * h;
+    pl.a30 = (RT)c.a30 * h; pl.a33 = (RT)c.a33 * h; pl.g3 = (RT)c.g3 * h;
+    pl.q[0] = (RT)c.q1a * h; pl.q[1] = (RT)c.q1n * h; pl.q[2] = (RT)c.q2a * h; pl.q[3] = (RT)c.q2n * h;
     pl.th1 = (RT)c.th1;
     pl.amp = amp;
 #pragma unroll
     for (int i = 0; i < 6; ++i) { pl.d0[i] = (RT)c.d0[i]; pl.sh[i] = (RT)c.sh[i]; }
     pl.pw = p[17];
     pl.pwd = (double)p[17] * rcp64((double)dt);
+}
+
+// ---------------------------------------------------------------------------
+// Transitions as polynomials
+// ---------------------------------------------------------------------------
+// In units of a base step (time in steps, omega per step; see plant_setup) let B be the mechanical block.
+// Every transition D = Phi - I over whole steps is F(B) for a polynomial F, and by Cayley-Hamilton that of
+// degree 3 which F leaves modulo the characteristic polynomial chi(z) = z^4 - c3 z^3 - c2 z^2 - c1 z - c0 of
+// B: four numbers a[] instead of a matrix.  The coupling column of an active state with rate q is the
+// divided difference (F(B) - F(q)) / (B - q) g = (a-part + s Q(B)) g, with Q = (chi(z) - chi(q)) / (z - q) and
+// s the value at q of the quotient of F by chi, so each rate carries s and f = F(q): no division, and
+// nothing singular where a rate meets an eigenvalue.  Doubling a step costs ~60 operations here and
+// 172 on matrices, and B is sparse enough that F(B)'s entries are short closed forms.  The Taylor
+// polynomial, the base step and so the truncation are those of a Horner evaluation on matrices; the
+// rounding is a few units (relative rms of the FP32 entries 4e-8 to 1.3e-7, Horner's 6e-8 to 1.4e-7).
+template <class RT>
+struct PolyBasis {
+    RT c0, c1, c2, c3;  // chi
+    RT u, v;            // a12 a20, a13 a30
+};
+
+template <class RT>
+struct Poly {
+    RT a[4];        // F modulo chi
+    RT s[4], f[4];  // per rate (pulse ag, ant, post ag, ant): the quotient's value and F
+};
+
+template <class RT>
+__device__ __forceinline__ void poly_basis(const PlantT<RT>& pl, PolyBasis<RT>& b)
+{
+    b.u = pl.a20 * pl.a12;
+    b.v = pl.a30 * pl.a13;
+    const RT sg = pl.a22 + pl.a33, pi = pl.a22 * pl.a33;
+    b.c3 = pl.a11 + sg;
+    b.c2 = fmr(-pl.a11, sg, pl.a10 - pi);
+    b.c1 = fmr(pl.a11, pi, fmr(-pl.a10, sg, b.u + b.v));
+    b.c0 = fmr(pl.a10, pi, fmr(-b.u, pl.a33, -b.v * pl.a22));
+}
+
+// F(z) = sum_{k=1..M} z^k / k!
+template <int M, class RT>
+__device__ __forceinline__ void poly_exp(const PlantT<RT>& pl, const PolyBasis<RT>& b, Poly<RT>& p)
+{
+    static_assert(M >= 4, "degree");
+    RT a[M + 1];
+    a[0] = RT(0);
+    double r = 1.0;
+#pragma unroll
+    for (int k = 1; k <= M; ++k) { r /= k; a[k] = (RT)r; }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        RT f = a[M];
+#pragma unroll
+        for (int k = M - 1; k >= 1; --k) f = fmr(f, pl.q[c], a[k]);
+        p.f[c] = f * pl.q[c];
+    }
+#pragma unroll
+    for (int k = M; k >= 4; --k) {  // the leading coefficient joins the quotient
+        a[k - 1] = fmr(b.c3, a[k], a[k - 1]);
+        a[k - 2] = fmr(b.c2, a[k], a[k - 2]);
+        a[k - 3] = fmr(b.c1, a[k], a[k - 3]);
+        a[k - 4] = fmr(b.c0, a[k], a[k - 4]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        RT s = a[M];
+#pragma unroll
+        for (int k = M - 1; k >= 4; --k) s = fmr(s, pl.q[c], a[k]);
+        p.s[c] = s;
+        p.a[c] = a[c];
+    }
+}
+
+// o = the transition over x's and y's steps together: (1 + x)(1 + y) - 1 modulo chi.  t[0..6]: the
+// coefficients of x y + x + y.  (o may be x or y.)
+template <class RT>
+__device__ __forceinline__ void poly_reduce(const PlantT<RT>& pl, const PolyBasis<RT>& b, const RT (&t)[7],
+                                            const Poly<RT>& x, const Poly<RT>& y, Poly<RT>& o)
+{
+    const RT e2 = t[6], e1 = fmr(b.c3, e2, t[5]), e0 = fmr(b.c3, e1, fmr(b.c2, e2, t[4]));  // the quotient
+    Poly<RT> r;
+    r.a[3] = fmr(b.c3, e0, fmr(b.c2, e1, fmr(b.c1, e2, t[3])));
+    r.a[2] = fmr(b.c2, e0, fmr(b.c1, e1, fmr(b.c0, e2, t[2])));
+    r.a[1] = fmr(b.c1, e0, fmr(b.c0, e1, t[1]));
+    r.a[0] = fmr(b.c0, e0, t[0]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const RT q = pl.q[c], eq = fmr(q, fmr(q, e2, e1), e0);
+        const RT xq = fmr(q, fmr(q, fmr(q, x.a[3], x.a[2]), x.a[1]), x.a[0]);
+        r.s[c] = fmr(x.s[c], y.f[c] + RT(1), fmr(y.s[c], xq + RT(1), eq));
+        r.f[c] = fmr(x.f[c], y.f[c], x.f[c] + y.f[c]);
+    }
+    o = r;
+}
+template <class RT>
+__device__ __forceinline__ void poly_twice(const PlantT<RT>& pl, const PolyBasis<RT>& b, const Poly<RT>& x, Poly<RT>& o)
+{
+    const RT a0 = x.a[0], a1 = x.a[1], a2 = x.a[2], a3 = x.a[3];
+    const RT d0 = a0 + a0, d1 = a1 + a1, d2 = a2 + a2, d3 = a3 + a3;
+    const RT t[7] = {fmr(a0, a0, d0), fmr(d1, a0, d1), fmr(a1, a1, fmr(d2, a0, d2)), fmr(d2, a1, fmr(d3, a0, d3)),
+                     fmr(a2, a2, d3 * a1), d3 * a2, a3 * a3};
+    poly_reduce(pl, b, t, x, x, o);
+}
+template <class RT>
+__device__ __forceinline__ void poly_join(const PlantT<RT>& pl, const PolyBasis<RT>& b, const Poly<RT>& x,
+                                          const Poly<RT>& y, Poly<RT>& o)
+{
+    const RT* p = x.a;
+    const RT* q = y.a;
+    const RT t[7] = {fmr(p[0], q[0], p[0] + q[0]),
+                     fmr(p[1], q[0], fmr(p[0], q[1], p[1] + q[1])),
+                     fmr(p[2], q[0], fmr(p[1], q[1], fmr(p[0], q[2], p[2] + q[2]))),
+                     fmr(p[3], q[0], fmr(p[2], q[1], fmr(p[1], q[2], fmr(p[0], q[3], p[3] + q[3])))),
+                     fmr(p[3], q[1], fmr(p[2], q[2], p[1] * q[3])),
+                     fmr(p[3], q[2], p[2] * q[3]), p[3] * q[3]};
+    poly_reduce(pl, b, t, x, y, o);
+}
+
+// Row 0 (theta) of F(B), and theta's coupling to the four active states.
+template <class RT>
+__device__ __forceinline__ void poly_theta_row(const PlantT<RT>& pl, const PolyBasis<RT>& b, const Poly<RT>& p,
+                                               RT (&m)[4], RT (&x)[4])
+{
+    const RT a0 = p.a[0], a1 = p.a[1], a2 = p.a[2], a3 = p.a[3];
+    m[0] = fmr(a2, pl.a10, fmr(a3, fmr(pl.a10, pl.a11, b.u + b.v), a0));
+    m[1] = fmr(a3, pl.a10, fmr(pl.a11, fmr(pl.a11, a3, a2), a1));
+    m[2] = pl.a12 * fmr(a3, pl.a11 + pl.a22, a2);
+    m[3] = pl.a13 * fmr(a3, pl.a11 + pl.a33, a2);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        x[c] = ((c & 1) ? pl.g3 * pl.a13 : pl.g2 * pl.a12) * fmr(p.s[c], pl.q[c] - ((c & 1) ? pl.a22 : pl.a33), a3);
+}
+
+// Rows 1..3 of F(B) from its row 0.  Row 1: B's row 0 is the unit row 1, so row 1 of F(B) is row 0 of
+// B F(B) = F(B) B.
+template <class RT>
+__device__ __forceinline__ void poly_block(const PlantT<RT>& pl, const PolyBasis<RT>& b, const Poly<RT>& p,
+                                           RT (&m)[4][4])
+{
+    const RT a0 = p.a[0], a1 = p.a[1], a2 = p.a[2], a3 = p.a[3];
+    const RT l2 = fmr(pl.a22, fmr(pl.a22, a3, a2), a1), l3 = fmr(pl.a33, fmr(pl.a33, a3, a2), a1);
+    m[1][0] = fmr(m[0][1], pl.a10, fmr(m[0][2], pl.a20, m[0][3] * pl.a30));
+    m[1][1] = fmr(m[0][1], pl.a11, m[0][0]);
+    m[1][2] = fmr(m[0][1], pl.a12, m[0][2] * pl.a22);
+    m[1][3] = fmr(m[0][1], pl.a13, m[0][3] * pl.a33);
+    m[2][0] = pl.a20 * fmr(a3, pl.a10, l2);
+    m[2][1] = pl.a20 * fmr(a3, pl.a11 + pl.a22, a2);
+    m[2][2] = fmr(a3, b.u, fmr(pl.a22, l2, a0));
+    m[2][3] = a3 * (pl.a20 * pl.a13);
+    m[3][0] = pl.a30 * fmr(a3, pl.a10, l3);
+    m[3][1] = pl.a30 * fmr(a3, pl.a11 + pl.a33, a2);
+    m[3][2] = a3 * (pl.a30 * pl.a12);
+    m[3][3] = fmr(a3, b.v, fmr(pl.a33, l3, a0));
+}
+
+// The divided difference of F at rate q as n[0] + n[1] z + n[2] z^2 + n[3] z^3.
+template <class RT>
+__device__ __forceinline__ void poly_difference(const PolyBasis<RT>& b, RT q, RT a1, RT a2, RT a3, RT s, RT (&n)[4])
+{
+    const RT q2 = q - b.c3, q1 = fmr(q, q2, -b.c2), q0 = fmr(q, q1, -b.c1);  // Q = z^3 + q2 z^2 + q1 z + q0
+    const RT n1 = fmr(q, a3, a2);
+    n[3] = s;
+    n[2] = fmr(s, q2, a3);
+    n[1] = fmr(s, q1, n1);
+    n[0] = fmr(s, q0, fmr(q, n1, a1));
+}
+
+// Rows 1..3 of coupling column c (its polynomial at B, applied to g's muscle: row 2 or 3).
+template <class RT>
+__device__ __forceinline__ void poly_column(const PlantT<RT>& pl, const PolyBasis<RT>& b, const Poly<RT>& p, int c,
+                                            RT (&x)[4][4])
+{
+    const bool ant = (c & 1) != 0;
+    const RT g = ant ? pl.g3 : pl.g2, sd = ant ? pl.a33 : pl.a22, s1 = ant ? pl.a13 : pl.a12;
+    RT n[4];
+    poly_difference(b, pl.q[c], p.a[1], p.a[2], p.a[3], p.s[c], n);
+    const RT k = fmr(n[3], pl.a11 + sd, n[2]);
+    x[1][c] = g * s1 * fmr(sd, k, fmr(n[3], pl.a10, fmr(pl.a11, fmr(pl.a11, n[3], n[2]), n[1])));
+    const RT own = g * fmr(n[3], ant ? b.v : b.u, fmr(sd, fmr(sd, fmr(sd, n[3], n[2]), n[1]), n[0]));
+    const RT other = g * n[3] * (ant ? pl.a20 * pl.a13 : pl.a30 * pl.a12);
+    x[2][c] = ant ? other : own;
+    x[3][c] = ant ? own : other;
+}
+
+// d <- Phi d in the pulse piece for the transition p.
+template <class RT>
+__device__ __forceinline__ void poly_apply(const PlantT<RT>& pl, const PolyBasis<RT>& b, const Poly<RT>& p, RT d[6])
+{
+    const RT* a = p.a;
+    RT na[4], nn[4];
+    poly_difference(b, pl.q[0], a[1], a[2], a[3], p.s[0], na);
+    poly_difference(b, pl.q[1], a[1], a[2], a[3], p.s[1], nn);
+    const RT ga = pl.g2 * d[4], gn = pl.g3 * d[5];
+    RT w0 = a[3] * d[0], w1 = a[3] * d[1], w2 = fmr(ga, na[3], a[3] * d[2]), w3 = fmr(gn, nn[3], a[3] * d[3]);
+#pragma unroll
+    for (int j = 2; j >= 0; --j) {  // w <- B w + a_j d + n_j g F
+        const RT r0 = fmr(a[j], d[0], w1);
+        const RT r1 = fmr(pl.a10, w0, fmr(pl.a11, w1, fmr(pl.a12, w2, fmr(pl.a13, w3, a[j] * d[1]))));
+        const RT r2 = fmr(pl.a20, w0, fmr(pl.a22, w2, fmr(ga, na[j], a[j] * d[2])));
+        const RT r3 = fmr(pl.a30, w0, fmr(pl.a33, w3, fmr(gn, nn[j], a[j] * d[3])));
+        w0 = r0; w1 = r1; w2 = r2; w3 = r3;
+    }
+    d[0] += w0; d[1] += w1; d[2] += w2; d[3] += w3;
+    d[4] = fmr(p.f[0], d[4], d[4]);
+    d[5] = fmr(p.f[1], d[5], d[5]);
 }
 
 // d <- Phi d for one step of pl's transition (D-form: d + D d) in the pulse (PIECE 0) or post (1) piece
@@ -491,9 +558,10 @@ __device__ __forceinline__ void step(const PlantT<RT>& pl, RT d[6])
     for (int i = 0; i < 4; ++i) d[i] = n[i];
 }
 
-// v <- exp(A t) v by a Taylor polynomial (degree Prec::expmv_m) in Horner form (t <= dt).
-template <class RT>
-__device__ __forceinline__ void expmv(const PlantT<RT>& pl, RT qa, RT qn, RT t, RT v[6])
+// v <- exp(A t) v (t in base steps) by a Taylor polynomial of degree Prec::expmv_m in Horner form, in
+// the pulse (PIECE 0) or post (1) piece; t is at most one sample.
+template <int PIECE, class RT>
+__device__ __forceinline__ void expmv(const PlantT<RT>& pl, RT t, RT v[6])
 {
     RT w[6];
 #pragma unroll
@@ -507,8 +575,8 @@ __device__ __forceinline__ void expmv(const PlantT<RT>& pl, RT qa, RT qn, RT t, 
         aw[1] = fmr(pl.a13, w[3], fmr(pl.a12, w[2], fmr(pl.a11, w[1], pl.a10 * w[0])));
         aw[2] = fmr(pl.g2, w[4], fmr(pl.a22, w[2], pl.a20 * w[0]));
         aw[3] = fmr(pl.g3, w[5], fmr(pl.a33, w[3], pl.a30 * w[0]));
-        aw[4] = qa * w[4];
-        aw[5] = qn * w[5];
+        aw[4] = pl.q[2 * PIECE] * w[4];
+        aw[5] = pl.q[2 * PIECE + 1] * w[5];
 #pragma unroll
         for (int i = 0; i < 6; ++i) w[i] = fmr(s, aw[i], v[i]);
     }
@@ -516,15 +584,16 @@ __device__ __forceinline__ void expmv(const PlantT<RT>& pl, RT qa, RT qn, RT t, 
     for (int i = 0; i < 6; ++i) v[i] = w[i];
 }
 
-// The sample that contains the pulse end: pulse dynamics for frac*dt, switch
-// to the post piece's coordinates, post dynamics for the rest of the sample.
+// The sample that contains the pulse end: pulse dynamics for frac of it, switch to the post piece's
+// coordinates, post dynamics for the rest.
 template <class RT>
-__device__ __forceinline__ void split_step(const PlantT<RT>& pl, RT frac, RT dt, RT d[6])
+__device__ __forceinline__ void split_step(const PlantT<RT>& pl, RT frac, RT d[6])
 {
-    expmv(pl, pl.q1a, pl.q1n, frac * dt, d);
+    constexpr RT steps = RT(1 << Prec<RT>::taylor_sq);  // base steps per sample
+    expmv<0>(pl, frac * steps, d);
 #pragma unroll
     for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
-    expmv(pl, pl.q2a, pl.q2n, (RT(1) - frac) * dt, d);
+    expmv<1>(pl, (RT(1) - frac) * steps, d);
 }
 
 // wave-wide min / max of an int (64 lanes)
@@ -589,18 +658,20 @@ __device__ __forceinline__ void block_step(const PlantT<RT>& pl, const ThetaRows
 }
 
 // Run the trajectory theta_k, k = 0..T-1: for each sample, t = sink.begin(k, u) and sink.end(k, t - v)
-// with theta_k = u + v.  pl holds the one-sample transition on entry and that of a block on exit.
+// with theta_k = u + v.  pl's transition (m, x, e) is set to that of a block.
 //
 // Bound by VALU issue.  A block of four samples costs one step of the four-sample transition (26
 // multiply-adds) and three rows (6 each) instead of four one-sample steps: 53 operations per block with a
-// squared residual instead of 116, for the two doublings that form the block's transition (~350
-// operations, paid back from ~25 samples on).  Measured on a round of 256 x 65536 candidates (mean T 57):
-// FP32 0.841 -> 0.708 ms, FP64 1.724 -> 1.425 ms.  Blocks of two save less on long traces (18 operations
-// per sample), blocks of eight need 42 more row coefficients in registers.  The lane's blocks end at its own pulse-end sample (the first k0 mod 4
-// samples are single steps), so a candidate's arithmetic depends on the candidate alone; lanes of a
-// wave whose pulse ends differ by a block mask a block each.
+// squared residual instead of 116.  The transitions over 1, 2, 3 and 4 samples come as polynomials
+// (~320 operations with the rows; as matrices, Horner and two doublings, ~870).  Measured on a
+// round of 256 x 65536 candidates (mean T 57), one-sample steps -> blocks -> blocks from polynomials:
+// FP32 0.841 -> 0.708 -> 0.604 ms, FP64 1.724 -> 1.425 -> 1.191 ms.  Blocks of two save less on long
+// traces (18 operations per sample), blocks of eight need 42 more row coefficients in registers.
+// The lane's blocks end at its own pulse-end sample: the first k0 mod 4 samples take their rows and a
+// jump, so a candidate's arithmetic depends on the candidate alone; lanes of a wave whose pulse ends
+// differ by a block mask a block each.
 template <class RT, class Sink>
-__device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, RT dt, int k0, RT frac, Sink& sink)
+__device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, int k0, RT frac, Sink& sink)
 {
     RT d[6];
 #pragma unroll
@@ -612,37 +683,46 @@ __device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, RT dt, int k0,
         theq = pl.amp;
     }
     ThetaRows<RT> rw;
+    PolyBasis<RT> pb;
+    Poly<RT> f1, f2;
+    poly_basis(pl, pb);
+    poly_exp<Prec<RT>::taylor_m>(pl, pb, f1);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) { rw.m[0][c] = pl.m[0][c]; rw.x[0][c] = pl.x[0][c]; }
-    const int np = max(k0, 0);  // samples before the pulse end (k0 <= T)
+    for (int q = 0; q < Prec<RT>::taylor_sq; ++q) poly_twice(pl, pb, f1, f1);
+    poly_theta_row(pl, pb, f1, rw.m[0], rw.x[0]);
+    poly_twice(pl, pb, f1, f2);
+    poly_theta_row(pl, pb, f2, rw.m[1], rw.x[1]);
+    const int np = max(k0, 0), head = np % BLOCK;  // samples before the pulse end (k0 <= T), and before the blocks
     int k = 0;
-#pragma unroll 1
-    for (const int head = np % BLOCK; k < head; ++k) {
-        sink.end(k, sink.begin(k, d[0] + theq));
-        step<0>(pl, d);
+    if (head) {
+        const RT u = d[0] + theq;
+        sink.end(0, sink.begin(0, u));
+        if (head > 1) row_sample<0>(rw, 1, 1, u, d, sink);
+        if (head > 2) row_sample<0>(rw, 2, 2, u, d, sink);
+        if (head & 2) poly_apply(pl, pb, f2, d);
+        if (head & 1) poly_apply(pl, pb, f1, d);
+        k = head;
     }
-    square_dform(pl.m, pl.x, pl.e);
+    poly_join(pl, pb, f1, f2, f1);
+    poly_theta_row(pl, pb, f1, rw.m[2], rw.x[2]);
+    poly_twice(pl, pb, f2, f2);
+    poly_theta_row(pl, pb, f2, pl.m[0], pl.x[0]);
+    poly_block(pl, pb, f2, pl.m);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        rw.m[1][c] = pl.m[0][c];
-        rw.x[1][c] = pl.x[0][c];
-        // three samples: D_1 + D_2 + D_1 D_2, its theta row
-        RT a = rw.m[0][c] + rw.m[1][c], b = fmr(rw.x[0][c], pl.e[c], rw.x[0][c] + rw.x[1][c]);
+    for (int c = 0; c < 4; ++c) { poly_column(pl, pb, f2, c, pl.x); pl.e[c] = f2.f[c]; }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            a = fmr(rw.m[0][i], pl.m[i][c], a);
-            b = fmr(rw.m[0][i], pl.x[i][c], b);
-        }
-        rw.m[2][c] = a;
-        rw.x[2][c] = b;
-        OPMM_KEEP(rw.x[2][c]);
+    for (int c = 2; c < 4; ++c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) OPMM_KEEP(pl.x[i][c]);
+#pragma unroll
+        for (int j = 0; j < BLOCK - 1; ++j) OPMM_KEEP(rw.x[j][c]);
+        OPMM_KEEP(pl.e[c]);
     }
-    square_dform(pl.m, pl.x, pl.e);
 #pragma unroll 1
     for (; k < np; k += BLOCK) block_step<0>(pl, rw, k, theq, d, sink);
     if (k0 >= 0 && k0 < T) {
         sink.end(k, sink.begin(k, d[0] + theq));
-        split_step(pl, frac, dt, d);
+        split_step(pl, frac, d);
         theq = pl.amp;
         ++k;
     }

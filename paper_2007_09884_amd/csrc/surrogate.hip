@@ -716,7 +716,7 @@ __global__ __launch_bounds__(64) void gen_batch_kernel(int B, uint64_t seed, con
     float* tr = trace + (int64_t)ii * MAX_T_GEN;
     GenSink sink{tr};
     if (!valid) return;
-    run_blocks(pl, T, (R)1.0, k0, frac, sink);
+    run_blocks(pl, T, k0, frac, sink);
     for (int k = 0; k < T; k += 2) {  // Box-Muller pairs
         float u1 = fmaxf(uni(32 + k), 0x1p-25f), u2 = uni(33 + k);
         float rad = sqrtf(-2.0f * logf(u1));
