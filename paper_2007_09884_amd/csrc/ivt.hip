@@ -8,14 +8,15 @@
 // saccade samples, its trace the run with the sample before it (the last
 // fixation sample) prepended, re-based to that sample.  Runs with duration
 // (T - 1) * dt below min_dur_ms or amplitude below min_amp_deg are dropped.
-// Output order is the stream order: segment starts are compacted with block
-// counts and a scan, never with an unordered atomic append.
+// Output order is the stream order.  Two launches: ivt_pass<false> counts each tile's kept runs and
+// their samples, ivt_pass<true> sums the tiles before its own and emits.  Both find the runs the same
+// way: the tile's saccade samples as bit words (a ballot per 64 samples), the last sample of a run from
+// a word and its neighbour, its length from the bits before it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <vector>
 
 #include "../../include/opmm.h"
 #include "runtime.hpp"
@@ -23,120 +24,212 @@
 namespace {
 
 constexpr int IVT_TPB = 256;
+constexpr int CHUNK = 2048;                  // samples whose flags a block holds at a time
+constexpr int WORDS = CHUNK / 64;
+constexpr int MAX_TILES = 4096;              // a tile is as many chunks as this bound needs (one up to 8.4 M samples)
+constexpr int HOST_RECS = 16384;             // records written straight to pinned host memory
+static_assert(WORDS <= 64 && WORDS % (IVT_TPB / 64) == 0, "one lane of wave 0 per word");
 
-__device__ __forceinline__ bool fast(const float* g, int64_t k, float thr2)
+// A gaze or trace sample; the caller's buffers are aligned to a float.
+struct __attribute__((packed, aligned(4))) Sample { float x, y; };
+
+struct IvtArgs {
+    const Sample* g;
+    int64_t N;
+    float thr2, dt, min_dur, min_amp;
+    int32_t max_T;
+    int chunks_per_tile;
+    // per tile: kept runs and their samples (written by the first pass)
+    int32_t* cnt;
+    int64_t* len;
+    // second pass
+    uint64_t seed_base;
+    int32_t max_out;
+    int64_t pos_cap;
+    Sample* pos;
+    opmm_saccade* recs;  // pinned host [HOST_RECS at most], and the records past them
+    int64_t* src;
+    opmm_saccade* more_recs;
+    int64_t* more_src;
+    int host_recs;
+    int32_t* emitted;    // pinned host, per tile
+};
+
+__device__ __forceinline__ bool fast(const IvtArgs& A, int64_t k)
 {
-    const float dx = g[2 * k] - g[2 * k - 2], dy = g[2 * k + 1] - g[2 * k - 1];
-    return dx * dx + dy * dy > thr2;
+    if (k < 1 || k >= A.N) return false;
+    const Sample p = A.g[k], q = A.g[k - 1];
+    const float dx = p.x - q.x, dy = p.y - q.y;
+    return dx * dx + dy * dy > A.thr2;
 }
 
-// flag[k] = 1 if a run of fast samples starts at k; per-block start counts
-__global__ void ivt_starts_kernel(const float* __restrict__ g, int64_t N, float thr2, int32_t* __restrict__ blk)
+__device__ __forceinline__ int64_t wave_sum(int64_t v)
 {
-    __shared__ int cnt;
-    if (threadIdx.x == 0) cnt = 0;
-    __syncthreads();
-    const int64_t k = (int64_t)blockIdx.x * IVT_TPB + threadIdx.x;
-    if (k >= 1 && k < N && fast(g, k, thr2) && (k == 1 || !fast(g, k - 1, thr2))) atomicAdd(&cnt, 1);
-    __syncthreads();
-    if (threadIdx.x == 0) blk[blockIdx.x] = cnt;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += (int64_t)__shfl_xor((long long)v, o);
+    return v;
 }
 
-// exclusive scan of n ints in place by one block (n up to millions: serial chunks)
-__global__ void scan_kernel(int32_t* a, int64_t n, int32_t* total)
+// Bound by latency, not bandwidth: 2048 samples per block put a ten-minute 1 kHz stream (580 k samples, 4.6 MB)
+// on 284 blocks, each a handful of dependent steps (flags, gathers of the runs' ends, copies).  Both
+// passes together take 17 us there; the five kernels before them (serial walks along each run, a
+// one-block scan) took 64 us, and with their allocations, copies and waits a call through the
+// binding 249 us against 46 us now.
+template <bool EMIT>
+__global__ __launch_bounds__(IVT_TPB) void ivt_pass(IvtArgs A)
 {
-    __shared__ int32_t part[1024];
-    const int t = threadIdx.x;
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t b = t * per, e = min(n, b + per);
-    int32_t s = 0;
-    for (int64_t i = b; i < e; ++i) s += a[i];
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        int32_t run = 0;
-        for (int i = 0; i < 1024; ++i) { int32_t v = part[i]; part[i] = run; run += v; }
-        *total = run;
-    }
-    __syncthreads();
-    int32_t run = part[t];
-    for (int64_t i = b; i < e; ++i) { int32_t v = a[i]; a[i] = run; run += v; }
-}
-
-// write the start sample of every run, in stream order
-__global__ void ivt_scatter_kernel(const float* __restrict__ g, int64_t N, float thr2, const int32_t* __restrict__ blk,
-                                   int64_t* __restrict__ starts)
-{
-    __shared__ int32_t pre[IVT_TPB];
-    const int64_t k = (int64_t)blockIdx.x * IVT_TPB + threadIdx.x;
-    const int f = (k >= 1 && k < N && fast(g, k, thr2) && (k == 1 || !fast(g, k - 1, thr2))) ? 1 : 0;
-    pre[threadIdx.x] = f;
-    __syncthreads();
-    for (int o = 1; o < IVT_TPB; o <<= 1) {  // inclusive block scan
-        int32_t v = threadIdx.x >= o ? pre[threadIdx.x - o] : 0;
+    __shared__ uint64_t bits[WORDS + 1];
+    __shared__ int64_t s_carry;                              // saccade samples right before the chunk
+    __shared__ int64_t s_cnt[IVT_TPB / 64], s_len[IVT_TPB / 64];
+    __shared__ int s_kept;
+    __shared__ int64_t s_klen;
+    __shared__ int k_last[EMIT ? CHUNK / 2 : 1], k_T[EMIT ? CHUNK / 2 : 1], k_off[EMIT ? CHUNK / 2 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int64_t cnt = 0, len = 0;  // kept runs and their samples before the chunk: of the tile, or (EMIT) of the stream
+    if (EMIT) {
+        for (int i = tid; i < (int)blockIdx.x; i += IVT_TPB) { cnt += A.cnt[i]; len += A.len[i]; }
+        cnt = wave_sum(cnt);
+        len = wave_sum(len);
+        if (lane == 0) { s_cnt[wave] = cnt; s_len[wave] = len; }
         __syncthreads();
-        pre[threadIdx.x] += v;
+        cnt = len = 0;
+        for (int w = 0; w < IVT_TPB / 64; ++w) { cnt += s_cnt[w]; len += s_len[w]; }
+    }
+    int out = 0;  // records emitted by the tile (thread 0's count)
+    for (int ch = 0; ch < A.chunks_per_tile; ++ch) {
+        const int64_t c0 = ((int64_t)blockIdx.x * A.chunks_per_tile + ch) * CHUNK;
+        if (c0 >= A.N) break;
+        uint64_t w0 = 0;
+#pragma unroll
+        for (int i = 0; i < WORDS / (IVT_TPB / 64); ++i) {
+            const int w = wave * (WORDS / (IVT_TPB / 64)) + i;
+            const uint64_t b = __ballot(fast(A, c0 + 64 * w + lane));
+            if (i == 0) w0 = b;
+            if (lane == 0) bits[w] = b;
+        }
+        if (tid == IVT_TPB - 1) bits[WORDS] = fast(A, c0 + CHUNK) ? 1 : 0;
+        if (wave == 0) {  // a run may come in from before the chunk: its length so far, up to max_T
+            int64_t n = 0;
+            if (w0 & 1)
+                while (n < A.max_T) {
+                    const uint64_t b = __ballot(fast(A, c0 - 1 - n - lane));
+                    const int ones = b == ~0ull ? 64 : __builtin_ctzll(~b);
+                    n += ones;
+                    if (ones < 64) break;
+                }
+            if (lane == 0) s_carry = n;
+        }
         __syncthreads();
+        if (wave == 0) {
+            uint64_t keep = 0;
+            int mine = 0;
+            int64_t samples = 0;
+            // length of the run that ends at bit j of word `lane`
+            auto run_length = [&](int j) {
+                const uint64_t inv = ~(bits[lane] << (63 - j));
+                int64_t n = inv ? __builtin_clzll(inv) : 64;
+                if (n <= j) return n;
+                n = j + 1;
+                int w = lane - 1;
+                for (; w >= 0 && bits[w] == ~0ull; --w) n += 64;
+                return n + (w >= 0 ? (int64_t)__builtin_clzll(~bits[w]) : s_carry);
+            };
+            if (lane < WORDS) {
+                uint64_t e = bits[lane] & ~((bits[lane] >> 1) | (bits[lane + 1] << 63));  // last samples of runs
+                while (e) {
+                    const int j = __builtin_ctzll(e);
+                    e &= e - 1;
+                    const int64_t T = run_length(j) + 1;  // with the fixation sample before the run
+                    if (!((float)(T - 1) * A.dt >= A.min_dur && T <= A.max_T)) continue;
+                    const int64_t k1 = c0 + 64 * lane + j;
+                    const Sample p = A.g[k1], q = A.g[k1 - T + 1];
+                    const float dx = p.x - q.x, dy = p.y - q.y;
+                    if (!(sqrtf(dx * dx + dy * dy) >= A.min_amp)) continue;
+                    keep |= 1ull << j;
+                    ++mine;
+                    samples += T;
+                }
+            }
+            int before = mine;
+            int64_t sbefore = samples;
+#pragma unroll
+            for (int o = 1; o < WORDS; o <<= 1) {  // inclusive scan over the words
+                const int u = __shfl_up(before, o);
+                const int64_t v = (int64_t)__shfl_up((long long)sbefore, o);
+                if (lane >= o) { before += u; sbefore += v; }
+            }
+            if (lane == WORDS - 1) { s_kept = before; s_klen = sbefore; }
+            if (EMIT) {
+                int i = before - mine;
+                int off = (int)(sbefore - samples);
+                while (keep) {
+                    const int j = __builtin_ctzll(keep);
+                    keep &= keep - 1;
+                    const int T = (int)run_length(j) + 1;
+                    k_last[i] = 64 * lane + j;
+                    k_T[i] = T;
+                    k_off[i] = off;
+                    ++i;
+                    off += T;
+                }
+            }
+        }
+        __syncthreads();
+        const int kept = s_kept;
+        const int64_t klen = s_klen;
+        if (EMIT) {
+            for (int i = wave; i < kept; i += IVT_TPB / 64) {
+                const int T = k_T[i];
+                const int64_t o = cnt + i, off = len + k_off[i];
+                // the output is a prefix of the stream's kept runs: both bounds grow along it
+                if (o >= A.max_out || 2 * (off + T) > A.pos_cap) break;
+                const int64_t k1 = c0 + k_last[i], k = k1 - T + 1;
+                const Sample s0 = A.g[k];
+                for (int t = lane; t < T; t += 64) {
+                    const Sample p = A.g[k + t];
+                    A.pos[off + t] = Sample{p.x - s0.x, p.y - s0.y};
+                }
+                if (lane == 0) {
+                    const Sample s1 = A.g[k1];
+                    const float dx = s1.x - s0.x, dy = s1.y - s0.y;
+                    float d = atan2f(dy, dx) * (180.0f / 3.14159265358979f);
+                    if (d < 0.0f) d += 360.0f;
+                    opmm_saccade s;
+                    s.pos_offset = 2 * off;
+                    s.T = T;
+                    s.C = 2;
+                    s.amp_deg = sqrtf(dx * dx + dy * dy);
+                    s.dir_deg = d;
+                    s.dur_ms = (float)(T - 1) * A.dt;
+                    s.n_cand = 0;
+                    s.seed = A.seed_base + (uint64_t)k;
+                    if (o < A.host_recs) {
+                        A.recs[o] = s;
+                        A.src[o] = k;
+                    } else {
+                        A.more_recs[o - A.host_recs] = s;
+                        A.more_src[o - A.host_recs] = k;
+                    }
+                }
+            }
+            if (tid == 0)
+                for (int i = 0; i < kept; ++i) {
+                    if (cnt + i >= A.max_out || 2 * (len + k_off[i] + k_T[i]) > A.pos_cap) break;
+                    ++out;
+                }
+        }
+        cnt += kept;
+        len += klen;
+        __syncthreads();  // the chunk's words and lists are read; the next chunk may overwrite them
     }
-    if (f) starts[blk[blockIdx.x] + pre[threadIdx.x] - 1] = k;
-}
-
-// per run: length, amplitude, direction, acceptance
-__global__ void ivt_segments_kernel(const float* __restrict__ g, int64_t N, float thr2, int32_t n_runs,
-                                    const int64_t* __restrict__ starts, float dt, float min_dur, float min_amp,
-                                    int32_t max_T, int32_t* __restrict__ keep, int32_t* __restrict__ Ts,
-                                    float* __restrict__ amp, float* __restrict__ dir)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_runs) return;
-    const int64_t k0 = starts[i];
-    int64_t k1 = k0;
-    while (k1 + 1 < N && fast(g, k1 + 1, thr2)) ++k1;
-    const int64_t T = k1 - k0 + 2;  // the fixation sample before the run + the run
-    const float dx = g[2 * k1] - g[2 * (k0 - 1)], dy = g[2 * k1 + 1] - g[2 * (k0 - 1) + 1];
-    const float a = sqrtf(dx * dx + dy * dy);
-    float d = atan2f(dy, dx) * (180.0f / 3.14159265358979f);
-    if (d < 0.0f) d += 360.0f;
-    Ts[i] = (int32_t)min(T, (int64_t)0x7FFFFFFF);
-    amp[i] = a;
-    dir[i] = d;
-    keep[i] = ((float)(T - 1) * dt >= min_dur && a >= min_amp && T <= max_T) ? 1 : 0;
-}
-
-// kept runs -> records and traces re-based to their first sample
-__global__ void ivt_emit_kernel(const float* __restrict__ g, int32_t n_runs, const int64_t* __restrict__ starts,
-                                const int32_t* __restrict__ keep, const int32_t* __restrict__ slot,
-                                const int32_t* __restrict__ off, const int32_t* __restrict__ Ts,
-                                const float* __restrict__ amp, const float* __restrict__ dir, float dt,
-                                uint64_t seed_base, int32_t max_out, opmm_saccade* __restrict__ out,
-                                float* __restrict__ out_pos, int64_t* __restrict__ src_start)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_runs || !keep[i]) return;
-    const int o = slot[i];
-    if (o >= max_out) return;
-    const int64_t k = starts[i] - 1;
-    const int T = Ts[i];
-    const int64_t po = 2 * (int64_t)off[i];
-    const float x0 = g[2 * k], y0 = g[2 * k + 1];
-    for (int t = 0; t < T; ++t) {
-        out_pos[po + 2 * t] = g[2 * (k + t)] - x0;
-        out_pos[po + 2 * t + 1] = g[2 * (k + t) + 1] - y0;
+    if (tid == 0) {
+        if (EMIT) A.emitted[blockIdx.x] = out;
+        else {
+            A.cnt[blockIdx.x] = (int32_t)cnt;
+            A.len[blockIdx.x] = len;
+        }
     }
-    opmm_saccade s;
-    s.pos_offset = po;
-    s.T = T;
-    s.C = 2;
-    s.amp_deg = amp[i];
-    s.dir_deg = dir[i];
-    s.dur_ms = (float)(T - 1) * dt;
-    s.n_cand = 0;
-    s.seed = seed_base + (uint64_t)k;
-    out[o] = s;
-    if (src_start) src_start[o] = k;
 }
-
-int blocks_of(int64_t n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
 
@@ -156,92 +249,72 @@ int opmm_ivt_extract(opmm_ctx* ctx, const float* gaze, int64_t N, float dt_ms, f
     if (N < 2 || max_out == 0) return OPMM_OK;
     hipStream_t st = (hipStream_t)stream;
     const float v_per_sample = vel_thresh_deg_s * dt_ms * 1e-3f;  // deg per sample at the threshold
-    const float thr2 = v_per_sample * v_per_sample;
-    const int nb = blocks_of(N, IVT_TPB);
-    int32_t *blk = nullptr, *tot = nullptr;
-    int64_t* starts = nullptr;
+    const int64_t chunks = (N + CHUNK - 1) / CHUNK;
+    const int per_tile = (int)((chunks + MAX_TILES - 1) / MAX_TILES);
+    const int tiles = (int)((chunks + per_tile - 1) / per_tile);
+    // kept runs are separated by a slow sample and hold at least min_dur / dt samples
+    const double shortest = std::max(1.0, std::floor((double)min_dur_ms / (double)dt_ms) - 1.0);
+    const int64_t cap = std::min<int64_t>(max_out, (int64_t)((double)N / (shortest + 1.0)) + 1);
+    const int host_recs = (int)std::min<int64_t>(cap, HOST_RECS);
     int rc = OPMM_OK;
     auto ok = [&](hipError_t e, const char* w) { if (rc == OPMM_OK && e != hipSuccess) rc = opmm_rt::hip_fail(ctx, e, w); };
-    ok(hipMallocAsync((void**)&blk, sizeof(int32_t) * (nb + 1), st), "alloc");
-    ok(hipMallocAsync((void**)&tot, sizeof(int32_t) * 2, st), "alloc");
-    int32_t n_runs = 0;
+    // pinned host: emitted [MAX_TILES], first samples, records; kept between calls (every call waits for its
+    // kernels before it returns)
+    const size_t emitted_bytes = sizeof(int32_t) * MAX_TILES;
+    char *hp = nullptr, *tp = nullptr;
+    if ((rc = opmm_rt::ctx_ivt_stage(ctx, emitted_bytes + (sizeof(opmm_saccade) + sizeof(int64_t)) * (size_t)host_recs,
+                                     &hp, (sizeof(int64_t) + sizeof(int32_t)) * MAX_TILES, &tp)) != OPMM_OK)
+        return rc;
+    int32_t* h_emitted = (int32_t*)hp;
+    int64_t* h_src = (int64_t*)(hp + emitted_bytes);
+    opmm_saccade* h_recs = (opmm_saccade*)(h_src + host_recs);
+    const size_t more = (size_t)(cap - host_recs);
+    char* dp = nullptr;  // records past the pinned ones
+    if (more > 0) ok(hipMallocAsync((void**)&dp, (sizeof(opmm_saccade) + sizeof(int64_t)) * more, st), "alloc");
+    if (rc != OPMM_OK) return rc;
+    IvtArgs A;
+    A.g = (const Sample*)gaze;
+    A.N = N;
+    A.thr2 = v_per_sample * v_per_sample;
+    A.dt = dt_ms;
+    A.min_dur = min_dur_ms;
+    A.min_amp = min_amp_deg;
+    A.max_T = max_T;
+    A.chunks_per_tile = per_tile;
+    A.len = (int64_t*)tp;
+    A.cnt = (int32_t*)(A.len + MAX_TILES);
+    A.more_src = (int64_t*)dp;
+    A.more_recs = (opmm_saccade*)(A.more_src + more);
+    A.seed_base = seed_base;
+    A.max_out = (int32_t)cap;
+    A.pos_cap = pos_cap;
+    A.pos = (Sample*)pos_out;
+    A.recs = h_recs;
+    A.src = h_src;
+    A.host_recs = host_recs;
+    A.emitted = h_emitted;
+    hipLaunchKernelGGL(ivt_pass<false>, dim3(tiles), dim3(IVT_TPB), 0, st, A);
+    ok(hipGetLastError(), "ivt_pass");
+    hipLaunchKernelGGL(ivt_pass<true>, dim3(tiles), dim3(IVT_TPB), 0, st, A);
+    ok(hipGetLastError(), "ivt_pass");
+    ok(hipStreamSynchronize(st), "sync");
     if (rc == OPMM_OK) {
-        hipLaunchKernelGGL(ivt_starts_kernel, dim3(nb), dim3(IVT_TPB), 0, st, gaze, N, thr2, blk);
-        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, blk, (int64_t)nb, tot);
-        ok(hipMemcpyAsync(&n_runs, tot, sizeof(int32_t), hipMemcpyDeviceToHost, st), "copy");
-        ok(hipStreamSynchronize(st), "sync");
-    }
-    if (rc == OPMM_OK && n_runs > 0) {
-        // one allocation for the per-run arrays: starts (int64), then seven 4-byte arrays: keep, T,
-        // slot, offset, keep after truncation (int32), amplitude, direction (float).  keep and T are
-        // adjacent (one copy down), and so are slot, offset and the truncated keep (one copy up).
-        const size_t R = (size_t)n_runs;
-        char* runbuf = nullptr;
-        ok(hipMallocAsync((void**)&runbuf, R * (sizeof(int64_t) + 7 * sizeof(int32_t)), st), "alloc");
-        if (rc != OPMM_OK) runbuf = nullptr;
-        starts = (int64_t*)runbuf;
-        if (rc == OPMM_OK) {
-            int32_t* keep = (int32_t*)(runbuf + R * sizeof(int64_t));
-            int32_t* Ts = keep + R;
-            int32_t* slot = Ts + R;
-            int32_t* off = slot + R;
-            int32_t* keep2 = off + R;  // keep after truncation
-            float* amp = (float*)(keep2 + R);
-            float* dir = amp + R;
-            hipLaunchKernelGGL(ivt_scatter_kernel, dim3(nb), dim3(IVT_TPB), 0, st, gaze, N, thr2, blk, starts);
-            hipLaunchKernelGGL(ivt_segments_kernel, dim3(blocks_of(n_runs, 128)), dim3(128), 0, st, gaze, N, thr2,
-                               n_runs, starts, dt_ms, min_dur_ms, min_amp_deg, max_T, keep, Ts, amp, dir);
-            std::vector<int32_t> hkT(2 * R);  // keep, then T
-            ok(hipMemcpyAsync(hkT.data(), keep, sizeof(int32_t) * 2 * R, hipMemcpyDeviceToHost, st), "copy");
+        int64_t n = 0;
+        for (int i = 0; i < tiles; ++i) n += h_emitted[i];
+        const int64_t nh = std::min<int64_t>(n, host_recs);
+        std::memcpy(sacs_out, h_recs, sizeof(opmm_saccade) * (size_t)nh);
+        if (src_start_out) std::memcpy(src_start_out, h_src, sizeof(int64_t) * (size_t)nh);
+        if (n > nh) {
+            ok(hipMemcpyAsync(sacs_out + nh, A.more_recs, sizeof(opmm_saccade) * (size_t)(n - nh),
+                              hipMemcpyDeviceToHost, st), "copy");
+            if (src_start_out)
+                ok(hipMemcpyAsync(src_start_out + nh, A.more_src, sizeof(int64_t) * (size_t)(n - nh),
+                                  hipMemcpyDeviceToHost, st), "copy");
             ok(hipStreamSynchronize(st), "sync");
-            if (rc == OPMM_OK) {
-                // output slot and trace offset of the kept runs, in stream order; output stops at the
-                // first kept run past max_out records or pos_cap floats of trace (a prefix of the stream)
-                const int32_t* hk = hkT.data();
-                const int32_t* hT = hk + R;
-                std::vector<int32_t> up(3 * R, 0);  // slot, offset, keep after truncation
-                int32_t* hs = up.data();
-                int32_t* ho = hs + R;
-                int32_t* hk2 = ho + R;
-                int64_t acc = 0;
-                int32_t emitted = 0;
-                bool full = false;
-                for (size_t i = 0; i < R; ++i) {
-                    if (!hk[i]) continue;
-                    full = full || emitted >= max_out || 2 * (acc + hT[i]) > pos_cap;
-                    if (full) continue;
-                    hk2[i] = 1;
-                    ho[i] = (int32_t)acc;
-                    hs[i] = emitted;
-                    acc += hT[i];
-                    ++emitted;
-                }
-                opmm_saccade* d_recs = nullptr;
-                int64_t* d_src = nullptr;
-                ok(hipMallocAsync((void**)&d_recs, sizeof(opmm_saccade) * std::max(emitted, 1), st), "alloc");
-                ok(hipMallocAsync((void**)&d_src, sizeof(int64_t) * std::max(emitted, 1), st), "alloc");
-                ok(hipMemcpyAsync(slot, up.data(), sizeof(int32_t) * 3 * R, hipMemcpyHostToDevice, st), "copy");
-                if (rc == OPMM_OK)
-                    hipLaunchKernelGGL(ivt_emit_kernel, dim3(blocks_of(n_runs, 128)), dim3(128), 0, st, gaze, n_runs,
-                                       starts, keep2, slot, off, Ts, amp, dir, dt_ms, seed_base, max_out, d_recs,
-                                       pos_out, d_src);
-                if (emitted > 0) {
-                    ok(hipMemcpyAsync(sacs_out, d_recs, sizeof(opmm_saccade) * emitted, hipMemcpyDeviceToHost, st),
-                       "copy");
-                    if (src_start_out)
-                        ok(hipMemcpyAsync(src_start_out, d_src, sizeof(int64_t) * emitted, hipMemcpyDeviceToHost, st),
-                           "copy");
-                }
-                ok(hipStreamSynchronize(st), "sync");
-                if (d_recs) (void)hipFreeAsync(d_recs, st);
-                if (d_src) (void)hipFreeAsync(d_src, st);
-                *n_out = emitted;
-            }
         }
+        if (rc == OPMM_OK) *n_out = (int32_t)n;
     }
-    if (starts) (void)hipFreeAsync(starts, st);
-    if (blk) (void)hipFreeAsync(blk, st);
-    if (tot) (void)hipFreeAsync(tot, st);
+    if (dp) (void)hipFreeAsync(dp, st);
     return rc;
 }
 

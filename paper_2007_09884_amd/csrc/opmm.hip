@@ -1009,6 +1009,7 @@ struct opmm_ctx {
     uint32_t* giveup_report = nullptr;     // device word: give-ups since the last opmm_sync
     std::string err;
     FitScratch scratch;
+    DevBuf ivt_stage, ivt_tiles;  // opmm_ivt_extract: pinned host staging, per-tile counts
     FitScratch aux;  // projections for the learned seed, independent of the fit's scratch
     float* d_cand = nullptr;  // small per-call staging for opmm_score (projected trace)
     size_t d_cand_cap = 0;
@@ -1507,6 +1508,15 @@ int check_fit_args(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_
 
 namespace opmm_rt {
 
+int ctx_ivt_stage(opmm_ctx* ctx, size_t host_bytes, char** host, size_t dev_bytes, char** dev)
+{
+    int rc = ensure_host(ctx, ctx->ivt_stage, host_bytes);
+    if (rc == OPMM_OK) rc = ensure(ctx, ctx->ivt_tiles, dev_bytes);
+    *host = (char*)ctx->ivt_stage.p;
+    *dev = (char*)ctx->ivt_tiles.p;
+    return rc;
+}
+
 int validate_saccade(opmm_ctx* ctx, const opmm_saccade& s, int64_t pos_len, int i)
 {
     return validate_saccade_impl(ctx, s, pos_len, i);
@@ -1730,6 +1740,8 @@ int opmm_destroy(opmm_ctx* ctx)
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
     if (ctx->d_cand) (void)hipFree(ctx->d_cand);
+    if (ctx->ivt_stage.p) (void)hipHostFree(ctx->ivt_stage.p);
+    if (ctx->ivt_tiles.p) (void)hipFree(ctx->ivt_tiles.p);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->giveup_report) (void)hipFree(ctx->giveup_report);
     opmm_rt::order_release(ctx->order);

@@ -133,6 +133,10 @@ int hip_fail(opmm_ctx* ctx, hipError_t e, const char* what);
 int ctx_device(const opmm_ctx* ctx);
 int ctx_cu_count(const opmm_ctx* ctx);  // compute units of the context's device
 
+// Buffers of opmm_ivt_extract, kept in the context between calls: at least host_bytes of pinned host
+// memory and dev_bytes of device memory.
+int ctx_ivt_stage(opmm_ctx* ctx, size_t host_bytes, char** host, size_t dev_bytes, char** dev);
+
 // Validate and upload saccade records, then project every trace on its
 // movement direction (ctx-owned scratch, valid until the next call on ctx).
 int project_batch(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_saccade* sacs, int S,
