@@ -3,16 +3,15 @@
 // an iteration evaluated simultaneously, the simplex sorted every iteration,
 // both exit tolerances or an iteration cap.
 //
-// One or two saccades per 64-lane wave.  The simplex (19 vertices x 18
-// coordinates, FP64, relative to the Table 1 nominal) and the projected trace
-// (sized to the batch's longest) live in LDS.  Every iteration lanes 0..21 of
-// a task build and evaluate reflection, expansion, outside and inside
-// contraction and the 18 shrink vertices at once; lane 0 of the task takes the
-// Lagarias decision (reflection 1, expansion 2, contraction 1/2, shrink 1/2);
-// the exit test, the vertex update and the stable re-sort run one coordinate
-// or one vertex per lane.  Each evaluation is the same plant
-// simulation and RMSE as the box search (points clamped to the search box and
-// rounded to FP32, the candidate format).
+// One to three saccades per 64-lane wave, a group of lanes each.  Lane j of a group holds coordinate j of
+// all 19 vertices (FP64, relative to the Table 1 nominal, sorted by value) in registers and lane i the
+// value of vertex i; a new vertex goes to its rank by a ballot and a shift, so nothing is sorted but
+// after a shrink.  An evaluation runs on a quad of lanes: each lane one column of the transition, then
+// one row of the recurrence.  An iteration evaluates reflection, expansion, outside and inside
+// contraction at once on four quads; the 18 shrink vertices follow on every quad of the group in
+// the few iterations that the Lagarias decision (reflection 1, expansion 2, contraction 1/2, shrink 1/2)
+// asks for them.  Each evaluation is the same plant simulation and RMSE as the box search (points
+// clamped to the search box and rounded to FP32, the candidate format).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,217 +29,137 @@ using opmm_rt::SacDev;
 namespace {
 
 constexpr int NV = P + 1;   // simplex vertices
-constexpr int NPT = 4 + P;  // points per iteration: r, e, oc, ic, 18 shrink
+constexpr int PTS = 20;     // floats per row of points in LDS (P and padding to 16 bytes)
 
-// One task's simplex state (the trace lives in dynamic LDS after the groups).
-struct NmGroup {
-    double v[NV][P];
-    double f[NV];
-    double pt[NPT][P];
-    double fp[NPT];
-    double xb[P];
-    double nom[P];
-    double tv[NV][P];  // sort staging
-    double tf[NV];
-    double dxc[P];     // per-coordinate spread of the simplex
-    int flag;          // exit test passed
-    int dec;
-    int active;        // still iterating
-    int iters;         // iterations taken (set when the task stops)
-};
+// Lanes of a group of a wave with G groups: whole quads, a lane per vertex at least.
+constexpr int group_lanes(int g) { return g == 1 ? 64 : g == 2 ? 32 : 20; }
+static_assert(group_lanes(3) >= NV && group_lanes(3) % 4 == 0 && 3 * group_lanes(3) <= 64, "lane groups");
 
-// The simplex's iterates depend on every rounding of its costs, so this file keeps the sample-by-sample
-// evaluation its results are defined by: the transition by Horner's rule on matrices and one step per
-// sample (run_blocks in plant.hpp gives the same trajectories to ~1e-14 deg).
-struct NmPlant {
-    R a10, a11, a12, a13;       // per ms; omega row: theta, omega, x_ag, x_ant
-    R a20, a22, g2;             // x_ag row: theta, x_ag, F_ag
-    R a30, a33, g3;             // x_ant row: theta, x_ant, F_ant
-    R q1a, q1n, q2a, q2n;       // F rows: -1/tau, pulse (activation) and post (deactivation)
-    R m[4][4], x1[4][2], x2[4][2], e1[2], e2[2];  // one-sample transition in D-form (Phi - I), both pieces
-    R th1, amp, sh[6], d0[6];   // equilibria (theta), pulse minus post, rest minus pulse
-    double pwd;                 // PW in sample periods
-};
-
-// mechanical rows of (s*A) V, plus `acc` on the diagonal of column `diag` (-1: none)
-#define OPMM_MV(s10, s11, s12, s13, s20, s22, s30, s33, sv, V0, V1, V2, V3, o0, o1, o2, o3, i0, i1, i2, i3) \
-    do {                                                                                               \
-        o0 = fmr(sv, V1, i0);                                                                    \
-        o1 = fmr(s13, V3, fmr(s12, V2, fmr(s11, V1, fmr(s10, V0, i1))));       \
-        o2 = fmr(s22, V2, fmr(s20, V0, i2));                                               \
-        o3 = fmr(s33, V3, fmr(s30, V0, i3));                                               \
-    } while (0)
-
-// Horner evaluation of D = sum_{k=1..M} (hA)^k / k! for the augmented block
-// matrix [[Mech, G1, G2], [0, Q1, 0], [0, 0, Q2]] whose off-diagonal blocks
-// give the pulse-piece and post-piece coupling columns at once, on the step
-// h/2^SQ, then SQ squarings in D-form: D_2h = D_h^2 + 2 D_h.  The Horner
-// iterates P_k = I + (B/k) P_{k+1} (B = hA) are carried scaled, Q_k = c_k P_k
-// with c_M = M and c_k = k c_{k+1}: then Q_M = M I + B, Q_k = c_k I + B Q_{k+1}
-// and D = B Q_2 / M!, so the entries of B are formed once instead of once per
-// step (fewer instructions and fewer live registers).
-__device__ __forceinline__ void transition_dform(NmPlant& pl, R hfull)
+// ---- quad exchange ----------------------------------------------------------
+constexpr int quad(int a, int b, int c, int d) { return a | (b << 2) | (c << 4) | (d << 6); }
+template <int CTRL>
+__device__ __forceinline__ double quad_perm(double x)
 {
-    constexpr int M = Prec<R>::taylor_m, SQ = Prec<R>::taylor_sq;
-    const R h = hfull * (R(1) / R(1 << SQ));
-    const R qv[4] = {pl.q1a, pl.q1n, pl.q2a, pl.q2n};
-    const R s10 = pl.a10 * h, s11 = pl.a11 * h, s12 = pl.a12 * h, s13 = pl.a13 * h;
-    const R s20 = pl.a20 * h, s22 = pl.a22 * h, s30 = pl.a30 * h, s33 = pl.a33 * h;
-    const R sg2 = pl.g2 * h, sg3 = pl.g3 * h;
-    R sq[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) sq[c] = qv[c] * h;
-    R pm[4][4], px[4][4], pd[4];
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int K>
+__device__ __forceinline__ double quad_bcast(double x) { return quad_perm<quad(K, K, K, K)>(x); }
+
+// Least x over the wave, for an x that is the same on the four lanes of a quad (a scalar).
+__device__ __forceinline__ int min_over_quads(int x)
+{
+    x = min(x, __builtin_amdgcn_mov_dpp(x, 0x124, 0xf, 0xf, true));  // row_ror:4
+    x = min(x, __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true));  // row_ror:8
+    return min(min(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+               min(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+
+// One of four values by lane.  (The pins keep the choice among registers: seen as a choice among struct
+// fields it becomes an indexed load, and the struct goes to scratch memory.)
+__device__ __forceinline__ double pick(int i, double a, double b, double c, double d)
+{
+    OPMM_KEEP(a); OPMM_KEEP(b); OPMM_KEEP(c); OPMM_KEEP(d);
+    return i == 0 ? a : i == 1 ? b : i == 2 ? c : d;
+}
+
+// ---- one evaluation on a quad -------------------------------------------------
+// The simplex's iterates depend on every rounding of its costs, so this file keeps the sample-by-sample
+// evaluation its results are defined by: the transition by Horner's rule and squarings on matrices, one
+// step per sample (run_blocks in plant.hpp gives the same trajectories to ~1e-14 deg).  A quad only
+// spreads that evaluation's operations over four lanes; each result goes through the same operations in
+// the same order as on one.
+
+// Column c of the one-sample transition in D-form (D = Phi - I): mechanical block m[.][c], coupling x[.][c]
+// of active state c (pulse ag, pulse ant, post ag, post ant) and that state's factor minus one e.
+// Horner on the step dt/4 with scaled iterates (B = hA: Q_M = M I + B, Q_k = c_k I + B Q_{k+1}, c_k = k c_{k+1},
+// D = B Q_2 / M!), then two squarings D_2h = D_h^2 + 2 D_h.  A column of a product needs the left factor
+// whole: its columns come from the other lanes.
+__device__ __forceinline__ void transition_column(const PlantScalars<double>& pc, double dt, int c, double m[4],
+                                                  double x[4], double& e)
+{
+    constexpr int M = Prec<double>::taylor_m, SQ = Prec<double>::taylor_sq;
+    const double h = dt * (1.0 / (double)(1 << SQ));
+    const double s10 = pc.a10 * h, s11 = pc.a11 * h, s12 = pc.a12 * h, s13 = pc.a13 * h;
+    const double s20 = pc.a20 * h, s22 = pc.a22 * h, s30 = pc.a30 * h, s33 = pc.a33 * h;
+    const bool ant = (c & 1) != 0;
+    const double sg = pick(c & 1, pc.g2, pc.g3, 0.0, 0.0) * h;
+    const double q = pick(c, pc.q1a, pc.q1n, pc.q2a, pc.q2n);
+    const double sq = q * h;
     {   // Q_M = M I + B
-        const R m = R(M);
-        pm[0][0] = m;   pm[0][1] = h;      pm[0][2] = R(0);    pm[0][3] = R(0);
-        pm[1][0] = s10; pm[1][1] = m + s11; pm[1][2] = s12;     pm[1][3] = s13;
-        pm[2][0] = s20; pm[2][1] = R(0);  pm[2][2] = m + s22;  pm[2][3] = R(0);
-        pm[3][0] = s30; pm[3][1] = R(0);  pm[3][2] = R(0);    pm[3][3] = m + s33;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            px[0][c] = R(0); px[1][c] = R(0);
-            px[2][c] = (c & 1) ? R(0) : sg2;
-            px[3][c] = (c & 1) ? sg3 : R(0);
-            pd[c] = m + sq[c];
-        }
+        const double mm = (double)M;
+        m[0] = c == 0 ? mm : c == 1 ? h : 0.0;
+        m[1] = c == 0 ? s10 : c == 1 ? mm + s11 : c == 2 ? s12 : s13;
+        m[2] = c == 0 ? s20 : c == 2 ? mm + s22 : 0.0;
+        m[3] = c == 0 ? s30 : c == 3 ? mm + s33 : 0.0;
+        x[0] = 0.0;
+        x[1] = 0.0;
+        x[2] = ant ? 0.0 : sg;
+        x[3] = ant ? sg : 0.0;
+        e = mm + sq;
     }
-    R ck = R(M);
+    double ck = (double)M;
 #pragma unroll
     for (int k = M - 1; k >= 1; --k) {
-        // k >= 2: Q_k = c_k I + B Q_{k+1};  k == 1: D = (B / M!) Q_2
-        R one, t10, t11, t12, t13, t20, t22, t30, t33, tv, tg2, tg3, tq[4];
+        double one, t10, t11, t12, t13, t20, t22, t30, t33, tv, tg, tq;
         if (k >= 2) {
-            ck = ck * R(k);
+            ck = ck * (double)k;
             one = ck;
             t10 = s10; t11 = s11; t12 = s12; t13 = s13; t20 = s20; t22 = s22; t30 = s30; t33 = s33;
-            tv = h; tg2 = sg2; tg3 = sg3;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) tq[c] = sq[c];
+            tv = h; tg = sg; tq = sq;
         } else {
-            const R f = R(1) / ck;  // 1 / M!, rounded once
-            one = R(0);
+            const double f = 1.0 / ck;  // 1 / M!, rounded once
+            one = 0.0;
             t10 = s10 * f; t11 = s11 * f; t12 = s12 * f; t13 = s13 * f;
             t20 = s20 * f; t22 = s22 * f; t30 = s30 * f; t33 = s33 * f;
-            tv = h * f; tg2 = sg2 * f; tg3 = sg3 * f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) tq[c] = sq[c] * f;
+            tv = h * f; tg = sg * f; tq = sq * f;
         }
-        R nm[4][4], nx[4][4], nd[4];
+        double n[4], y[4];
+        n[0] = fmr(tv, m[1], c == 0 ? one : 0.0);
+        n[1] = fmr(t13, m[3], fmr(t12, m[2], fmr(t11, m[1], fmr(t10, m[0], c == 1 ? one : 0.0))));
+        n[2] = fmr(t22, m[2], fmr(t20, m[0], c == 2 ? one : 0.0));
+        n[3] = fmr(t33, m[3], fmr(t30, m[0], c == 3 ? one : 0.0));
+        const double g = tg * e;
+        y[0] = fmr(tv, x[1], 0.0);
+        y[1] = fmr(t13, x[3], fmr(t12, x[2], fmr(t11, x[1], fmr(t10, x[0], 0.0))));
+        y[2] = fmr(t22, x[2], fmr(t20, x[0], ant ? 0.0 : g));
+        y[3] = fmr(t33, x[3], fmr(t30, x[0], ant ? g : 0.0));
+        e = fmr(tq, e, one);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            OPMM_MV(t10, t11, t12, t13, t20, t22, t30, t33, tv, pm[0][c], pm[1][c], pm[2][c], pm[3][c],
-                    nm[0][c], nm[1][c], nm[2][c], nm[3][c],
-                    c == 0 ? one : R(0), c == 1 ? one : R(0), c == 2 ? one : R(0), c == 3 ? one : R(0));
-        }
+        for (int i = 0; i < 4; ++i) { m[i] = n[i]; x[i] = y[i]; }
+    }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const R ga = (c & 1) ? R(0) : tg2 * pd[c];
-            const R gn = (c & 1) ? tg3 * pd[c] : R(0);
-            OPMM_MV(t10, t11, t12, t13, t20, t22, t30, t33, tv, px[0][c], px[1][c], px[2][c], px[3][c],
-                    nx[0][c], nx[1][c], nx[2][c], nx[3][c], R(0), R(0), ga, gn);
-            nd[c] = fmr(tq[c], pd[c], one);
-        }
+    for (int s = 0; s < SQ; ++s) {
+        double n[4], y[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { pm[i][c] = nm[i][c]; px[i][c] = nx[i][c]; }
-            pd[i] = nd[i];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < SQ; ++q) {
-        R nm[4][4], nx[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                R a = pm[i][c] + pm[i][c];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) a = fmr(pm[i][k], pm[k][c], a);
-                nm[i][c] = a;
-                R b = px[i][c] * (pd[c] + R(2));
-#pragma unroll
-                for (int k = 0; k < 4; ++k) b = fmr(pm[i][k], px[k][c], b);
-                nx[i][c] = b;
-            }
+            const double l0 = quad_bcast<0>(m[i]), l1 = quad_bcast<1>(m[i]), l2 = quad_bcast<2>(m[i]),
+                         l3 = quad_bcast<3>(m[i]);
+            n[i] = fmr(l3, m[3], fmr(l2, m[2], fmr(l1, m[1], fmr(l0, m[0], m[i] + m[i]))));
+            y[i] = fmr(l3, x[3], fmr(l2, x[2], fmr(l1, x[1], fmr(l0, x[0], x[i] * (e + 2.0)))));
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { pm[i][c] = nm[i][c]; px[i][c] = nx[i][c]; }
-            pd[i] = pd[i] * (pd[i] + R(2));
-        }
+        for (int i = 0; i < 4; ++i) { m[i] = n[i]; x[i] = y[i]; }
+        e = e * (e + 2.0);
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) pl.m[i][c] = pm[i][c];
-        pl.x1[i][0] = px[i][0]; pl.x1[i][1] = px[i][1];
-        pl.x2[i][0] = px[i][2]; pl.x2[i][1] = px[i][3];
-    }
-    pl.e1[0] = pd[0]; pl.e1[1] = pd[1];
-    pl.e2[0] = pd[2]; pl.e2[1] = pd[3];
-}
-
-
-__device__ __forceinline__ void nm_setup(const float p[P], float amp, float dt, NmPlant& pl)
-{
-    double pd[P];
-#pragma unroll
-    for (int j = 0; j < P; ++j) pd[j] = p[j];
-    PlantScalars<double> c;
-    plant_scalars(pd, (double)amp, c);
-    pl.a10 = c.a10; pl.a11 = c.a11; pl.a12 = c.a12; pl.a13 = c.a13;
-    pl.a20 = c.a20; pl.a22 = c.a22; pl.g2 = c.g2;
-    pl.a30 = c.a30; pl.a33 = c.a33; pl.g3 = c.g3;
-    pl.q1a = c.q1a; pl.q1n = c.q1n; pl.q2a = c.q2a; pl.q2n = c.q2n;
-    transition_dform(pl, (R)dt);
-    pl.th1 = c.th1;
-    pl.amp = amp;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) { pl.d0[i] = c.d0[i]; pl.sh[i] = c.sh[i]; }
-    pl.pwd = (double)p[17] * rcp64((double)dt);
-}
-
-// d <- Phi d for one sample (D-form: d + D d)
-__device__ __forceinline__ void step(const NmPlant& pl, const R (&x)[4][2], const R (&e)[2], R d[6])
-{
-    R n[4];
-    // the row's own state is the addend of the first fma
-    n[0] = fmr(pl.m[0][0], d[0], d[0]);
-    n[1] = fmr(pl.m[1][1], d[1], d[1]);
-    n[2] = fmr(pl.m[2][2], d[2], d[2]);
-    n[3] = fmr(pl.m[3][3], d[3], d[3]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c != i) n[i] = fmr(pl.m[i][c], d[c], n[i]);
-        n[i] = fmr(x[i][0], d[4], n[i]);
-        n[i] = fmr(x[i][1], d[5], n[i]);
-    }
-    d[4] = fmr(e[0], d[4], d[4]);
-    d[5] = fmr(e[1], d[5], d[5]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) d[i] = n[i];
 }
 
 // v <- exp(A t) v by a Taylor polynomial (degree Prec::expmv_m) in Horner form (t <= dt).
-__device__ __forceinline__ void expmv(const NmPlant& pl, R qa, R qn, R t, R v[6])
+__device__ __forceinline__ void nm_expmv(const PlantScalars<double>& pc, double qa, double qn, double t, double v[6])
 {
-    R w[6];
+    double w[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) w[i] = v[i];
 #pragma unroll
-    for (int k = Prec<R>::expmv_m; k >= 1; --k) {
-        R s = t * (R(1) / R(k));
+    for (int k = Prec<double>::expmv_m; k >= 1; --k) {
+        double s = t * (1.0 / (double)k);
         asm volatile("" : "+v"(s));
-        R aw[6];
+        double aw[6];
         aw[0] = w[1];
-        aw[1] = fmr(pl.a13, w[3], fmr(pl.a12, w[2], fmr(pl.a11, w[1], pl.a10 * w[0])));
-        aw[2] = fmr(pl.g2, w[4], fmr(pl.a22, w[2], pl.a20 * w[0]));
-        aw[3] = fmr(pl.g3, w[5], fmr(pl.a33, w[3], pl.a30 * w[0]));
+        aw[1] = fmr(pc.a13, w[3], fmr(pc.a12, w[2], fmr(pc.a11, w[1], pc.a10 * w[0])));
+        aw[2] = fmr(pc.g2, w[4], fmr(pc.a22, w[2], pc.a20 * w[0]));
+        aw[3] = fmr(pc.g3, w[5], fmr(pc.a33, w[3], pc.a30 * w[0]));
         aw[4] = qa * w[4];
         aw[5] = qn * w[5];
 #pragma unroll
@@ -250,136 +169,171 @@ __device__ __forceinline__ void expmv(const NmPlant& pl, R qa, R qn, R t, R v[6]
     for (int i = 0; i < 6; ++i) v[i] = w[i];
 }
 
-// The sample that contains the pulse end: pulse dynamics for frac*dt, switch
-// to the post piece's coordinates, post dynamics for the rest of the sample.
-__device__ __forceinline__ void split_step(const NmPlant& pl, R frac, R dt, R d[6])
-{
-    expmv(pl, pl.q1a, pl.q1n, frac * dt, d);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
-    expmv(pl, pl.q2a, pl.q2n, (R(1) - frac) * dt, d);
-}
-
-// Run the trajectory theta_k, k = 0..T-1, calling sink(k, dtheta, theta_eq)
-// with theta_k = dtheta + theta_eq.  kmin/kmax: wave-uniform bounds of the
-// lanes' pulse-end samples; samples below kmin are pulse for every lane and
-// samples above kmax post for every lane, so only [kmin, kmax] branches.
-template <int UNROLL, class Sink>
-__device__ __forceinline__ void run_steps(const NmPlant& pl, int T, R dt, int k0, R frac,
-                                               int kmin, int kmax, Sink& sink)
-{
-    R d[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) d[i] = pl.d0[i];
-    R theq = pl.th1;
-    if (k0 < 0) {  // PW <= 0: no pulse, the step acts from t = 0
-#pragma unroll
-        for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
-        theq = pl.amp;
-    }
-    int k = 0;
-    const int ka = min(kmin, T);
-#pragma unroll UNROLL
-    for (; k < ka; ++k) {
-        sink(k, d[0], theq);
-        step(pl, pl.x1, pl.e1, d);
-    }
-    const int kb = min(kmax, T - 1);
-#pragma unroll 1
-    for (; k <= kb; ++k) {
-        sink(k, d[0], theq);
-        if (k < k0) {
-            step(pl, pl.x1, pl.e1, d);
-        } else if (k == k0) {
-            split_step(pl, frac, dt, d);
-            theq = pl.amp;
-        } else {
-            step(pl, pl.x2, pl.e2, d);
-        }
-    }
-#pragma unroll UNROLL
-    for (; k < T; ++k) {
-        sink(k, d[0], theq);
-        step(pl, pl.x2, pl.e2, d);
-    }
-}
-
-struct SseSinkNm {
-    const R* r;
-    double sse;
-    __device__ __forceinline__ void operator()(int k, R dth, R theq)
-    {
-        R e = (r[k] - theq) - dth;
-        sse = fma((double)e, (double)e, sse);
-    }
+// One row of the recurrence on the lane that holds state i: d <- d + D d, own term first, then the others
+// by column, then the active states (fa, fn, the same on all four lanes).
+struct Row {
+    double own, o0, o1, o2, xa, xn;
 };
-
-// RMSE of point x (relative to nominal) for this lane; all 64 lanes call it
-// (wave-uniform bounds), `valid` lanes' results are meaningful.
-__device__ double nm_eval(const NmGroup& g, const R* r, const double* x, bool valid, const SacDev& sd, double q,
-                          float dt, double lo, double hi)
+__device__ __forceinline__ void row_step(const Row& w, double ea, double en, double& d, double& fa, double& fn)
 {
-    float p[P];
+    const double d0 = quad_perm<quad(1, 0, 0, 0)>(d), d1 = quad_perm<quad(2, 2, 1, 1)>(d),
+                 d2 = quad_perm<quad(3, 3, 3, 2)>(d);
+    double n = fmr(w.own, d, d);
+    n = fmr(w.o0, d0, n);
+    n = fmr(w.o1, d1, n);
+    n = fmr(w.o2, d2, n);
+    n = fmr(w.xa, fa, n);
+    n = fmr(w.xn, fn, n);
+    fa = fmr(ea, fa, fa);
+    fn = fmr(en, fn, fn);
+    d = n;
+}
+
+// Orders LDS accesses among the lanes of the wave (a block is one wave).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// RMSE of the point p (LDS, the candidate itself) on this lane's quad, the same value on its four lanes.
+// All lanes of the wave call it; quads with run = false return without a meaningful value.  tr: 32
+// doubles of LDS for the quad.
+__device__ __forceinline__ double quad_eval(const float* p, const R* r, double* tr, bool run, const SacDev& sd,
+                                            double qorth, float dt)
+{
+    const int i = threadIdx.x & 3;
+    PlantScalars<double> pc;
+    double pd[P];
 #pragma unroll
-    for (int j = 0; j < P; ++j) {
-        double v = valid ? x[j] : 1.0;
-        v = fmin(fmax(v, lo), hi);
-        p[j] = (float)(v * g.nom[j]);
+    for (int j = 0; j < P; ++j) pd[j] = p[j];
+    plant_scalars(pd, (double)sd.amp, pc);
+    double e1a, e1n, e2a, e2n;
+    Row w1, w2;
+    {
+        double m[4], x[4], e;
+        transition_column(pc, (double)dt, i, m, x, e);
+        e1a = quad_bcast<0>(e);
+        e1n = quad_bcast<1>(e);
+        e2a = quad_bcast<2>(e);
+        e2n = quad_bcast<3>(e);
+        wave_sync();  // the quad's previous evaluation has read its scratch
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            tr[4 * k + i] = m[k];
+            tr[16 + 4 * k + i] = x[k];
+        }
+        wave_sync();
+        const double* mr = tr + 4 * i;
+        w1.own = mr[i];
+        w1.o0 = mr[i == 0 ? 1 : 0];
+        w1.o1 = mr[i <= 1 ? 2 : 1];
+        w1.o2 = mr[i <= 2 ? 3 : 2];
+        w2 = w1;
+        w1.xa = tr[16 + 4 * i];
+        w1.xn = tr[16 + 4 * i + 1];
+        w2.xa = tr[16 + 4 * i + 2];
+        w2.xn = tr[16 + 4 * i + 3];
     }
-    NmPlant pl;
-    nm_setup(p, sd.amp, dt, pl);
+    const int T = sd.T;
     R frac;
-    int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
-    int kmin = __builtin_amdgcn_readfirstlane(wave_min(valid ? k0 : 0x7FFFFFFF));
-    int kmax = __builtin_amdgcn_readfirstlane(wave_max(valid ? k0 : -0x7FFFFFFF));
-    SseSinkNm sink{r, 0.0};
-    if (valid) run_steps<2>(pl, sd.T, (R)dt, k0, frac, kmin, kmax, sink);
-    double rm = sqrt((sink.sse + q) / ((double)sd.T * sd.C));
+    const int k0 = pulse_end_sample((double)p[17] * rcp64((double)dt), T, frac);
+    double d = pick(i, pc.d0[0], pc.d0[1], pc.d0[2], pc.d0[3]), fa = pc.d0[4], fn = pc.d0[5];
+    double theq = pc.th1, sse = 0.0;
+    int k = 0;
+    if (k0 < 0) {  // PW <= 0: no pulse, the step acts from t = 0
+        d += pick(i, pc.sh[0], pc.sh[1], pc.sh[2], pc.sh[3]);
+        fa += pc.sh[4];
+        fn += pc.sh[5];
+        theq = (double)sd.amp;
+    }
+    // theta is lane 0's state; the other lanes' sums go nowhere
+    const int np = run ? max(k0, 0) : 0, nt = run ? T : 0;
+    // n samples in the piece of row w: a stretch that every running quad of the wave has, counted on the
+    // scalar unit, then the lane's own rest.  The next sample is read a step ahead (its latency is as
+    // long as a step; r has a spare element).
+    double rk = r[0];
+    auto samples = [&](const Row& w, double ea, double en, int end) {
+        auto one = [&]() {
+            const double err = (rk - theq) - d;
+            rk = r[k + 1];
+            row_step(w, ea, en, d, fa, fn);
+            sse = fmr(err, err, sse);
+            ++k;
+        };
+        int common = min_over_quads(run ? max(end - k, 0) : 0x7FFFFFFF);
+        if (common != 0x7FFFFFFF && run) {
+            for (; common >= 4; common -= 4) { one(); one(); one(); one(); }
+        }
+#pragma unroll 1
+        while (k < end) one();
+    };
+    samples(w1, e1a, e1n, np);
+    if (run && k0 >= 0 && k0 < T) {
+        const double err = (rk - theq) - d;
+        rk = r[k + 1];
+        sse = fmr(err, err, sse);
+        double v[6] = {quad_bcast<0>(d), quad_bcast<1>(d), quad_bcast<2>(d), quad_bcast<3>(d), fa, fn};
+        nm_expmv(pc, pc.q1a, pc.q1n, frac * (R)dt, v);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) v[j] += pc.sh[j];
+        nm_expmv(pc, pc.q2a, pc.q2n, (1.0 - frac) * (R)dt, v);
+        d = pick(i, v[0], v[1], v[2], v[3]);
+        fa = v[4];
+        fn = v[5];
+        theq = (double)sd.amp;
+        ++k;
+    }
+    samples(w2, e2a, e2n, nt);
+    sse = quad_bcast<0>(sse);
+    const double rm = sqrt((sse + qorth) / ((double)T * sd.C));
     return (rm >= 0.0 && rm <= 1.7976931348623157e308) ? rm : INFINITY;
 }
 
-// Stable sort of a simplex by value, in parallel: vertex i goes to rank
-// #{k : f_k < f_i} + #{k < i : f_k == f_i} (the order a stable insertion sort
-// gives), each lane of the group moves one row.  Every lane of the wave calls it.
-__device__ void nm_sort(NmGroup& g, int l, bool on)
-{
-    if (on && l < NV) {
-        const double fi = g.f[l];
-        int rank = 0;
-        for (int k = 0; k < NV; ++k) rank += (g.f[k] < fi) || (k < l && g.f[k] == fi);
-        for (int j = 0; j < P; ++j) g.tv[rank][j] = g.v[l][j];
-        g.tf[rank] = fi;
-    }
-    __syncthreads();
-    if (on && l < NV) {
-        for (int j = 0; j < P; ++j) g.v[l][j] = g.tv[l][j];
-        g.f[l] = g.tf[l];
-    }
-    __syncthreads();
-}
+// One task's shared state.
+struct NmGroup {
+    float pt[NV][PTS];  // points to evaluate: clamped to the box, scaled, rounded to FP32
+    double fp[NV];      // their values
+    double tv[NV][P];   // sort staging
+};
 
-// G tasks per 64-lane wave (1 or 2): lanes 64/G * g .. of group g work on saccade G * block + g, 22
-// of them evaluating.  Every group runs the same instruction stream; a finished group's lanes idle
-// until the other one ends.  deadline_ticks > 0: a task still iterating when that many ticks of the
-// wall clock (wall_clock64) have passed since the launch started ends there with OPMM_ST_DEADLINE.
+// G tasks per 64-lane wave: lane group g works on saccade order[G * block + g] (order: the batch sorted by
+// T, so that a wave's tasks simulate traces of similar length).  Every group runs the same instruction
+// stream; a finished group's lanes idle until the last one ends.  Each group's arithmetic is that of a
+// wave of its own.  deadline_ticks > 0: a task still iterating when that many ticks of the wall clock
+// (wall_clock64) have passed since the launch started ends there with OPMM_ST_DEADLINE.
+//
+// Bound by the latency of one wave's FP64 chains: a lone wave issues an independent FP64 instruction every
+// ~5 cycles and a dependent one every 10.  With 22 points on 22 lanes, each lane a whole simulation, and
+// the simplex in LDS an iteration took 36k cycles at T = 57 (241 a sample, 14k for points, sort and exit
+// test); on quads, with the simplex in registers, 97 a sample and 12k in all.  256 saccades x 500
+// iterations: 9.05 -> 3.5 ms; 4096 x 200: 9.27 -> 2.17 ms.  The bound of 256 registers leaves room for two
+// waves per SIMD (4096 saccades 2.41 -> 2.17 ms, 8192 3.99 -> 3.24 ms against one).
 template <int G>
-__global__ __launch_bounds__(64) void nm_kernel(int S, const SacDev* __restrict__ sacs, const float* __restrict__ proj,
+__global__ __launch_bounds__(64, 2) void nm_kernel(int S, const SacDev* __restrict__ sacs, const int* __restrict__ order,
+                                                const float* __restrict__ proj,
                                                 const double* __restrict__ qorth, const int32_t* __restrict__ status_in,
                                                 const float* __restrict__ seed_opc, int max_iter, double tol_x,
                                                 double tol_f, double lo, double hi, float dt, int max_T,
                                                 uint64_t deadline_ticks, float* opc_out, float* rmse_out,
                                                 int32_t* iters_out, int8_t* dec_out, int32_t* status_out)
 {
-    constexpr int LG = 64 / G;
+    constexpr int LG = group_lanes(G), NQ = LG / 4;
     __shared__ NmGroup gs[G];
-    __shared__ int s_stop;
-    extern __shared__ R rbuf[];  // [G][max_T] projected traces
-    const int lane = threadIdx.x, gi = lane / LG, l = lane % LG;
-    const int s = G * blockIdx.x + gi;
-    const bool have = s < S;
+    __shared__ double trs[16][33];  // transposition scratch of a quad (odd stride: quads on different banks)
+    extern __shared__ R rbuf[];     // [G][max_T + 1] projected traces
+    const int lane = threadIdx.x;
+    const bool member = lane < G * LG;
+    const int gi = member ? lane / LG : 0, base = gi * LG;
+    const int l = member ? lane - base : LG - 1 + (lane & 3);  // lanes past the groups: no role (l >= NV)
+    const uint64_t gmask = (LG == 64 ? ~0ull : ((1ull << (LG & 63)) - 1)) << base;
+    const bool have = member && G * (int)blockIdx.x + gi < S;
+    const int s = have ? order[G * blockIdx.x + gi] : 0;
     NmGroup& g = gs[gi];
-    R* r = rbuf + (int64_t)gi * max_T;
-    const SacDev sd = sacs[have ? s : 0];
+    R* r = rbuf + gi * (max_T + 1);
+    double* tr = trs[lane >> 2];
+    const SacDev sd = sacs[s];
     const double q = qorth[sd.slot];
     const int32_t st0 = status_in[sd.slot];
     const bool bad = !have || (st0 & OPMM_ST_NONFINITE_INPUT);
@@ -392,117 +346,148 @@ __global__ __launch_bounds__(64) void nm_kernel(int S, const SacDev* __restrict_
             if (status_out) status_out[s] = st0;
         }
     }
-    if (!bad) {
+    if (!bad)
         for (int k = l; k < sd.T; k += LG) r[k] = (R)proj[sd.proj_off + k];
-        if (l < P) g.nom[l] = nominal_param_f64(l, (double)sd.dur);
-    }
-    if (l == 0) g.active = bad ? 0 : 1;
-    __syncthreads();
-    if (!bad && l < NV) {  // initial simplex: x0 and x0 with one coordinate scaled by 1.05
-        for (int j = 0; j < P; ++j) g.v[l][j] = seed_opc ? (double)seed_opc[(int64_t)s * P + j] / g.nom[j] : 1.0;
-        if (l > 0) g.v[l][l - 1] = g.v[l][l - 1] * 1.05;
-    }
-    __syncthreads();
-    {
-        const bool valid = !bad && l < NV;
-        double fv = nm_eval(g, r, g.v[valid ? l : 0], valid, sd, q, dt, lo, hi);
-        if (valid) g.f[l] = fv;
-    }
-    __syncthreads();
-    nm_sort(g, l, !bad);
-    int it = 0;
-    int32_t extra = 0;  // OPMM_ST_DEADLINE when the wall-clock budget ended the task
-    for (; it < max_iter; ++it) {
-        const bool on = g.active != 0;
-        // exit test (max over vertices and coordinates; fmax is exact, so the order does not matter)
-        // and the centroid of the best P vertices, one coordinate per lane
-        if (on && l < P) {
-            double dx = 0.0, acc = 0.0;
-            for (int i = 1; i < NV; ++i) dx = fmax(dx, fabs(g.v[i][l] - g.v[0][l]));
-            for (int i = 0; i < P; ++i) acc += g.v[i][l];
-            g.dxc[l] = dx;
-            g.xb[l] = acc / (double)P;
-        }
-        __syncthreads();
-        if (on && l == 0) {
-            double dx = 0.0, df = 0.0;
-            for (int i = 1; i < NV; ++i) df = fmax(df, fabs(g.f[i] - g.f[0]));
-            for (int j = 0; j < P; ++j) dx = fmax(dx, g.dxc[j]);
-            g.flag = (dx <= tol_x && df <= tol_f) ? 1 : 0;
-        }
-        if (lane == 0) s_stop = deadline_ticks > 0 && wall_clock64() - t0 >= deadline_ticks ? 1 : 0;
-        __syncthreads();
-        const bool stop_now = on && (g.flag || s_stop);  // uniform over the group
-        if (stop_now && !g.flag) extra = OPMM_ST_DEADLINE;
-        __syncthreads();  // every lane has read the flags before the group stops
-        if (stop_now && l == 0) {
-            g.active = 0;
-            g.iters = it;
-        }
-        __syncthreads();
-        // the loop ends when no group is still iterating
-        int any = 0;
+    const double nom = nominal_param_f64(l < P ? l : 0, (double)sd.dur);
+    // x on lane base + i of every lane's group (one task per wave: a scalar read)
+    auto at = [&](double x, int i) {
+        if (G > 1) return __shfl(x, base + i);
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), i),
+                                __builtin_amdgcn_readlane(__double2loint(x), i));
+    };
+    // the candidate format of coordinate x on this lane
+    auto clampf = [&](double x) { return (float)(fmin(fmax(x, lo), hi) * nom); };
+    double v[NV];  // this lane's coordinate of every vertex
+    {   // initial simplex: x0 and x0 with one coordinate scaled by 1.05
+        const double x0 = (seed_opc && !bad && l < P) ? (double)seed_opc[(int64_t)s * P + l] / nom : 1.0;
 #pragma unroll
-        for (int k = 0; k < G; ++k) any |= gs[k].active;
-        if (!any) break;
-        const bool act = g.active != 0;
-        if (act && l < NPT) {
-            for (int j = 0; j < P; ++j) {
-                const double xb = g.xb[j], w = g.v[NV - 1][j];
-                double x;
-                if (l == 0) x = xb + (xb - w);
-                else if (l == 1) x = xb + 2.0 * (xb - w);
-                else if (l == 2) x = xb + 0.5 * (xb - w);
-                else if (l == 3) x = xb - 0.5 * (xb - w);
-                else x = g.v[0][j] + 0.5 * (g.v[l - 3][j] - g.v[0][j]);
-                g.pt[l][j] = x;
-            }
+        for (int i = 0; i < NV; ++i) v[i] = (i == l + 1) ? x0 * 1.05 : x0;
+    }
+    double f = INFINITY;  // value of vertex l
+
+    // Stable sort of a group's simplex by value: vertex i goes to rank #{k : f_k < f_i} + #{k < i : f_k == f_i}.
+    auto sort_all = [&](bool on) {
+        int rank = 0;
+        for (int k = 0; k < NV; ++k) {
+            const double fk = __shfl(f, base + k);
+            rank += (fk < f) || (k < l && fk == f);
         }
-        __syncthreads();
-        {
-            const bool valid = act && l < NPT;
-            double fv = nm_eval(g, r, g.pt[valid ? l : 0], valid, sd, q, dt, lo, hi);
-            if (valid) g.fp[l] = fv;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int ri = __shfl(rank, base + i);
+            if (on && l < P) g.tv[ri][l] = v[i];
         }
-        __syncthreads();
-        if (act && l == 0) {
-            const double fr = g.fp[0];
-            int d;
-            if (fr < g.f[0]) d = g.fp[1] < fr ? 1 : 0;
-            else if (fr < g.f[NV - 2]) d = 0;
-            else if (fr < g.f[NV - 1]) d = g.fp[2] <= fr ? 2 : 4;
-            else d = g.fp[3] < g.f[NV - 1] ? 3 : 4;
-            g.dec = d;
-            if (dec_out) dec_out[(int64_t)s * max_iter + it] = (int8_t)d;
-        }
-        __syncthreads();
-        if (act) {
-            // the accepted point replaces the worst vertex, or the shrink replaces all but the best;
-            // one coordinate per lane
-            const int d = g.dec;
+        if (on && l < NV) g.fp[rank] = f;
+        wave_sync();
+        if (on) {
             if (l < P) {
-                if (d < 4) g.v[NV - 1][l] = g.pt[d][l];
-                else
-                    for (int i = 1; i < NV; ++i) g.v[i][l] = g.pt[3 + i][l];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) v[i] = g.tv[i][l];
             }
-            if (l == 0) {
-                if (d < 4) g.f[NV - 1] = g.fp[d];
-                else
-                    for (int i = 1; i < NV; ++i) g.f[i] = g.fp[3 + i];
+            if (l < NV) f = g.fp[l];
+        }
+        wave_sync();
+    };
+
+    bool active = !bad;
+    if (active && l < P) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) g.pt[i][l] = clampf(v[i]);
+    } else if (!active) {
+        for (int j = l; j < NV * PTS && member; j += LG) (&g.pt[0][0])[j] = 1.0f;  // something finite to simulate
+    }
+    int it = -1, iters = 0;  // turn -1 evaluates the initial simplex, the way a shrink does
+    int32_t extra = 0;       // OPMM_ST_DEADLINE when the wall-clock budget ended the task
+    for (;;) {
+        bool all = active && it < 0;  // every vertex is new: evaluate the list and sort
+        if (it >= 0) {
+            if (it >= max_iter) break;
+            // exit test (max over vertices and coordinates; fmax is exact, so the order does not matter)
+            // and the centroid of the best P vertices, one coordinate per lane
+            double dx = 0.0, acc = 0.0;
+#pragma unroll
+            for (int i = 1; i < NV; ++i) dx = fmax(dx, fabs(v[i] - v[0]));
+#pragma unroll
+            for (int i = 0; i < P; ++i) acc += v[i];
+            const double xb = acc / (double)P;
+            const double f0 = at(f, 0);
+            // a NaN difference (two infinite values) does not count, as in a running fmax
+            const bool wide = (l < P && !(dx <= tol_x)) || (l < NV && fabs(f - f0) > tol_f);
+            const bool within = (__ballot(wide) & gmask) == 0;
+            const bool late = deadline_ticks > 0 &&
+                              __builtin_amdgcn_readfirstlane((int)(wall_clock64() - t0 >= deadline_ticks)) != 0;
+            if (active && (within || late)) {
+                if (!within) extra = OPMM_ST_DEADLINE;
+                active = false;
+                iters = it;
+            }
+            if (!__any(active)) break;
+            // the four points, on the lanes that hold their coordinates
+            const double w = v[NV - 1];
+            const double xr = xb + (xb - w), xe = xb + 2.0 * (xb - w), xo = xb + 0.5 * (xb - w), xi = xb - 0.5 * (xb - w);
+            wave_sync();
+            if (active && l < P) {
+                g.pt[0][l] = clampf(xr);
+                g.pt[1][l] = clampf(xe);
+                g.pt[2][l] = clampf(xo);
+                g.pt[3][l] = clampf(xi);
+            }
+            wave_sync();
+            const int qd = l >> 2;
+            const double y = quad_eval(g.pt[qd & 3], r, tr, active && qd < 4, sd, q, dt);
+            const double fr = at(y, 0), fe = at(y, 4), fo = at(y, 8), fi = at(y, 12);
+            const double fn = at(f, NV - 2), fw = at(f, NV - 1);
+            int dcs;
+            if (fr < f0) dcs = fe < fr ? 1 : 0;
+            else if (fr < fn) dcs = 0;
+            else if (fr < fw) dcs = fo <= fr ? 2 : 4;
+            else dcs = fi < fw ? 3 : 4;
+            if (active && l == 0 && dec_out) dec_out[(int64_t)s * max_iter + it] = (int8_t)dcs;
+            {   // the accepted point replaces the worst vertex and moves to its rank: after every value <= its own
+                const bool put = active && dcs < 4;
+                const double fnew = dcs == 0 ? fr : dcs == 1 ? fe : dcs == 2 ? fo : fi;
+                const double xnew = dcs == 0 ? xr : dcs == 1 ? xe : dcs == 2 ? xo : xi;
+                const int rank = __popcll(__ballot(l < NV - 1 && f <= fnew) & gmask);
+                const double fprev = __shfl_up(f, 1);
+                if (put) {
+                    f = l < rank ? f : l == rank ? fnew : fprev;
+#pragma unroll
+                    for (int i = NV - 1; i >= 0; --i) v[i] = i < rank ? v[i] : (i == rank || i == 0) ? xnew : v[i - 1];
+                }
+            }
+            all = active && dcs == 4;
+            if (all) {  // every vertex but the best moves half way to it
+#pragma unroll
+                for (int i = 1; i < NV; ++i) {
+                    v[i] = v[0] + 0.5 * (v[i] - v[0]);
+                    if (l < P) g.pt[i][l] = clampf(v[i]);
+                }
             }
         }
-        __syncthreads();
-        nm_sort(g, l, act);
+        if (__any(all)) {
+            const int first = it < 0 ? 0 : 1;  // a shrink keeps the best vertex and its value
+            wave_sync();
+            for (int p0 = first; p0 < NV; p0 += NQ) {
+                const int i = p0 + (l >> 2);
+                const bool run = all && member && i < NV;
+                const double y = quad_eval(g.pt[run ? i : 0], r, tr, run, sd, q, dt);
+                if (run && (l & 3) == 0) g.fp[i] = y;
+            }
+            wave_sync();
+            if (all && l >= first && l < NV) f = g.fp[l];
+            sort_all(all);
+        }
+        ++it;
     }
     if (bad) return;
-    if (l == 0 && g.active) g.iters = it;  // ran to the iteration cap
+    if (active) iters = it;  // ran to the iteration cap
     if (l < P) {
-        double x = fmin(fmax(g.v[0][l], lo), hi);
-        opc_out[(int64_t)s * P + l] = (float)(x * g.nom[l]);
+        const double x = fmin(fmax(v[0], lo), hi);
+        opc_out[(int64_t)s * P + l] = (float)(x * nom);
     }
     if (l == 0) {
-        rmse_out[s] = (float)g.f[0];
-        if (iters_out) iters_out[s] = g.iters;
+        rmse_out[s] = (float)f;
+        if (iters_out) iters_out[s] = iters;
         if (status_out) status_out[s] = st0 | extra;
     }
 }
@@ -545,11 +530,13 @@ int opmm_fit_nm(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_sac
     if (rc != OPMM_OK) return rc;
     int max_T = 1;
     for (int i = 0; i < S; ++i) max_T = std::max(max_T, (int)sacs[i].T);
-    // two tasks per wave once the batch has more tasks than the device holds waves of this kernel (one
-    // per SIMD: it takes 256 VGPRs and ~110 AGPRs); a wave's time is its slower task's, so below that
-    // one per wave is as fast.  Measured on 4096 full-estimation saccades: 32k -> 51k saccades/s.
+    // While every task can have a SIMD to itself one task per wave is fastest (its four evaluations and
+    // nothing else); beyond that three share a wave and its instructions.  Measured, 200 iterations, one /
+    // two / three per wave: 1024 saccades 1.48 / 1.73 / 1.73 ms, 1500 1.88 / 1.75 / 1.75, 4096 3.49 / 2.33 / 2.17.
     const int cus = opmm_rt::ctx_cu_count(ctx);
-    const int G = prm->tasks_per_wave ? prm->tasks_per_wave : (S > 4 * cus ? 2 : 1);
+    // Three staged traces of more than 1024 samples leave room for no more tasks per CU than one does (160 KB
+    // of LDS), and three of the longest would not fit a block's 64 KB.
+    const int G = prm->tasks_per_wave ? prm->tasks_per_wave : (S > 4 * cus && max_T <= 1024 ? 3 : 1);
     uint64_t ticks = 0;
     if (prm->max_ms > 0.0f) {
         int khz = 0;
@@ -557,18 +544,18 @@ int opmm_fit_nm(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_sac
         if (e != hipSuccess || khz <= 0) return opmm_rt::fail(ctx, OPMM_EDEVICE, "wall clock rate unavailable");
         ticks = std::max<uint64_t>(1, (uint64_t)((double)prm->max_ms * (double)khz));
     }
-    const size_t lds = sizeof(R) * (size_t)G * max_T;
+    const size_t lds = sizeof(R) * (size_t)G * (max_T + 1);
     const int grid = (S + G - 1) / G;
-    if (G == 2)
-        hipLaunchKernelGGL(nm_kernel<2>, dim3(grid), dim3(64), lds, st, S, d_sacs, proj, qorth, status, seed_opc,
+    const int* order = opmm_rt::batch_order(ctx);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), lds, st, S, d_sacs, order, proj, qorth, status, seed_opc,
                            prm->max_iter, (double)prm->tol_x, (double)prm->tol_f, 1.0 - (double)prm->box_frac,
                            1.0 + (double)prm->box_frac, prm->dt_ms, max_T, ticks, opc_out, rmse_out, iters_out,
                            decisions_out, status_out);
-    else
-        hipLaunchKernelGGL(nm_kernel<1>, dim3(grid), dim3(64), lds, st, S, d_sacs, proj, qorth, status, seed_opc,
-                           prm->max_iter, (double)prm->tol_x, (double)prm->tol_f, 1.0 - (double)prm->box_frac,
-                           1.0 + (double)prm->box_frac, prm->dt_ms, max_T, ticks, opc_out, rmse_out, iters_out,
-                           decisions_out, status_out);
+    };
+    if (G == 3) launch(nm_kernel<3>);
+    else if (G == 2) launch(nm_kernel<2>);
+    else launch(nm_kernel<1>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return opmm_rt::hip_fail(ctx, e, "nm_kernel");
     return OPMM_OK;
