@@ -81,7 +81,7 @@ enum {
     OPMM_KERNEL_ROUND = 0,       /* one FP64 round of every tile (per-round mode)       */
     OPMM_KERNEL_SCREEN = 1,      /* FP32 pass of a screened round                       */
     OPMM_KERNEL_VERIFY = 2,      /* FP64 re-simulation of a screened round's survivors
-                                    (the FP64 anchor launch before it is not timed)     */
+                                    (an FP64 anchor launch before it is not timed)      */
     OPMM_KERNEL_PERSISTENT = 3,  /* the work-queue launch of a persistent fit           */
     OPMM_KERNEL_KINDS = 4
 };
@@ -126,9 +126,9 @@ typedef struct {
                             OPMM_FIT_PERSISTENT: one work-queue launch for
                             every round and saccade (uneven batches)         */
     int32_t tile;        /* kernel shape index; -1 = autotuned/default, and
-                            the 512-candidate tile for a launch with fewer
-                            tiles than the device has CUs (same results,
-                            each block finishes sooner)                      */
+                            a tile of 512 or 256 candidates for a launch with
+                            fewer tiles than the device has CUs (same
+                            results, each block finishes sooner)             */
     int32_t model;       /* 18: the 18-parameter OPMM (Section 2.2.1);
                             9: the 9-parameter OPMM (Section 2.2.2, Table 2):
                             one K_SE and one K_LT for both muscles (the
@@ -140,7 +140,9 @@ typedef struct {
                             the FP32 best b is simulated again in FP64, and
                             only the candidates whose FP32 RMSE is at most
                             RMSE64(b) + screen_tol / 2 are simulated again
-                            in FP64, which decides the argmin.  The winner
+                            in FP64, which decides the argmin (in a round
+                            where the anchor b spares less than it costs:
+                            at most RMSE32(b) + screen_tol).  The winner
                             is the FP64 argmin whenever the FP32 RMSE
                             errors stay below screen_tol / 2 (measured:
                             below 8.6e-6 deg; opmm_score_screen measures

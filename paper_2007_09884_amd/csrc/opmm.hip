@@ -45,33 +45,16 @@ constexpr int NBIN = 256;  // pulse-end sample bins of the in-tile sort
 // Small kernels
 // ---------------------------------------------------------------------------
 
-__global__ void fill_u64_kernel(uint64_t* p, int64_t n, uint64_t v)
+// Project saccade sd's trace on its movement direction, by one wave: r_k = h cos + v sin, and the energy
+// orthogonal to it, Q = sum (v cos - h sin)^2.  Then sum_k sum_c (pos - theta u)^2 = sum_k (r_k - theta_k)^2 + Q
+// for every theta.  Lanes take every 64th sample, then the wave combines Q and the finiteness flag.
+// Returns the status word (on every lane).
+__device__ __forceinline__ int32_t project_saccade(const SacDev& sd, const float* __restrict__ pos,
+                                                   float* __restrict__ proj, double* __restrict__ qorth)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-__global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-// Project each trace on the movement direction: r_k = h cos + v sin, and the
-// energy orthogonal to it, Q = sum (v cos - h sin)^2.  Then
-// sum_k sum_c (pos - theta u)^2 = sum_k (r_k - theta_k)^2 + Q for every theta.
-// One wave per saccade (block s): lanes take every 64th sample, then the
-// wave combines Q and the finiteness flag.
-__global__ __launch_bounds__(64) void prep_kernel(int S, const SacDev* __restrict__ sacs, const float* __restrict__ pos,
-                                                  float* __restrict__ proj, double* __restrict__ qorth,
-                                                  int32_t* __restrict__ status)
-{
-    const int s = blockIdx.x;
-    if (s >= S) return;
-    const SacDev sd = sacs[s];
     bool ok = true;
     double q = 0.0;
-    for (int k = threadIdx.x; k < sd.T; k += 64) {
+    for (int k = threadIdx.x & 63; k < sd.T; k += 64) {
         double h = pos[sd.pos_off + (int64_t)k * sd.C];
         double v = sd.C == 2 ? (double)pos[sd.pos_off + (int64_t)k * sd.C + 1] : 0.0;
         ok = ok && isfinite(h) && isfinite(v);
@@ -85,45 +68,77 @@ __global__ __launch_bounds__(64) void prep_kernel(int S, const SacDev* __restric
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) q += __shfl_xor(q, o);
     ok = __all(ok);
-    if (threadIdx.x == 0) {
-        qorth[sd.slot] = q;
-        status[sd.slot] = ok ? OPMM_ST_OK : OPMM_ST_NONFINITE_INPUT;
-    }
+    if ((threadIdx.x & 63) == 0) qorth[sd.slot] = q;
+    return ok ? OPMM_ST_OK : OPMM_ST_NONFINITE_INPUT;
 }
 
-// Round-0 box: centre = nominal (PW = D - 6), w = box_frac * centre, bounds
-// centre -/+ w; optional seed centre (clamped) and narrower round-0 width.
-__global__ void init_kernel(int S, const SacDev* __restrict__ sacs, float box_frac, float w_init_frac,
-                            const float* __restrict__ seed_opc, float* __restrict__ centre,
-                            float* __restrict__ hw, float* __restrict__ lo, float* __restrict__ hi,
-                            int32_t* __restrict__ status)
+// Component j of saccade sd's round-0 box (seed: its row of seed_opc, or null): centre = nominal (PW = D - 6),
+// w = box_frac * centre, bounds centre -/+ w; optional seed centre (clamped) and narrower round-0 width.
+__device__ __forceinline__ void init_box(const SacDev& sd, int j, float box_frac, float w_init_frac,
+                                         const float* __restrict__ seed, float* __restrict__ centre,
+                                         float* __restrict__ hw, float* __restrict__ lo, float* __restrict__ hi)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= S * P) return;
-    int s = i / P, j = i % P;
-    const int slot = sacs[s].slot;
-    float c0 = nominal_param(j, sacs[s].dur);
-    float w0 = (sacs[s].model == 9 && fixed_in_model9(j)) ? 0.0f : box_frac * c0;
+    float c0 = nominal_param(j, sd.dur);
+    float w0 = (sd.model == 9 && fixed_in_model9(j)) ? 0.0f : box_frac * c0;
     float l = c0 - w0, h = c0 + w0;
     float c = c0;
-    if (seed_opc) {
+    if (seed) {
         // 9-parameter model: tied components take the agonist's seed
-        const int js = (sacs[s].model == 9 && (j == 1 || j == 3)) ? j - 1 : j;
-        float v = seed_opc[(int64_t)s * P + js];
+        float v = seed[(sd.model == 9 && (j == 1 || j == 3)) ? j - 1 : j];
         c = (v == v) ? fminf(fmaxf(v, l), h) : c0;
-        if (j == 0) status[slot] |= OPMM_ST_SEEDED;
     }
-    const int64_t o = (int64_t)slot * P + j;
+    const int64_t o = (int64_t)sd.slot * P + j;
     centre[o] = c;
     hw[o] = w0 * w_init_frac;
     lo[o] = l;
     hi[o] = h;
 }
 
-__global__ void reset_keys_kernel(int n, const SacDev* __restrict__ sacs, uint64_t* keys)
+// The projection alone, for callers that read it before the search begins.
+__global__ __launch_bounds__(64) void prep_kernel(const SacDev* __restrict__ sacs, const float* __restrict__ pos,
+                                                  float* __restrict__ proj, double* __restrict__ qorth,
+                                                  int32_t* __restrict__ status)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) keys[sacs[i].slot] = ~0ull;
+    const SacDev sd = sacs[blockIdx.x];
+    const int32_t st = project_saccade(sd, pos, proj, qorth);
+    if (threadIdx.x == 0) status[sd.slot] = st;
+}
+
+// Everything a search needs before its first round, one wave per saccade: projection (unless it is queued
+// already: pos null), round-0 box, status, R keys key_stride apart, tile counters (done; ready and the
+// queue words of a persistent launch, nullable), FP32 best (nullable).  One launch where five small ones
+// (projection, box and three fills) took 10-12 us of a fit.
+__global__ __launch_bounds__(64) void begin_kernel(int R, int key_stride, const SacDev* __restrict__ sacs,
+                                                   const float* __restrict__ pos, float* __restrict__ proj,
+                                                   double* __restrict__ qorth, int32_t* __restrict__ status,
+                                                   float box_frac, float w_init_frac,
+                                                   const float* __restrict__ seed_opc, float* __restrict__ centre,
+                                                   float* __restrict__ hw, float* __restrict__ lo,
+                                                   float* __restrict__ hi, uint64_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ done, uint32_t* __restrict__ ready,
+                                                   uint32_t* __restrict__ head, uint64_t* __restrict__ smin)
+{
+    const int s = blockIdx.x, lane = threadIdx.x;
+    const SacDev sd = sacs[s];
+    const int32_t st = pos ? project_saccade(sd, pos, proj, qorth) : status[sd.slot];
+    if (lane == 0) {
+        status[sd.slot] = st | (seed_opc ? OPMM_ST_SEEDED : 0);
+        done[sd.slot] = 0;
+        if (ready) ready[sd.slot] = 0;
+        if (smin) smin[sd.slot] = ~0ull;
+        if (head && s == 0) head[0] = head[1] = 0;  // queue head, give-ups
+    }
+    if (lane < P)
+        init_box(sd, lane, box_frac, w_init_frac, seed_opc ? seed_opc + (int64_t)s * P : nullptr, centre, hw, lo, hi);
+    for (int r = lane; r < R; r += 64) keys[(int64_t)r * key_stride + sd.slot] = ~0ull;
+}
+
+// Orders memory accesses among the lanes of a wave.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ void load_box(Box& b, int s, const float* centre, const float* hw,
@@ -140,44 +155,63 @@ __device__ __forceinline__ void load_box(Box& b, int s, const float* centre, con
     }
 }
 
-// next centre = winner of round r, half-width *= shrink (one thread / saccade)
-__device__ __forceinline__ void refine_one(const SacDev& sd, int s, int r, uint64_t key, float shrink,
-                                           float* centre, float* hw, const float* lo, const float* hi,
-                                           int32_t* status)
+// Component j of the next centre, the winner of round r (its key), and of the next half-width, shrink times
+// the last.  Lanes 0 .. 17 of a block call it, one component each.
+__device__ __forceinline__ void refine_component(const SacDev& sd, int s, int r, uint64_t key, float shrink, int j,
+                                                 float* centre, float* hw, const float* lo, const float* hi,
+                                                 int32_t* status)
 {
-    Box b;
-    for (int j = 0; j < P; ++j) {
-        b.c[j] = centre[s * P + j];
-        b.w[j] = hw[s * P + j];
-        b.lo[j] = lo[s * P + j];
-        b.hi[j] = hi[s * P + j];
-    }
     uint32_t idx = (uint32_t)(key & 0xFFFFFFFFull);
     if ((key >> 32) >= 0x7F800000ull) {
-        atomicOr(&status[s], (int32_t)OPMM_ST_NO_FINITE_CANDIDATE);
+        if (j == 0) atomicOr(&status[s], (int32_t)OPMM_ST_NO_FINITE_CANDIDATE);
         idx = 0;
     }
-    float p[P];
-    draw_candidate(sd.seed, (uint32_t)r, idx, b, p, sd.model);
-    for (int j = 0; j < P; ++j) {
-        centre[s * P + j] = p[j];
-        hw[s * P + j] = b.w[j] * shrink;
+    // 9-parameter model: tied components follow the agonist's
+    const int js = (sd.model == 9 && (j == 1 || j == 3)) ? j - 1 : j;
+    const float w = hw[s * P + j];
+    float v = centre[s * P + js];
+    if (idx != 0) {
+        const uint64_t z = splitmix64(sd.seed, stream_counter((uint32_t)r, idx, js >> 1));
+        const uint32_t u = (js & 1) ? (uint32_t)(z >> 16) & 0xFFFFFFu : (uint32_t)(z >> 40);
+        v = box_draw(u, v, hw[s * P + js], lo[s * P + js], hi[s * P + js]);
     }
+    wave_fence();  // every lane has read its pair's centre and width
+    centre[s * P + j] = v;
+    hw[s * P + j] = w * shrink;
 }
 
-// round >= 0: every saccade is at that round and keys are [round][key_stride];
-// round < 0: each saccade is at its own sd.round and keys are [slot].
-__global__ void refine_kernel(int S, const SacDev* __restrict__ sacs, int round, int key_stride,
-                              const uint64_t* __restrict__ keys, float shrink, float* centre, float* hw,
-                              const float* lo, const float* hi, int32_t* status)
+// Lowers *key to best and counts the tile in *done, in this order for every observer: both are atomics that
+// take effect where all XCDs meet, and the count waits for the minimum's return.  Nothing else passes
+// between the tiles' blocks, so no fence is needed (an agent-scope one writes the XCD's L2 back: with it
+// in every block the verify pass of 2048 x 1024 candidates took 71 us instead of 17).  Returns the tiles
+// counted before.
+__device__ __forceinline__ uint32_t post_tile(uint64_t best, uint64_t* key, uint32_t* done)
 {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    const SacDev sd = sacs[s];
-    if (status[sd.slot] & OPMM_ST_NONFINITE_INPUT) return;
-    const int r = round >= 0 ? round : sd.round;
-    refine_one(sd, sd.slot, r, keys[(int64_t)(round >= 0 ? r : 0) * key_stride + sd.slot], shrink, centre, hw, lo,
-               hi, status);
+    if (best != ~0ull) {
+        unsigned long long old = atomicMin((unsigned long long*)key, (unsigned long long)best);
+        asm volatile("s_waitcnt vmcnt(0)" : "+v"(old) : : "memory");
+    }
+    return atomicAdd(done, 1u);
+}
+
+// A tile of the saccade is searched (best: its least key, on thread 0).  The block that posts the last of the
+// saccade's tiles refines it and leaves the counter at 0 for the next round; reset (nullable): a key
+// put back to its start value.
+__device__ __forceinline__ void finish_tile(const SacDev& sd, int s, int r, uint64_t best, uint64_t* key,
+                                            uint32_t* done, uint64_t* reset, float shrink, float* centre, float* hw,
+                                            const float* lo, const float* hi, int32_t* status)
+{
+    if (threadIdx.x >= 64) return;
+    int last = 0;
+    if (threadIdx.x == 0) last = post_tile(best, key, done) + 1 == (uint32_t)sd.tiles;
+    if (!__shfl(last, 0)) return;
+    const uint64_t k = __hip_atomic_load(key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x < P) refine_component(sd, s, r, k, shrink, threadIdx.x, centre, hw, lo, hi, status);
+    wave_fence();  // every lane has read the key
+    if (threadIdx.x == 0) {
+        *done = 0;
+        if (reset) *reset = ~0ull;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -198,25 +232,6 @@ struct TrajSink {  // theta_k to global memory
     float* out;
     __device__ __forceinline__ R begin(int, R u) const { return -u; }
     __device__ __forceinline__ void end(int k, R e) { out[k] = (float)-e; }
-};
-
-struct Cost2dSink {  // both channels, FP64 accumulation (reporting only)
-    const float* pos;
-    int C;
-    double cphi, sphi, sq, ab;
-    __device__ __forceinline__ R begin(int, R u) const { return -u; }
-    __device__ __forceinline__ void end(int k, R e)
-    {
-        const double th = -(double)e;
-        double e0 = (double)pos[(int64_t)k * C] - th * cphi;
-        sq += e0 * e0;
-        ab += fabs(e0);
-        if (C == 2) {
-            double e1 = (double)pos[(int64_t)k * C + 1] - th * sphi;
-            sq += e1 * e1;
-            ab += fabs(e1);
-        }
-    }
 };
 
 __device__ __forceinline__ uint64_t cost_key(double sse64, uint32_t idx)
@@ -408,16 +423,16 @@ __device__ __forceinline__ int saccade_of_tile(const SacDev* __restrict__ sacs, 
     return find_saccade_wave(sacs, S, b);
 }
 
-// One round over a batch: round >= 0 puts every saccade at that round with keys
-// [round][key_stride]; round < 0 takes each saccade's own round (sd.round) and
+// One round over a batch, and its refinement: the block that finishes a saccade's last tile moves the
+// saccade's box (a launch of its own for that took 5 us of every round).  round >= 0 puts every saccade
+// at that round with keys [round][key_stride]; round < 0 takes each saccade's own round (sd.round) and
 // keys [slot] (saccades admitted at different times, see the server).
 template <int TPB, int PASSES>
 __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_round_kernel(const SacDev* __restrict__ sacs, int S, int round,
-                                                        int key_stride, float dt, const float* __restrict__ proj,
-                                                        const float* centre, const float* hw,
-                                                        const float* lo, const float* hi,
-                                                        const int32_t* __restrict__ status,
-                                                        uint64_t* keys, const int* __restrict__ ord,
+                                                        int key_stride, float dt, float shrink,
+                                                        const float* __restrict__ proj, float* centre, float* hw,
+                                                        const float* lo, const float* hi, int32_t* status,
+                                                        uint64_t* keys, uint32_t* done, const int* __restrict__ ord,
                                                         const int* __restrict__ obase)
 {
     __shared__ TileSmem<TPB, PASSES> sm;
@@ -433,9 +448,8 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_round_kernel(const Sa
     const int t = blockIdx.x - sd.tile_base;
     const int r = round >= 0 ? round : sd.round;
     uint64_t best = process_tile<TPB, PASSES>(sm, sd, s, t, r, dt, proj, centre, hw, lo, hi);
-    if (threadIdx.x == 0 && best != ~0ull)
-        atomicMin((unsigned long long*)&keys[(int64_t)(round >= 0 ? r : 0) * key_stride + sd.slot],
-                  (unsigned long long)best);
+    uint64_t* key = &keys[(int64_t)(round >= 0 ? r : 0) * key_stride + sd.slot];
+    finish_tile(sd, sd.slot, r, best, key, &done[sd.slot], round >= 0 ? nullptr : key, shrink, centre, hw, lo, hi, status);
 }
 
 // Screened round, first pass: the round's tiles with the recurrence in FP32.  Every candidate's
@@ -469,15 +483,19 @@ __global__ __launch_bounds__(TPB, OPMM_SCREEN_MIN_WAVES) void fit_screen_kernel(
     if (threadIdx.x == 0 && best != ~0ull) atomicMin((unsigned long long*)&smin[sd.slot], (unsigned long long)best);
 }
 
-// Screened round, between the passes: one wave per saccade stages the trace in LDS, and its first
-// lane re-simulates the FP32 pass's best candidate b in FP64, exactly as the round kernel would, and
-// sets the verify threshold in SSE terms: FP32 RMSE <= RMSE64(b) + tau / 2.  The FP64 argmin x*
-// passes it whenever the FP32 error eps stays below tau / 2: RMSE32(x*) <= RMSE64(x*) + eps <=
-// RMSE64(b) + eps.  (With the FP32 best itself as the anchor the bound would need RMSE32(b) +
-// 2 eps, a threshold about tau / 2 wider.)  The trace sits in dynamic LDS of max_T doubles.
+// Screened round, between the passes: a lane re-simulates the FP32 pass's best candidate b of its saccade in
+// FP64, exactly as the round kernel would, and sets the verify threshold in SSE terms: FP32 RMSE <=
+// RMSE64(b) + tau / 2.  The FP64 argmin x* passes it whenever the FP32 error eps stays below tau / 2:
+// RMSE32(x*) <= RMSE64(x*) + eps <= RMSE64(b) + eps.  (With the FP32 best itself as the anchor the bound would
+// need RMSE32(b) + 2 eps, a threshold about tau / 2 wider.)
+// Bound by one simulation's latency (11 us).  A wave takes `per` saccades, a lane each, neighbours in the
+// dispatch order (similar T): as many as keep the launch to one wave per SIMD (2048 saccades on 2048 waves
+// shared the SIMDs and took 24 us), at most ANCHOR_MAX, and as fit their traces in 48 KB of dynamic LDS.
+constexpr int ANCHOR_MAX = 8;
 extern __shared__ R anchor_trace[];
 
-__global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restrict__ sacs, int round, float dt,
+__global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restrict__ sacs, int S, int per,
+                                                           const int* __restrict__ ord, int round, float dt,
                                                            const float* __restrict__ proj, const float* centre,
                                                            const float* hw, const float* lo, const float* hi,
                                                            const int32_t* __restrict__ status,
@@ -485,31 +503,42 @@ __global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restr
                                                            const uint64_t* __restrict__ smin, float tau, int max_T,
                                                            double* __restrict__ thr)
 {
-    __shared__ Box box;
-    const SacDev sd = sacs[blockIdx.x];
+    __shared__ Box box[ANCHOR_MAX];
+    const int lane = threadIdx.x, i0 = blockIdx.x * per;
+    const int n = min(per, S - i0);
+    {   // 64 / per lanes stage each saccade (per is a power of two)
+        const int w = 64 / per, i = lane / w, l = lane % w;
+        if (i < n) {
+            const SacDev sd = sacs[ord ? ord[i0 + i] : i0 + i];
+            for (int j = l; j < 4 * P; j += w) {
+                const float* src = j < P ? centre : j < 2 * P ? hw : j < 3 * P ? lo : hi;
+                (&box[i].c[0])[j] = src[sd.slot * P + j % P];
+            }
+            if (sd.T <= max_T)
+                for (int k = l; k < sd.T; k += w) anchor_trace[i * max_T + k] = (R)proj[sd.proj_off + k];
+        }
+    }
+    __syncthreads();
+    if (lane >= n) return;
+    const SacDev sd = sacs[ord ? ord[i0 + lane] : i0 + lane];
     const int slot = sd.slot;
     const uint64_t key = smin[slot];
     const float fbest = __uint_as_float((uint32_t)(key >> 32));
     if ((status[slot] & OPMM_ST_NONFINITE_INPUT) || !(fbest <= 3.402823466e38f) || sd.T > max_T) {
-        if (threadIdx.x == 0) thr[slot] = __builtin_inf();  // every candidate is verified
+        thr[slot] = __builtin_inf();  // every candidate is verified
         return;
     }
-    R* const r = anchor_trace;
-    for (int k = threadIdx.x; k < sd.T; k += 64) r[k] = (R)proj[sd.proj_off + k];
-    load_box(box, slot, centre, hw, lo, hi);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
     float p[P];
-    draw_candidate(sd.seed, (uint32_t)round, (uint32_t)key, box, p, sd.model);
+    draw_candidate(sd.seed, (uint32_t)round, (uint32_t)key, box[lane], p, sd.model);
     Plant pl;
     plant_setup(p, sd.amp, dt, pl);
     R frac;
     const int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
-    SseSink sink{r, 0.0};
+    SseSink sink{anchor_trace + lane * max_T, 0.0};
     run_blocks(pl, sd.T, k0, frac, sink);
-    const double n = (double)sd.T * sd.C, q = qorth[slot];
-    const double rm = sqrt((sink.sse + q) / n) + 0.5 * (double)tau;
-    thr[slot] = rm <= 1e300 ? rm * rm * n - q : __builtin_inf();  // a non-finite anchor verifies all
+    const double m = (double)sd.T * sd.C, q = qorth[slot];
+    const double rm = sqrt((sink.sse + q) / m) + 0.5 * (double)tau;
+    thr[slot] = rm <= 1e300 ? rm * rm * m - q : __builtin_inf();  // a non-finite anchor verifies all
 }
 
 // Screened round, second pass, one wave per tile (a tile's survivors are often fewer than one
@@ -520,6 +549,19 @@ __global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restr
 // orthogonal energy, RMSE = sqrt((SSE + Q) / n), so a candidate passes when its FP32 SSE <=
 // (RMSE64(b) + tau / 2)^2 n - Q.  A tile whose least FP32 SSE (tmin, 0 when one is NaN) misses that
 // is left without reading its costs.
+// Verify threshold (SSE units) without an anchor: FP32 RMSE <= RMSE32(b) + tau for the FP32 best b.  The FP64
+// argmin x* passes under the same condition eps <= tau / 2: RMSE32(x*) <= RMSE64(x*) + eps <= RMSE64(b) + eps
+// <= RMSE32(b) + 2 eps.
+__device__ __forceinline__ double best_threshold(const SacDev& sd, const uint64_t* smin,
+                                                 const double* __restrict__ qorth, float tau)
+{
+    const float best = __uint_as_float((uint32_t)(smin[sd.slot] >> 32));
+    if (!(best <= 3.402823466e38f)) return __builtin_inf();  // every candidate is verified
+    const double m = (double)sd.T * sd.C, q = qorth[sd.slot];
+    const double rm = sqrt(((double)best + q) / m) + (double)tau;
+    return rm <= 1e300 ? rm * rm * m - q : __builtin_inf();
+}
+
 template <int TILE>
 struct VerifySmem {
     Box box;
@@ -532,9 +574,10 @@ extern __shared__ R verify_trace[];
 template <int TILE>
 __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
     const SacDev* __restrict__ sacs, int S, int round, int key_stride, float dt, const float* __restrict__ proj,
-    const float* centre, const float* hw, const float* lo, const float* hi, const int32_t* __restrict__ status,
-    uint64_t* keys, const int* __restrict__ ord, const int* __restrict__ obase, const uint64_t* __restrict__ costs,
-    const uint32_t* __restrict__ tmin, const double* __restrict__ vthr, int max_T)
+    float shrink, float* centre, float* hw, const float* lo, const float* hi, int32_t* status, uint64_t* keys,
+    uint32_t* done, const int* __restrict__ ord, const int* __restrict__ obase, const uint64_t* __restrict__ costs,
+    const uint32_t* __restrict__ tmin, const double* __restrict__ vthr, const double* __restrict__ qorth, float tau,
+    uint64_t* smin, int max_T)
 {
     static_assert(TILE % 64 == 0 && TILE <= 65536, "tile");
     constexpr int CH = TILE / 64;  // 64-slot chunks of the tile
@@ -543,29 +586,35 @@ __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
     const int lane = threadIdx.x;
     const int s = __builtin_amdgcn_readfirstlane(saccade_of_tile(sacs, ord, obase, S, blockIdx.x));
     const SacDev sd = sacs[s];
-    if ((status[sd.slot] & OPMM_ST_NONFINITE_INPUT) || sd.T > max_T) return;  // max_T bounds the trace's LDS
+    if (status[sd.slot] & OPMM_ST_NONFINITE_INPUT) return;
     const int t = blockIdx.x - sd.tile_base;
     const int T = sd.T;
-    const double thr = vthr[sd.slot];
-    if (!((double)__uint_as_float(tmin[sd.tile_base + t]) <= thr)) return;
-    // compaction in slot order, 64 slots at a time, PFV chunks of loads in flight
-    const uint64_t* tc = costs + (int64_t)(sd.tile_base + t) * TILE + lane;
-    uint64_t vals[PFV];
-#pragma unroll
-    for (int c = 0; c < PFV; ++c) vals[c] = tc[64 * c];
+    const double thr = vthr ? vthr[sd.slot] : best_threshold(sd, smin, qorth, tau);
     int nv = 0;
+    // (max_T bounds the trace's LDS)
+    if ((double)__uint_as_float(tmin[sd.tile_base + t]) <= thr && T <= max_T) {
+        // compaction in slot order, 64 slots at a time, PFV chunks of loads in flight
+        const uint64_t* tc = costs + (int64_t)(sd.tile_base + t) * TILE + lane;
+        uint64_t vals[PFV];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const uint64_t v = vals[c % PFV];
-        if (c + PFV < CH) vals[c % PFV] = tc[64 * (c + PFV)];
-        const uint32_t j = (uint32_t)v;
-        const float f = __uint_as_float((uint32_t)(v >> 32));
-        const bool pass = j != 0xFFFFFFFFu && ((double)f <= thr || f != f);
-        const uint64_t m = __ballot(pass);
-        if (pass) sm.list[nv + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)j;
-        nv += __popcll(m);
+        for (int c = 0; c < PFV; ++c) vals[c] = tc[64 * c];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const uint64_t v = vals[c % PFV];
+            if (c + PFV < CH) vals[c % PFV] = tc[64 * (c + PFV)];
+            const uint32_t j = (uint32_t)v;
+            const float f = __uint_as_float((uint32_t)(v >> 32));
+            const bool pass = j != 0xFFFFFFFFu && ((double)f <= thr || f != f);
+            const uint64_t m = __ballot(pass);
+            if (pass) sm.list[nv + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)j;
+            nv += __popcll(m);
+        }
     }
-    if (nv == 0) return;
+    uint64_t* key = &keys[(int64_t)round * key_stride + sd.slot];
+    if (nv == 0) {
+        finish_tile(sd, sd.slot, round, ~0ull, key, &done[sd.slot], &smin[sd.slot], shrink, centre, hw, lo, hi, status);
+        return;
+    }
     R* const r = verify_trace;
     for (int k = lane; k < T; k += 64) r[k] = (R)proj[sd.proj_off + k];
     load_box(sm.box, sd.slot, centre, hw, lo, hi);
@@ -592,8 +641,7 @@ __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
         }
     }
     best = wave_min_u64(best);
-    if (lane == 0 && best != ~0ull)
-        atomicMin((unsigned long long*)&keys[(int64_t)round * key_stride + sd.slot], (unsigned long long)best);
+    finish_tile(sd, sd.slot, round, best, key, &done[sd.slot], &smin[sd.slot], shrink, centre, hw, lo, hi, status);
 }
 
 // Every round of every saccade in one launch: a work queue of (round, tile)
@@ -613,7 +661,9 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_persistent_kernel(
     const int* __restrict__ ord, const int* __restrict__ obase, uint32_t wait_limit)
 {
     __shared__ TileSmem<TPB, PASSES> sm;
-    __shared__ int s_item, s_sac, s_gaveup;
+    __shared__ int s_item, s_sac, s_gaveup, s_last;
+    __shared__ uint64_t s_key;
+    if (threadIdx.x == 0) s_last = 0;
     const int64_t total = (int64_t)R * tiles_per_round;
     for (;;) {
         if (threadIdx.x == 0) s_item = (int)atomicAdd(head, 1u);
@@ -657,15 +707,20 @@ __global__ __launch_bounds__(TPB, OPMM_MIN_WAVES) void fit_persistent_kernel(
             uint64_t best = ~0ull;
             if (!s_gaveup) best = process_tile<TPB, PASSES>(sm, sd, s, t, r, dt, proj, centre, hw, lo, hi);
             if (threadIdx.x == 0) {
-                if (best != ~0ull)
-                    atomicMin((unsigned long long*)&keys[(int64_t)r * S + s], (unsigned long long)best);
-                __threadfence();
-                uint32_t old = atomicAdd(&done[s], 1u);
-                if (old + 1 == (uint32_t)((r + 1) * sd.tiles)) {
+                if (post_tile(best, &keys[(int64_t)r * S + s], &done[s]) + 1 == (uint32_t)((r + 1) * sd.tiles)) {
+                    s_key = __hip_atomic_load(&keys[(int64_t)r * S + s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    s_last = 1;
+                }
+            }
+            __syncthreads();
+            if (s_last) {
+                if (threadIdx.x < P) {
+                    refine_component(sd, s, r, s_key, shrink, threadIdx.x, centre, hw, lo, hi, status);
                     __threadfence();
-                    uint64_t key = __hip_atomic_load(&keys[(int64_t)r * S + s], __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-                    refine_one(sd, s, r, key, shrink, centre, hw, lo, hi, status);
+                }
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    s_last = 0;
                     __threadfence();
                     __hip_atomic_store(&ready[s], (uint32_t)(r + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                 }
@@ -687,35 +742,54 @@ __global__ void harvest_giveups_kernel(const uint32_t* __restrict__ errflag, uin
 
 // Final report: re-simulate each saccade's winner and score it on the full
 // 2-channel trace (RMSE and mean absolute difference), FP64 accumulation.
-// One wave per saccade (block s): the wave stages the trace in LDS, every
-// lane runs the same simulation and lane 0 writes the results.
+// One wave per saccade (block s): every lane runs the same simulation into LDS, then lanes take every 64th
+// sample's residuals (on one lane, sample by sample, they were half of the report's 17 us).
+struct ThetaSink {  // theta_k to LDS
+    double* th;
+    __device__ __forceinline__ R begin(int, R u) const { return -u; }
+    __device__ __forceinline__ void end(int k, R e) { th[k] = -(double)e; }
+};
+
 __global__ __launch_bounds__(64) void report_kernel(int S, const SacDev* __restrict__ sacs, const float* __restrict__ pos,
                                                     float dt, const float* __restrict__ centre, float* opc_out,
                                                     float* rmse_out, float* mae_out, const int32_t* __restrict__ status,
                                                     int32_t* status_out)
 {
-    __shared__ float tr[2 * OPMM_MAX_T];
-    const int s = blockIdx.x;
-    if (s >= S) return;
+    __shared__ double th[OPMM_MAX_T];
+    const int s = blockIdx.x, lane = threadIdx.x;
     const SacDev sd = sacs[s];
-    for (int i = threadIdx.x; i < sd.T * sd.C; i += 64) tr[i] = pos[sd.pos_off + i];
-    __syncthreads();
     float p[P];
     for (int j = 0; j < P; ++j) p[j] = centre[(int64_t)sd.slot * P + j];
     Plant pl;
     plant_setup(p, sd.amp, dt, pl);
     R frac;
     const int k0 = pulse_end_sample(pl.pwd, sd.T, frac);
-    Cost2dSink sink{tr, sd.C, sd.cphi, sd.sphi, 0.0, 0.0};
+    ThetaSink sink{th};
     run_blocks(pl, sd.T, k0, frac, sink);
-    if (threadIdx.x != 0) return;
+    wave_fence();
+    double sq = 0.0, ab = 0.0;
+    for (int k = lane; k < sd.T; k += 64) {
+        const double e0 = (double)pos[sd.pos_off + (int64_t)k * sd.C] - th[k] * sd.cphi;
+        sq += e0 * e0;
+        ab += fabs(e0);
+        if (sd.C == 2) {
+            const double e1 = (double)pos[sd.pos_off + (int64_t)k * sd.C + 1] - th[k] * sd.sphi;
+            sq += e1 * e1;
+            ab += fabs(e1);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        sq += __shfl_xor(sq, o);
+        ab += __shfl_xor(ab, o);
+    }
+    if (lane != 0) return;
     const int32_t st = status[sd.slot];
     const bool bad = (st & OPMM_ST_NONFINITE_INPUT) != 0;
     const double n = (double)sd.T * sd.C;
     for (int j = 0; j < P; ++j) opc_out[s * P + j] = bad ? __int_as_float(0x7FC00000) : p[j];
-    double rm = sqrt(sink.sq / n);
-    rmse_out[s] = bad ? __int_as_float(0x7FC00000) : (float)rm;
-    if (mae_out) mae_out[s] = bad ? __int_as_float(0x7FC00000) : (float)(sink.ab / n);
+    rmse_out[s] = bad ? __int_as_float(0x7FC00000) : (float)sqrt(sq / n);
+    if (mae_out) mae_out[s] = bad ? __int_as_float(0x7FC00000) : (float)(ab / n);
     if (status_out) status_out[s] = st;
 }
 
@@ -812,8 +886,10 @@ const Shape kShapes[] = {
     {256, 4, "tpb256_pass4_unroll8"},
     {64, 16, "tpb64_pass16_unroll4"},
     {128, 8, "tpb128_pass8_unroll4"},
+    {256, 1, "tpb256_pass1"},  // of launches too small for one generation of waves; not a caller's choice
 };
-constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
+constexpr int kOnePassShape = sizeof(kShapes) / sizeof(kShapes[0]) - 1;
+constexpr int kNumShapes = kOnePassShape;  // the shapes of opmm_fit_params.tile
 constexpr int kDefaultShape = 9;  // fastest per-round shape on the full-estimation workload (sweep)
 
 struct FitLaunch {
@@ -827,6 +903,7 @@ struct FitLaunch {
     uint64_t* keys;
     uint32_t *head, *done, *ready, *errflag;
     int grid_persistent;
+    int simds;  // of the device
     const int *ord, *obase;  // dispatch order (nullable: record order)
     uint32_t wait_limit;     // polls of a persistent block waiting for its round
     // screened rounds: FP32 costs of every candidate, FP32 best per saccade, orthogonal energies
@@ -837,6 +914,7 @@ struct FitLaunch {
     double* vthr;     // [S]: verify threshold per saccade (SSE units, screen_anchor_kernel)
     const double* qorth;
     float tau;
+    float w0;            // round-0 half-width relative to nominal
     KernelTimer* timer;  // non-null: record an event pair around each search-kernel launch
 };
 
@@ -866,8 +944,8 @@ hipError_t launch_shape(const FitLaunch& L, bool persistent, int round, hipStrea
                            L.wait_limit);
     } else {
         hipLaunchKernelGGL((fit_round_kernel<TPB, PASSES>), dim3(L.tiles_per_round), dim3(TPB), 0, st,
-                           L.sacs, L.S, round, L.key_stride, L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status,
-                           L.keys, L.ord, L.obase);
+                           L.sacs, L.S, round, L.key_stride, L.dt, L.shrink, L.proj, L.centre, L.hw, L.lo, L.hi,
+                           L.status, L.keys, L.done, L.ord, L.obase);
     }
     return hipGetLastError();
 }
@@ -882,13 +960,23 @@ hipError_t launch_screened(const FitLaunch& L, int round, hipStream_t st)
                            L.costs, L.tmin, L.smin);
     }
     const int max_T = L.max_T > 0 && L.max_T <= OPMM_MAX_T ? L.max_T : OPMM_MAX_T;
-    hipLaunchKernelGGL(screen_anchor_kernel, dim3(L.S), dim3(64), sizeof(R) * (size_t)max_T, st, L.sacs, round,
-                       L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status, L.qorth, L.smin, L.tau, max_T, L.vthr);
+    // The anchor tightens the threshold by about tau / 2 and so spares FP64 simulations: on 256 x 65536
+    // candidates 0.45 us of verify time over the round's relative half-width w (10 us at 3 %, 220 us at
+    // 0.2 %), in proportion to the candidates, against the 11 us of its own launch.
+    const double w = (double)L.w0 * std::pow((double)L.shrink, round);
+    const bool anchor = (double)L.tiles_per_round * TPB * PASSES > 4.5e8 * w;
+    int per = 1;
+    while (anchor && 2 * per <= ANCHOR_MAX && per * L.simds < L.S && 2 * per * (int)sizeof(R) * max_T <= (48 << 10)) per *= 2;
+    if (anchor)
+        hipLaunchKernelGGL(screen_anchor_kernel, dim3((L.S + per - 1) / per), dim3(64), sizeof(R) * (size_t)max_T * per, st,
+                       L.sacs, L.S, per, L.ord, round, L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status, L.qorth,
+                       L.smin, L.tau, max_T, L.vthr);
     {
         TimedLaunch tl(L.timer, OPMM_KERNEL_VERIFY, st);
         hipLaunchKernelGGL(fit_verify_kernel<TPB * PASSES>, dim3(L.tiles_per_round), dim3(64),
-                           sizeof(R) * (size_t)max_T, st, L.sacs, L.S, round, L.key_stride, L.dt, L.proj, L.centre,
-                           L.hw, L.lo, L.hi, L.status, L.keys, L.ord, L.obase, L.costs, L.tmin, L.vthr, max_T);
+                           sizeof(R) * (size_t)max_T, st, L.sacs, L.S, round, L.key_stride, L.dt, L.proj, L.shrink,
+                           L.centre, L.hw, L.lo, L.hi, L.status, L.keys, L.done, L.ord, L.obase, L.costs, L.tmin,
+                           anchor ? L.vthr : nullptr, L.qorth, L.tau, L.smin, max_T);
     }
     return hipGetLastError();
 }
@@ -898,6 +986,7 @@ hipError_t launch_screened_round(int shape, const FitLaunch& L, int round, hipSt
 {
     switch (shape) {
     case 1: return launch_screened<256, 2>(L, round, st);
+    case kOnePassShape: return launch_screened<256, 1>(L, round, st);
     case 2:
     case 9: return launch_screened<256, 8>(L, round, st);
     case 3:
@@ -914,6 +1003,7 @@ hipError_t launch_fit_kernel(int shape, const FitLaunch& L, bool persistent, int
 {
     switch (shape) {
     case 1: return launch_shape<256, 2>(L, persistent, round, st);
+    case kOnePassShape: return launch_shape<256, 1>(L, persistent, round, st);
     case 2:
     case 9: return launch_shape<256, 8>(L, persistent, round, st);
     case 3:
@@ -940,6 +1030,7 @@ int shape_blocks_per_cu(int shape)
 {
     switch (shape) {
     case 1: return persistent_blocks_per_cu<256, 2>();
+    case kOnePassShape: return persistent_blocks_per_cu<256, 1>();
     case 2:
     case 9: return persistent_blocks_per_cu<256, 8>();
     case 3:
@@ -1280,7 +1371,7 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
                      float* mae_out, int32_t* status_out, hipStream_t st, bool run_prep);
 
 // Queue the whole fit on `st` (no host synchronisation inside: capturable).
-// run_prep = false: the projection of this upload is already queued (fit_stage).
+// run_prep = false: the projection of this upload is already queued.
 int enqueue_fit(opmm_ctx* ctx, FitScratch& sc, const float* pos, int S, int64_t total_T, int tiles_per_round,
                 const opmm_fit_params* prm, int shape, const float* seed_opc, float* opc_out, float* rmse_out,
                 float* mae_out, int32_t* status_out, uint64_t* round_keys, hipStream_t st, bool run_prep = true)
@@ -1342,13 +1433,9 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
     uint32_t* head = ready + S;
     uint32_t* errflag = head + 1;
 
-    if (run_prep) hipLaunchKernelGGL(prep_kernel, dim3(S), dim3(64), 0, st, S, d_sacs, pos, proj, qorth, status);
-    hipLaunchKernelGGL(init_kernel, dim3(blocks_for((int64_t)S * P, 256)), dim3(256), 0, st, S, d_sacs, prm->box_frac,
-                       prm->w_init_frac, seed_opc, centre, hw, lo, hi, status);
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks_for((int64_t)R * S, 256)), dim3(256), 0, st, keys,
-                       (int64_t)R * S, ~0ull);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(2 * (int64_t)S + 2, 256)), dim3(256), 0, st, done,
-                       2 * (int64_t)S + 2, 0u);
+    hipLaunchKernelGGL(begin_kernel, dim3(S), dim3(64), 0, st, R, S, d_sacs, run_prep ? pos : nullptr, proj, qorth,
+                       status, prm->box_frac, prm->w_init_frac, seed_opc, centre, hw, lo, hi, keys, done, ready, head,
+                       B.smin);
     OPMM_HIP(ctx, hipGetLastError());
 
     FitLaunch L;
@@ -1356,6 +1443,7 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
     L.shrink = prm->shrink; L.proj = proj; L.centre = centre; L.hw = hw; L.lo = lo; L.hi = hi;
     L.status = status; L.keys = keys; L.head = head; L.done = done; L.ready = ready; L.errflag = errflag;
     L.grid_persistent = 0;
+    L.simds = 4 * opmm_rt::ctx_cu_count(ctx);
     L.ord = B.order;
     L.obase = B.order ? B.order + S : nullptr;
     L.key_stride = S;
@@ -1367,6 +1455,7 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
     L.smin = B.smin;
     L.qorth = qorth;
     L.tau = prm->screen_tol;
+    L.w0 = prm->w_init_frac * prm->box_frac;
     L.timer = nullptr;
     if (ctx->timer.on) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -1388,15 +1477,10 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
                 if (r < prm->screen_rounds) {
                     if (!B.costs || !B.tmin || !B.smin || !B.vthr)
                         return fail(ctx, OPMM_EINVAL, "screened rounds need their buffers");
-                    hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks_for(S, 256)), dim3(256), 0, st, B.smin, (int64_t)S,
-                                       ~0ull);
                     OPMM_HIP(ctx, launch_screened_round(shape, L, r, st));
                 } else {
                     OPMM_HIP(ctx, launch_fit_kernel(shape, L, false, r, st));
                 }
-                hipLaunchKernelGGL(refine_kernel, dim3(blocks_for(S, 128)), dim3(128), 0, st, S, d_sacs, r, S, keys,
-                                   prm->shrink, centre, hw, lo, hi, status);
-                OPMM_HIP(ctx, hipGetLastError());
             }
         }
     }
@@ -1426,18 +1510,23 @@ int shape_for(const opmm_ctx* ctx, int64_t n_cand)
     return smallest;
 }
 
-// Smallest tile: 512 candidates, two per thread.
-constexpr int kSmallTileShape = 1;  // tpb256_pass2_unroll1
+constexpr int kSmallTileShape = 1;  // tpb256_pass2_unroll1: 512 candidates, two per thread
 
 // Shape for a launch of `tiles` tiles of shape `base`.  A launch with fewer tiles than the device
-// has CUs leaves CUs idle, and its time is one block's: the small tile (more, shorter blocks)
-// finishes sooner, e.g. one saccade x 4096 candidates in 0.075 instead of 0.125 ms per captured
-// fit.  This holds for a shape the autotuner picked too (it times full batches); only an explicit
-// opmm_fit_params.tile is kept as given.
+// has CUs leaves CUs idle, and its time is one block's: a small tile (more, shorter blocks) finishes sooner.
+// While one candidate per thread fits the device at once (the FP64 kernels hold two waves per SIMD, so two
+// blocks per CU) that is the shortest: one saccade x 4096 candidates 28.3 us per captured fit against
+// 34.9 with two and 75 with eight, a burst of 500 served saccades 631 us against 689; past that point
+// two per thread start fewer blocks (61 saccades x 4096 x 10: 290 against 295 us).  This holds for a shape the
+// autotuner picked too (it times full batches); only an explicit opmm_fit_params.tile is kept as given.
 int launch_shape_impl(const opmm_ctx* ctx, int base, int64_t tiles)
 {
+    const int64_t cus = std::max(ctx->cu_count, 1);
+    if (shape_tile(base) > shape_tile(kOnePassShape) &&
+        tiles * shape_tile(base) <= 2 * cus * shape_tile(kOnePassShape))
+        return kOnePassShape;
     if (shape_tile(base) <= shape_tile(kSmallTileShape)) return base;
-    return tiles < std::max(ctx->cu_count, 1) ? kSmallTileShape : base;
+    return tiles < cus ? kSmallTileShape : base;
 }
 
 int pow2_at_least(int64_t v)
@@ -1545,42 +1634,31 @@ SacDev make_record(const opmm_saccade& s, int n_cand_default)
 hipError_t launch_prep(const SacDev* sacs, int n, const float* pos, const SlotState& ss, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(prep_kernel, dim3(n), dim3(64), 0, st, n, sacs, pos, ss.proj, ss.qorth,
+    hipLaunchKernelGGL(prep_kernel, dim3(n), dim3(64), 0, st, sacs, pos, ss.proj, ss.qorth,
                        ss.status);
     return hipGetLastError();
 }
 
-hipError_t launch_init(const SacDev* sacs, int n, float box_frac, float w_init_frac, const float* seed_opc,
-                       const SlotState& ss, hipStream_t st)
+hipError_t launch_begin(const SacDev* sacs, int n, float box_frac, float w_init_frac, const float* seed_opc,
+                        const SlotState& ss, hipStream_t st)
 {
-    hipLaunchKernelGGL(init_kernel, dim3(blocks_for((int64_t)n * P, 256)), dim3(256), 0, st, n, sacs, box_frac,
-                       w_init_frac, seed_opc, ss.centre, ss.hw, ss.lo, ss.hi, ss.status);
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(begin_kernel, dim3(n), dim3(64), 0, st, 1, 0, sacs, (const float*)nullptr, ss.proj, ss.qorth,
+                       ss.status, box_frac, w_init_frac, seed_opc, ss.centre, ss.hw, ss.lo, ss.hi, ss.keys, ss.done,
+                       (uint32_t*)nullptr, (uint32_t*)nullptr, (uint64_t*)nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_reset_keys(const SacDev* sacs, int n, const SlotState& ss, hipStream_t st)
-{
-    hipLaunchKernelGGL(reset_keys_kernel, dim3(blocks_for(n, 128)), dim3(128), 0, st, n, sacs, ss.keys);
-    return hipGetLastError();
-}
-
-hipError_t launch_round(int shape, const SacDev* sacs, int n, int tiles_total, float dt, const SlotState& ss,
-                        hipStream_t st)
+hipError_t launch_round(int shape, const SacDev* sacs, int n, int tiles_total, float dt, float shrink,
+                        const SlotState& ss, hipStream_t st)
 {
     if (tiles_total <= 0) return hipSuccess;
     FitLaunch L;
     std::memset(&L, 0, sizeof L);
     L.sacs = sacs; L.S = n; L.R = 1; L.tiles_per_round = tiles_total; L.key_stride = 0; L.dt = dt;
     L.proj = ss.proj; L.centre = ss.centre; L.hw = ss.hw; L.lo = ss.lo; L.hi = ss.hi;
-    L.status = ss.status; L.keys = ss.keys;
+    L.status = ss.status; L.keys = ss.keys; L.done = ss.done; L.shrink = shrink;
     return launch_fit_kernel(shape, L, false, -1, st);
-}
-
-hipError_t launch_refine(const SacDev* sacs, int n, float shrink, const SlotState& ss, hipStream_t st)
-{
-    hipLaunchKernelGGL(refine_kernel, dim3(blocks_for(n, 128)), dim3(128), 0, st, n, sacs, -1, 0, ss.keys, shrink,
-                       ss.centre, ss.hw, ss.lo, ss.hi, ss.status);
-    return hipGetLastError();
 }
 
 hipError_t launch_report(const SacDev* sacs, int n, const float* pos, float dt, const SlotState& ss, float* opc_out,
@@ -1612,7 +1690,7 @@ int project_batch(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_s
     if ((rc = ensure(ctx, sc.qorth, sizeof(double) * S)) != OPMM_OK) return rc;
     if ((rc = ensure(ctx, sc.status, sizeof(int32_t) * S)) != OPMM_OK) return rc;
     if (S > 0) {
-        hipLaunchKernelGGL(prep_kernel, dim3(S), dim3(64), 0, st, S, (const SacDev*)sc.sacs.p, pos,
+        hipLaunchKernelGGL(prep_kernel, dim3(S), dim3(64), 0, st, (const SacDev*)sc.sacs.p, pos,
                            (float*)sc.proj.p, (double*)sc.qorth.p, (int32_t*)sc.status.p);
     }
     OPMM_HIP(ctx, hipGetLastError());
@@ -1637,7 +1715,9 @@ int fit_stage(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_sacca
     if ((rc = ensure(ctx, sc.proj, sizeof(float) * fs->total_T)) != OPMM_OK) return rc;
     if ((rc = ensure(ctx, sc.qorth, sizeof(double) * S)) != OPMM_OK) return rc;
     if ((rc = ensure(ctx, sc.status, sizeof(int32_t) * S)) != OPMM_OK) return rc;
-    hipLaunchKernelGGL(prep_kernel, dim3(S), dim3(64), 0, st, S, (const SacDev*)sc.sacs.p, pos, (float*)sc.proj.p,
+    fs->projected = proj != nullptr;
+    if (!proj) return OPMM_OK;
+    hipLaunchKernelGGL(prep_kernel, dim3(S), dim3(64), 0, st, (const SacDev*)sc.sacs.p, pos, (float*)sc.proj.p,
                        (double*)sc.qorth.p, (int32_t*)sc.status.p);
     OPMM_HIP(ctx, hipGetLastError());
     *sacs_dev = (const SacDev*)sc.sacs.p;
@@ -1651,7 +1731,7 @@ int fit_launch(opmm_ctx* ctx, const float* pos, int S, const FitStage& fs, const
 {
     if (S == 0) return OPMM_OK;
     return enqueue_fit(ctx, ctx->scratch, pos, S, fs.total_T, fs.tiles, prm, fs.shape, seed_opc, opc_out, rmse_out,
-                       mae_out, status_out, round_keys, st, false);
+                       mae_out, status_out, round_keys, st, !fs.projected);
 }
 
 int project_batch_full(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_saccade* sacs, int S,
@@ -1926,7 +2006,7 @@ int score_impl(opmm_ctx* ctx, const float* opc, int64_t n, const float* pos, int
     if ((rc = ensure(ctx, sc.proj, sizeof(float) * total_T)) != OPMM_OK) return rc;
     if ((rc = ensure(ctx, sc.qorth, sizeof(double))) != OPMM_OK) return rc;
     if ((rc = ensure(ctx, sc.status, sizeof(int32_t))) != OPMM_OK) return rc;
-    hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(64), 0, st, 1, (const SacDev*)sc.sacs.p, pos, (float*)sc.proj.p,
+    hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(64), 0, st, (const SacDev*)sc.sacs.p, pos, (float*)sc.proj.p,
                        (double*)sc.qorth.p, (int32_t*)sc.status.p);
     if (fp32)
         hipLaunchKernelGGL(score_kernel<float>, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, opc,
@@ -1964,9 +2044,7 @@ int opmm_fit(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_saccad
     opmm_rt::Ordered ord(ctx->order, st);
     OPMM_HIP(ctx, ord.error());
     opmm_rt::FitStage fs;
-    const SacDev* sd;
-    const float* proj;
-    int rc = opmm_rt::fit_stage(ctx, pos, pos_len, sacs, S, params, opc_out, rmse_out, &fs, &sd, &proj, st);
+    int rc = opmm_rt::fit_stage(ctx, pos, pos_len, sacs, S, params, opc_out, rmse_out, &fs, nullptr, nullptr, st);
     if (rc != OPMM_OK || S == 0) return rc;
     return opmm_rt::fit_launch(ctx, pos, S, fs, params, seed_opc, opc_out, rmse_out, mae_out, status_out, round_keys,
                                st);

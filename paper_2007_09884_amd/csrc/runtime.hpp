@@ -145,11 +145,13 @@ int project_batch(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_s
 // A fit in two halves, for callers that queue work of their own on the batch between the upload
 // and the search (the learned seed reads the projection).  fit_stage validates like opmm_fit,
 // uploads the records into the context's fit scratch and queues the projection; *sacs_dev and
-// *proj stay valid until the next fit on ctx.  fit_launch queues the search of that upload.
+// *proj stay valid until the next fit on ctx.  fit_launch queues the search of that upload.  With
+// proj (and sacs_dev) null the projection is left to fit_launch's first kernel.
 struct FitStage {
     int shape;
     int64_t total_T;
     int tiles;
+    bool projected;
 };
 int fit_stage(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_saccade* sacs, int S,
               const opmm_fit_params* prm, float* opc_out, float* rmse_out, FitStage* fs, const SacDev** sacs_dev,
@@ -183,19 +185,20 @@ struct SlotState {
     float *centre, *hw, *lo, *hi;  // [slots][18]
     int32_t* status;               // [slots]
     uint64_t* keys;                // [slots]: argmin key of the slot's current round
+    uint32_t* done;                // [slots]: tiles of that round searched
     float* proj;                   // projected traces (SacDev::proj_off)
     double* qorth;                 // [slots]
 };
 
 // Launchers over a compact device list of n records (each names its slot).
 hipError_t launch_prep(const SacDev* sacs, int n, const float* pos, const SlotState& ss, hipStream_t st);
-hipError_t launch_init(const SacDev* sacs, int n, float box_frac, float w_init_frac, const float* seed_opc,
-                       const SlotState& ss, hipStream_t st);
-hipError_t launch_reset_keys(const SacDev* sacs, int n, const SlotState& ss, hipStream_t st);
-// one round for every listed saccade at its own SacDev::round (records carry tile_base/tiles)
-hipError_t launch_round(int shape, const SacDev* sacs, int n, int tiles_total, float dt, const SlotState& ss,
-                        hipStream_t st);
-hipError_t launch_refine(const SacDev* sacs, int n, float shrink, const SlotState& ss, hipStream_t st);
+// box, status, key and tile counter of each listed slot, its trace already projected
+hipError_t launch_begin(const SacDev* sacs, int n, float box_frac, float w_init_frac, const float* seed_opc,
+                        const SlotState& ss, hipStream_t st);
+// one round for every listed saccade at its own SacDev::round (records carry tile_base/tiles), with its
+// refinement; the slot's key is back at its start value afterwards
+hipError_t launch_round(int shape, const SacDev* sacs, int n, int tiles_total, float dt, float shrink,
+                        const SlotState& ss, hipStream_t st);
 hipError_t launch_report(const SacDev* sacs, int n, const float* pos, float dt, const SlotState& ss, float* opc_out,
                          float* rmse_out, float* mae_out, int32_t* status_out, hipStream_t st);
 int shape_tile(int shape);

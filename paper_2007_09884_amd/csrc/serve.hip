@@ -112,6 +112,7 @@ struct opmm_server {
     float* d_box = nullptr;   // 4 x [slots][18]
     int32_t* d_status = nullptr;
     uint64_t* d_keys = nullptr;
+    uint32_t* d_done = nullptr;  // [slots], the one array the budget does not count (4 bytes a slot)
     float* d_proj = nullptr;  // [slots][max_T]
     double* d_qorth = nullptr;
     SacDev* d_list = nullptr;  // [slots] active / admitted / finished lists
@@ -254,6 +255,7 @@ int opmm_server_create(opmm_ctx* ctx, opmm_surrogate* sg, const opmm_serve_param
     dm((void**)&sv->d_box, sizeof(float) * 4 * P * (size_t)slots);
     dm((void**)&sv->d_status, sizeof(int32_t) * slots);
     dm((void**)&sv->d_keys, sizeof(uint64_t) * slots);
+    dm((void**)&sv->d_done, sizeof(uint32_t) * slots);
     dm((void**)&sv->d_proj, sizeof(float) * (size_t)slots * sv->max_T);
     dm((void**)&sv->d_qorth, sizeof(double) * slots);
     dm((void**)&sv->d_list, sizeof(SacDev) * slots);
@@ -296,6 +298,7 @@ int opmm_server_create(opmm_ctx* ctx, opmm_surrogate* sg, const opmm_serve_param
     sv->ss.hi = sv->d_box + 3 * (size_t)P * slots;
     sv->ss.status = sv->d_status;
     sv->ss.keys = sv->d_keys;
+    sv->ss.done = sv->d_done;
     sv->ss.proj = sv->d_proj;
     sv->ss.qorth = sv->d_qorth;
     sv->slot.resize(slots);
@@ -311,7 +314,8 @@ int opmm_server_destroy(opmm_server* sv)
     if (sv->stream) (void)hipStreamSynchronize(sv->stream);
     for (PolishBatch& b : sv->pb)
         if (b.stream) (void)hipStreamSynchronize(b.stream);
-    for (void* p : {(void*)sv->d_pos, (void*)sv->d_box, (void*)sv->d_status, (void*)sv->d_keys, (void*)sv->d_proj,
+    for (void* p : {(void*)sv->d_pos, (void*)sv->d_box, (void*)sv->d_status, (void*)sv->d_keys, (void*)sv->d_done,
+                    (void*)sv->d_proj,
                     (void*)sv->d_qorth, (void*)sv->d_list, (void*)sv->d_seed, (void*)sv->d_out, (void*)sv->d_st,
                     (void*)sv->d_adm_trace})
         if (p) (void)hipFree(p);
@@ -458,7 +462,7 @@ int opmm_server_step(opmm_server* sv, int32_t* n_done_out)
         const int n = (int)sv->reinit.size();
         for (int i = 0; i < n; ++i) h_re[i] = slot_record(sv, sv->reinit[i]);
         SV_HIP(hipMemcpyAsync(sv->d_list, h_re, sizeof(SacDev) * n, hipMemcpyHostToDevice, st));
-        SV_HIP(opmm_rt::launch_init(sv->d_list, n, box, sv->prm.plain.w_init_frac, nullptr, sv->ss, st));
+        SV_HIP(opmm_rt::launch_begin(sv->d_list, n, box, sv->prm.plain.w_init_frac, nullptr, sv->ss, st));
         sv->reinit.clear();
         queued = true;
     }
@@ -501,7 +505,7 @@ int opmm_server_step(opmm_server* sv, int32_t* n_done_out)
             seeds = sv->d_seed;
         }
         const opmm_fit_params& fp = phase_params(sv, PH_FIRST);
-        SV_HIP(opmm_rt::launch_init(sv->d_list, n, box, fp.w_init_frac, seeds, sv->ss, st));
+        SV_HIP(opmm_rt::launch_begin(sv->d_list, n, box, fp.w_init_frac, seeds, sv->ss, st));
         queued = true;
     }
     // 3. one round for every occupied slot, each at its own round; a step too small to fill the
@@ -533,9 +537,7 @@ int opmm_server_step(opmm_server* sv, int32_t* n_done_out)
             tiles += h_it[i].tiles;
         }
         SV_HIP(hipMemcpyAsync(sv->d_list, h_it, sizeof(SacDev) * na, hipMemcpyHostToDevice, st));
-        SV_HIP(opmm_rt::launch_reset_keys(sv->d_list, na, sv->ss, st));
-        SV_HIP(opmm_rt::launch_round(shape, sv->d_list, na, tiles, dt, sv->ss, st));
-        SV_HIP(opmm_rt::launch_refine(sv->d_list, na, phase_params(sv, PH_FIRST).shrink, sv->ss, st));
+        SV_HIP(opmm_rt::launch_round(shape, sv->d_list, na, tiles, dt, phase_params(sv, PH_FIRST).shrink, sv->ss, st));
         queued = true;
         std::vector<int> next;
         for (int k : act)
