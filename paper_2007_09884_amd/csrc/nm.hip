@@ -60,7 +60,7 @@ __device__ __forceinline__ int min_over_quads(int x)
 // fields it becomes an indexed load, and the struct goes to scratch memory.)
 __device__ __forceinline__ double pick(int i, double a, double b, double c, double d)
 {
-    OPMM_KEEP(a); OPMM_KEEP(b); OPMM_KEEP(c); OPMM_KEEP(d);
+    keep(a); keep(b); keep(c); keep(d);
     return i == 0 ? a : i == 1 ? b : i == 2 ? c : d;
 }
 

@@ -225,6 +225,7 @@ struct SseSinkT {  // squared residual against the projected trace in LDS, summe
     A sse;
     __device__ __forceinline__ RT begin(int k, RT u) const { return r[k] - u; }
     __device__ __forceinline__ void end(int, RT e) { sse = fmr((A)e, (A)e, sse); }
+    __device__ __forceinline__ void block_end() const {}
 };
 using SseSink = SseSinkT<R>;
 
@@ -232,6 +233,7 @@ struct TrajSink {  // theta_k to global memory
     float* out;
     __device__ __forceinline__ R begin(int, R u) const { return -u; }
     __device__ __forceinline__ void end(int k, R e) { out[k] = (float)-e; }
+    __device__ __forceinline__ void block_end() const {}
 };
 
 __device__ __forceinline__ uint64_t cost_key(double sse64, uint32_t idx)
@@ -748,6 +750,7 @@ struct ThetaSink {  // theta_k to LDS
     double* th;
     __device__ __forceinline__ R begin(int, R u) const { return -u; }
     __device__ __forceinline__ void end(int k, R e) { th[k] = -(double)e; }
+    __device__ __forceinline__ void block_end() const {}
 };
 
 __global__ __launch_bounds__(64) void report_kernel(int S, const SacDev* __restrict__ sacs, const float* __restrict__ pos,

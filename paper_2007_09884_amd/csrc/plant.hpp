@@ -25,15 +25,17 @@ namespace opmm {
 
 constexpr int P = 18;
 
-// OPMM_KEEP(x): x is computed here.  Without it the compiler sinks what only the post piece reads (its
+// keep(x): x is computed here.  Without it the compiler sinks what only the post piece reads (its
 // coupling columns and rows) behind the pulse loop and keeps their operands live until then (with
 // the doublings on matrices: 166 registers instead of 128 in the FP32 pass, 95 spilled instead of none
 // in the FP64 kernels, an FP64 round of 256 x 65536 candidates 2.32 ms instead of 1.42).
+template <class T>
+__device__ __forceinline__ void keep(T& x)
+{
 #ifdef __HIP_DEVICE_COMPILE__
-#define OPMM_KEEP(x) asm volatile("" : "+v"(x))
-#else
-#define OPMM_KEEP(x) ((void)0)
+    asm volatile("" : "+v"(x));
 #endif
+}
 
 // Precision of the per-sample recurrence and of the transition matrix.
 #ifndef OPMM_REC_T
@@ -165,7 +167,7 @@ __device__ __forceinline__ void draw_candidate(uint64_t seed, uint32_t round, ui
         const uint64_t z = splitmix64(seed, stream_counter(round, idx, k));
         uint32_t ua = (uint32_t)(z >> 40);
         // seen as a shifted 64-bit value, ua would be converted to float as one (five more instructions a draw)
-        OPMM_KEEP(ua);
+        keep(ua);
         const uint32_t ub = (uint32_t)(z >> 16) & 0xFFFFFFu;
         p[2 * k] = box_draw(ua, b.c[2 * k], b.w[2 * k], b.lo[2 * k], b.hi[2 * k]);
         p[2 * k + 1] = box_draw(ub, b.c[2 * k + 1], b.w[2 * k + 1], b.lo[2 * k + 1], b.hi[2 * k + 1]);
@@ -209,7 +211,6 @@ struct PlantT {
     RT amp;                     // theta at the post equilibrium (= amplitude)
     RT sh[6];                   // pulse equilibrium minus post equilibrium
     RT d0[6];                   // resting state minus pulse equilibrium
-    float pw;                  // PW (ms)
     double pwd;                // PW in sample periods
 };
 using Plant = PlantT<R>;
@@ -237,6 +238,9 @@ __device__ __forceinline__ float rcp64(float x)
 // types, FP64 for the dual numbers of the sensitivity pass.
 template <class S> struct LitT { using type = double; };
 template <> struct LitT<float> { using type = float; };
+// 1 / k in that type, rounded once
+template <class S>
+__device__ constexpr typename LitT<S>::type inverse(int k) { return typename LitT<S>::type(1) / (typename LitT<S>::type)k; }
 
 // Continuous-time coefficients (per ms) and the statics of candidate p for a
 // saccade of amplitude amp (deg): the matrix entries of the mechanical block,
@@ -302,9 +306,24 @@ __device__ __forceinline__ void plant_scalars(const S p[P], S amp, PlantScalars<
     o.sh[4] = ns_a - fa2; o.sh[5] = ns_n - fn2;
 }
 
-// Coefficients and equilibria of candidate p for a saccade of amplitude amp
-// (deg), sample period dt (ms), in units of the base step dt / 2^taylor_sq
-// (omega included: rest and equilibria have none, so no state is rescaled).  The scalar part is formed in ST
+// Coefficients and equilibria c (per ms) in units of the base step h = dt / 2^taylor_sq of discretisation D
+// (omega included: rest and equilibria have none, so no state is rescaled).
+template <class D, class RT, class ST>
+__device__ __forceinline__ void plant_scale(const PlantScalars<ST>& c, RT amp, RT dt, PlantT<RT>& pl)
+{
+    const RT h = dt * (1.0f / (float)(1 << D::taylor_sq));
+    const RT hh = h * h;
+    pl.a10 = (RT)c.a10 * hh; pl.a11 = (RT)c.a11 * h; pl.a12 = (RT)c.a12 * hh; pl.a13 = (RT)c.a13 * hh;
+    pl.a20 = (RT)c.a20 * h; pl.a22 = (RT)c.a22 * h; pl.g2 = (RT)c.g2 * h;
+    pl.a30 = (RT)c.a30 * h; pl.a33 = (RT)c.a33 * h; pl.g3 = (RT)c.g3 * h;
+    pl.q[0] = (RT)c.q1a * h; pl.q[1] = (RT)c.q1n * h; pl.q[2] = (RT)c.q2a * h; pl.q[3] = (RT)c.q2n * h;
+    pl.th1 = (RT)c.th1;
+    pl.amp = amp;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) { pl.d0[i] = (RT)c.d0[i]; pl.sh[i] = (RT)c.sh[i]; }
+}
+
+// Candidate p for a saccade of amplitude amp (deg), sample period dt (ms).  The scalar part is formed in ST
 // and rounded once to RT.  FP32 chains of reciprocals shift the equilibria by
 // a few ulps of ~10 deg, i.e. ~1e-6 deg on every sample: below the FP32
 // recurrence's own error, and a bias the FP64 recurrence does not take.
@@ -316,16 +335,7 @@ __device__ __forceinline__ void plant_setup(const float p[P], float amp, float d
     for (int j = 0; j < P; ++j) pd[j] = p[j];
     PlantScalars<ST> c;
     plant_scalars(pd, (ST)amp, c);
-    const RT h = (RT)dt * (RT(1) / RT(1 << Prec<RT>::taylor_sq));
-    pl.a10 = (RT)c.a10 * (h * h); pl.a11 = (RT)c.a11 * h; pl.a12 = (RT)c.a12 * (h * h); pl.a13 = (RT)c.a13 * (h * h);
-    pl.a20 = (RT)c.a20 * h; pl.a22 = (RT)c.a22 * h; pl.g2 = (RT)c.g2 * h;
-    pl.a30 = (RT)c.a30 * h; pl.a33 = (RT)c.a33 * h; pl.g3 = (RT)c.g3 * h;
-    pl.q[0] = (RT)c.q1a * h; pl.q[1] = (RT)c.q1n * h; pl.q[2] = (RT)c.q2a * h; pl.q[3] = (RT)c.q2n * h;
-    pl.th1 = (RT)c.th1;
-    pl.amp = amp;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) { pl.d0[i] = (RT)c.d0[i]; pl.sh[i] = (RT)c.sh[i]; }
-    pl.pw = p[17];
+    plant_scale<Prec<RT>>(c, (RT)amp, (RT)dt, pl);
     pl.pwd = (double)p[17] * rcp64((double)dt);
 }
 
@@ -375,7 +385,7 @@ __device__ __forceinline__ void poly_exp(const PlantT<RT>& pl, const PolyBasis<R
     a[0] = RT(0);
     double r = 1.0;
 #pragma unroll
-    for (int k = 1; k <= M; ++k) { r /= k; a[k] = (RT)r; }
+    for (int k = 1; k <= M; ++k) { r /= k; a[k] = (RT)(typename LitT<RT>::type)r; }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         RT f = a[M];
@@ -529,7 +539,7 @@ __device__ __forceinline__ void poly_apply(const PlantT<RT>& pl, const PolyBasis
         const RT r3 = fmr(pl.a30, w0, fmr(pl.a33, w3, fmr(gn, nn[j], a[j] * d[3])));
         w0 = r0; w1 = r1; w2 = r2; w3 = r3;
     }
-    d[0] += w0; d[1] += w1; d[2] += w2; d[3] += w3;
+    d[0] = d[0] + w0; d[1] = d[1] + w1; d[2] = d[2] + w2; d[3] = d[3] + w3;
     d[4] = fmr(p.f[0], d[4], d[4]);
     d[5] = fmr(p.f[1], d[5], d[5]);
 }
@@ -558,18 +568,18 @@ __device__ __forceinline__ void step(const PlantT<RT>& pl, RT d[6])
     for (int i = 0; i < 4; ++i) d[i] = n[i];
 }
 
-// v <- exp(A t) v (t in base steps) by a Taylor polynomial of degree Prec::expmv_m in Horner form, in
+// v <- exp(A t) v (t in base steps) by a Taylor polynomial of degree D::expmv_m in Horner form, in
 // the pulse (PIECE 0) or post (1) piece; t is at most one sample.
-template <int PIECE, class RT>
+template <class D, int PIECE, class RT>
 __device__ __forceinline__ void expmv(const PlantT<RT>& pl, RT t, RT v[6])
 {
     RT w[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) w[i] = v[i];
 #pragma unroll
-    for (int k = Prec<RT>::expmv_m; k >= 1; --k) {
-        RT s = t * (RT(1) / RT(k));
-        asm volatile("" : "+v"(s));
+    for (int k = D::expmv_m; k >= 1; --k) {
+        RT s = t * inverse<RT>(k);
+        keep(s);
         RT aw[6];
         aw[0] = w[1];
         aw[1] = fmr(pl.a13, w[3], fmr(pl.a12, w[2], fmr(pl.a11, w[1], pl.a10 * w[0])));
@@ -586,14 +596,14 @@ __device__ __forceinline__ void expmv(const PlantT<RT>& pl, RT t, RT v[6])
 
 // The sample that contains the pulse end: pulse dynamics for frac of it, switch to the post piece's
 // coordinates, post dynamics for the rest.
-template <class RT>
+template <class D, class RT>
 __device__ __forceinline__ void split_step(const PlantT<RT>& pl, RT frac, RT d[6])
 {
-    constexpr RT steps = RT(1 << Prec<RT>::taylor_sq);  // base steps per sample
-    expmv<0>(pl, frac * steps, d);
+    constexpr float steps = (float)(1 << D::taylor_sq);  // base steps per sample
+    expmv<D, 0>(pl, frac * steps, d);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
-    expmv<1>(pl, (RT(1) - frac) * steps, d);
+    for (int i = 0; i < 6; ++i) d[i] = d[i] + pl.sh[i];
+    expmv<D, 1>(pl, (RT(1) - frac) * steps, d);
 }
 
 // wave-wide min / max of an int (64 lanes)
@@ -658,7 +668,7 @@ __device__ __forceinline__ void block_step(const PlantT<RT>& pl, const ThetaRows
 }
 
 // Run the trajectory theta_k, k = 0..T-1: for each sample, t = sink.begin(k, u) and sink.end(k, t - v)
-// with theta_k = u + v.  pl's transition (m, x, e) is set to that of a block.
+// with theta_k = u + v; sink.block_end() after each whole block (at most 7 samples lie outside blocks).  pl's transition (m, x, e) is set to that of a block.
 //
 // Bound by VALU issue.  A block of four samples costs one step of the four-sample transition (26
 // multiply-adds) and three rows (6 each) instead of four one-sample steps: 53 operations per block with a
@@ -670,8 +680,8 @@ __device__ __forceinline__ void block_step(const PlantT<RT>& pl, const ThetaRows
 // The lane's blocks end at its own pulse-end sample: the first k0 mod 4 samples take their rows and a
 // jump, so a candidate's arithmetic depends on the candidate alone; lanes of a wave whose pulse ends
 // differ by a block mask a block each.
-template <class RT, class Sink>
-__device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, int k0, RT frac, Sink& sink)
+template <class D, class RT, class Sink>
+__device__ __forceinline__ void run_blocks_as(PlantT<RT>& pl, int T, int k0, RT frac, Sink& sink)
 {
     RT d[6];
 #pragma unroll
@@ -679,16 +689,16 @@ __device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, int k0, RT fra
     RT theq = pl.th1;
     if (k0 < 0) {  // PW <= 0: no pulse, the step acts from t = 0
 #pragma unroll
-        for (int i = 0; i < 6; ++i) d[i] += pl.sh[i];
+        for (int i = 0; i < 6; ++i) d[i] = d[i] + pl.sh[i];
         theq = pl.amp;
     }
     ThetaRows<RT> rw;
     PolyBasis<RT> pb;
     Poly<RT> f1, f2;
     poly_basis(pl, pb);
-    poly_exp<Prec<RT>::taylor_m>(pl, pb, f1);
+    poly_exp<D::taylor_m>(pl, pb, f1);
 #pragma unroll
-    for (int q = 0; q < Prec<RT>::taylor_sq; ++q) poly_twice(pl, pb, f1, f1);
+    for (int q = 0; q < D::taylor_sq; ++q) poly_twice(pl, pb, f1, f1);
     poly_theta_row(pl, pb, f1, rw.m[0], rw.x[0]);
     poly_twice(pl, pb, f1, f2);
     poly_theta_row(pl, pb, f2, rw.m[1], rw.x[1]);
@@ -713,21 +723,27 @@ __device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, int k0, RT fra
 #pragma unroll
     for (int c = 2; c < 4; ++c) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) OPMM_KEEP(pl.x[i][c]);
+        for (int i = 0; i < 4; ++i) keep(pl.x[i][c]);
 #pragma unroll
-        for (int j = 0; j < BLOCK - 1; ++j) OPMM_KEEP(rw.x[j][c]);
-        OPMM_KEEP(pl.e[c]);
+        for (int j = 0; j < BLOCK - 1; ++j) keep(rw.x[j][c]);
+        keep(pl.e[c]);
     }
 #pragma unroll 1
-    for (; k < np; k += BLOCK) block_step<0>(pl, rw, k, theq, d, sink);
+    for (; k < np; k += BLOCK) {
+        block_step<0>(pl, rw, k, theq, d, sink);
+        sink.block_end();
+    }
     if (k0 >= 0 && k0 < T) {
         sink.end(k, sink.begin(k, d[0] + theq));
-        split_step(pl, frac, d);
+        split_step<D>(pl, frac, d);
         theq = pl.amp;
         ++k;
     }
 #pragma unroll 1
-    for (; k + BLOCK <= T; k += BLOCK) block_step<1>(pl, rw, k, theq, d, sink);
+    for (; k + BLOCK <= T; k += BLOCK) {
+        block_step<1>(pl, rw, k, theq, d, sink);
+        sink.block_end();
+    }
     // the last samples need no further state: their rows alone
     if (k < T) {
         const RT u = d[0] + theq;
@@ -736,6 +752,13 @@ __device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, int k0, RT fra
         for (int j = 1; j < BLOCK - 1; ++j)
             if (k + j < T) row_sample<1>(rw, j, k + j, u, d, sink);
     }
+}
+
+// run_blocks_as in the search's discretisation.
+template <class RT, class Sink>
+__device__ __forceinline__ void run_blocks(PlantT<RT>& pl, int T, int k0, RT frac, Sink& sink)
+{
+    run_blocks_as<Prec<RT>>(pl, T, k0, frac, sink);
 }
 
 }  // namespace opmm

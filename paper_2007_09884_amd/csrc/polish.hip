@@ -6,9 +6,9 @@
 // pulse-step control (Section 2.1), so theta_k is a smooth function of the OPC
 // p (PW included: it moves the switching instant inside its sample).  The
 // derivative d theta_k / d p_j is computed in forward mode: the plant's scalar
-// physics (the same template as the search path), the one-sample transition
-// of each piece, the exact split of the pulse-end sample and the recurrence
-// all run on dual numbers (value, derivative) seeded with the unit direction
+// physics, the transitions as polynomials, the exact split of the pulse-end
+// sample and the block recurrence (all the search path's templates)
+// run on dual numbers (value, derivative) seeded with the unit direction
 // of parameter j.  One lane per parameter, one wave per saccade.  The
 // sensitivity entry point's discretisation (Taylor degree 12 on dt/4 and two
 // squarings; degree 20 for the split) truncates below 1e-11 relative even for
@@ -73,6 +73,12 @@ __device__ __forceinline__ Dual rcp64(Dual a)
     const double r = rcp64(a.v);
     return Dual(r, -a.d * r * r);
 }
+__device__ __forceinline__ Dual operator*(Dual a, float b) { return a * (double)b; }
+__device__ __forceinline__ void keep(Dual& x)
+{
+    keep(x.v);
+    keep(x.d);
+}
 __device__ __forceinline__ double val(double a) { return a; }
 __device__ __forceinline__ double val(Dual a) { return a.v; }
 
@@ -93,151 +99,26 @@ constexpr int group_lanes(int pg) { return pg == 1 ? 64 : pg == 2 ? 32 : 21; }
 static_assert(group_lanes(3) >= P && group_lanes(3) >= NLAM + 1 && 3 * group_lanes(3) <= 64, "lane groups");
 // traces up to this length may share a wave (three staged traces leave room for four waves per CU)
 constexpr int GROUPED_MAX_T = 512;
-// Discretisations of the plant: Taylor degree M and squarings SQ of the
-// one-sample transition (on dt / 2^SQ), Taylor degree EXM of the split
+// Discretisations of the plant: Taylor degree taylor_m on dt / 2^taylor_sq and
+// taylor_sq doublings up to the sample, Taylor degree expmv_m of the split
 // sample's exponentials.  Exact: truncation below 1e-11 relative for the
 // fastest mechanical mode of a +/-25% box (~2.6 per ms).  Fast: the search
 // path's (~1e-8 deg on trajectories), enough for a Gauss-Newton model.
-struct DiscExact { static constexpr int M = 12, SQ = 2, EXM = 20; };
-struct DiscFast { static constexpr int M = 6, SQ = 2, EXM = 11; };
+struct DiscExact { static constexpr int taylor_m = 12, taylor_sq = 2, expmv_m = 20; };
+using DiscFast = Prec<double>;
 // damping factors of the 8 trial lanes, relative to the current lambda
 __constant__ double LAM_FAC[NLAM] = {1e-4, 1e-3, 1e-2, 1e-1, 1.0, 1e1, 1e2, 1e3};
 
-// D-form transition of one piece: mechanical block, coupling to (F_ag, F_ant),
-// active-state factors minus one.
-template <class S>
-struct Piece {
-    S m[4][4], x[4][2], e[2];
-};
-
-// rows of Mc * V for the mechanical block Mc (theta' = omega is row 0)
-template <class S>
-__device__ __forceinline__ void mech_rows(const PlantScalars<S>& c, const S v[4], S o[4])
-{
-    o[0] = v[1];
-    o[1] = fmr(c.a13, v[3], fmr(c.a12, v[2], fmr(c.a11, v[1], c.a10 * v[0])));
-    o[2] = fmr(c.a22, v[2], c.a20 * v[0]);
-    o[3] = fmr(c.a33, v[3], c.a30 * v[0]);
-}
-
-// D = exp(dt A) - I of the piece with active-state rates (qa, qn): Horner
-// evaluation of the degree-M Taylor polynomial on h = dt / 2^SQ in block form
-// A = [[Mc, G], [0, diag(q)]], then SQ squarings D_2h = D_h^2 + 2 D_h.
-template <int M, int SQ, class S>
-__device__ void lti_dform(const PlantScalars<S>& c, S qa, S qn, double dt, Piece<S>& o)
-{
-    const double h = dt / (double)(1 << SQ);
-    const S q[2] = {qa, qn};
-    S qm[4][4], qx[4][2], qd[2];
-    for (int i = 0; i < 4; ++i) {
-        for (int j = 0; j < 4; ++j) qm[i][j] = S(i == j ? 1.0 : 0.0);
-        qx[i][0] = S(0.0); qx[i][1] = S(0.0);
-    }
-    qd[0] = S(1.0); qd[1] = S(1.0);
-    for (int k = M; k >= 1; --k) {
-        // Q <- I + (h/k) A Q  (k >= 2);  D = h A Q  (k == 1)
-        const double s = h / (double)k;
-        S am[4][4], ax[4][2], ad[2];
-        for (int col = 0; col < 4; ++col) {
-            S v[4] = {qm[0][col], qm[1][col], qm[2][col], qm[3][col]}, r[4];
-            mech_rows(c, v, r);
-            for (int i = 0; i < 4; ++i) am[i][col] = r[i];
-        }
-        for (int col = 0; col < 2; ++col) {
-            S v[4] = {qx[0][col], qx[1][col], qx[2][col], qx[3][col]}, r[4];
-            mech_rows(c, v, r);
-            for (int i = 0; i < 4; ++i) ax[i][col] = r[i];
-        }
-        ax[2][0] = fmr(c.g2, qd[0], ax[2][0]);
-        ax[3][1] = fmr(c.g3, qd[1], ax[3][1]);
-        ad[0] = q[0] * qd[0];
-        ad[1] = q[1] * qd[1];
-        const double one = k >= 2 ? 1.0 : 0.0;
-        for (int i = 0; i < 4; ++i) {
-            for (int j = 0; j < 4; ++j) qm[i][j] = fmr(S(s), am[i][j], S(i == j ? one : 0.0));
-            qx[i][0] = S(s) * ax[i][0];
-            qx[i][1] = S(s) * ax[i][1];
-        }
-        qd[0] = fmr(S(s), ad[0], S(one));
-        qd[1] = fmr(S(s), ad[1], S(one));
-    }
-    // squarings in D-form
-    for (int q = 0; q < SQ; ++q) {
-        S nm[4][4], nx[4][2];
-        for (int i = 0; i < 4; ++i) {
-            for (int j = 0; j < 4; ++j) {
-                S a = qm[i][j] + qm[i][j];
-                for (int k = 0; k < 4; ++k) a = fmr(qm[i][k], qm[k][j], a);
-                nm[i][j] = a;
-            }
-            for (int j = 0; j < 2; ++j) {
-                S b = qx[i][j] * (qd[j] + S(2.0));
-                for (int k = 0; k < 4; ++k) b = fmr(qm[i][k], qx[k][j], b);
-                nx[i][j] = b;
-            }
-        }
-        for (int i = 0; i < 4; ++i) {
-            for (int j = 0; j < 4; ++j) qm[i][j] = nm[i][j];
-            qx[i][0] = nx[i][0];
-            qx[i][1] = nx[i][1];
-        }
-        qd[0] = qd[0] * (qd[0] + S(2.0));
-        qd[1] = qd[1] * (qd[1] + S(2.0));
-    }
-    for (int i = 0; i < 4; ++i) {
-        for (int j = 0; j < 4; ++j) o.m[i][j] = qm[i][j];
-        o.x[i][0] = qx[i][0];
-        o.x[i][1] = qx[i][1];
-    }
-    o.e[0] = qd[0];
-    o.e[1] = qd[1];
-}
-
-template <class S>
-__device__ __forceinline__ void piece_step(const Piece<S>& pc, S d[6])
-{
-    S n[4];
-    for (int i = 0; i < 4; ++i) {
-        S a = d[i];
-        for (int j = 0; j < 4; ++j) a = fmr(pc.m[i][j], d[j], a);
-        a = fmr(pc.x[i][0], d[4], a);
-        n[i] = fmr(pc.x[i][1], d[5], a);
-    }
-    d[4] = fmr(pc.e[0], d[4], d[4]);
-    d[5] = fmr(pc.e[1], d[5], d[5]);
-    for (int i = 0; i < 4; ++i) d[i] = n[i];
-}
-
-// v <- exp(t A) v by the Taylor polynomial of degree EXM (|t| <= dt)
-template <int EXM, class S>
-__device__ void expmv_t(const PlantScalars<S>& c, S qa, S qn, S t, S v[6])
-{
-    S w[6];
-    for (int i = 0; i < 6; ++i) w[i] = v[i];
-    for (int k = EXM; k >= 1; --k) {
-        const S s = t * (1.0 / (double)k);
-        S mv[4], aw[6];
-        S w4[4] = {w[0], w[1], w[2], w[3]};
-        mech_rows(c, w4, mv);
-        aw[0] = mv[0];
-        aw[1] = mv[1];
-        aw[2] = fmr(c.g2, w[4], mv[2]);
-        aw[3] = fmr(c.g3, w[5], mv[3]);
-        aw[4] = qa * w[4];
-        aw[5] = qn * w[5];
-        for (int i = 0; i < 6; ++i) w[i] = fmr(s, aw[i], v[i]);
-    }
-    for (int i = 0; i < 6; ++i) v[i] = w[i];
-}
-
-// theta_k, k = 0..T-1, of OPC p (deg), handed to sink(k, theta_k), with the
+// theta_k, k = 0..T-1, of OPC p (deg), through the sink (begin and end, see run_blocks_as), with the
 // discretisation Disc.  Control flow depends on value parts only, so every
 // lane of a Dual pass at one point takes the same path.
 template <class Disc, class S, class Sink>
-__device__ void simulate_s(const S p[P], double amp, double dt, int T, Sink& sink)
+__device__ __forceinline__ void simulate_s(const S p[P], double amp, double dt, int T, Sink& sink)
 {
     PlantScalars<S> c;
     plant_scalars(p, S(amp), c);
+    PlantT<S> pl;
+    plant_scale<Disc>(c, S(amp), S(dt), pl);
     const S pwd = p[17] * rcp64(dt);
     const double fl = floor(val(pwd));
     int k0;
@@ -245,35 +126,7 @@ __device__ void simulate_s(const S p[P], double amp, double dt, int T, Sink& sin
     if (!(val(pwd) > 0.0)) k0 = -1;
     else if (fl >= (double)T) k0 = T;
     else { k0 = (int)fl; frac = pwd - S(fl); }
-    S d[6];
-    for (int i = 0; i < 6; ++i) d[i] = c.d0[i];
-    S theq = c.th1;
-    // one piece's transition at a time (the post piece is formed when the pulse ends), which
-    // keeps the dual pass within the register file
-    Piece<S> pc;
-    int k = 0;
-    if (k0 < 0) {
-        for (int i = 0; i < 6; ++i) d[i] = d[i] + c.sh[i];
-        theq = S(amp);
-    } else {
-        lti_dform<Disc::M, Disc::SQ>(c, c.q1a, c.q1n, dt, pc);
-        for (; k < k0 && k < T; ++k) {
-            sink(k, d[0] + theq);
-            piece_step(pc, d);
-        }
-        if (k0 >= T) return;
-        sink(k, d[0] + theq);
-        expmv_t<Disc::EXM>(c, c.q1a, c.q1n, frac * dt, d);
-        for (int i = 0; i < 6; ++i) d[i] = d[i] + c.sh[i];
-        expmv_t<Disc::EXM>(c, c.q2a, c.q2n, (S(1.0) - frac) * dt, d);
-        theq = S(amp);
-        ++k;
-    }
-    lti_dform<Disc::M, Disc::SQ>(c, c.q2a, c.q2n, dt, pc);
-    for (; k < T; ++k) {
-        sink(k, d[0] + theq);
-        piece_step(pc, d);
-    }
+    run_blocks_as<Disc>(pl, T, k0, frac, sink);
 }
 
 // ---- sinks ----------------------------------------------------------------
@@ -282,11 +135,14 @@ struct JacSink {  // theta and d theta / d p_lane
     double* theta;
     double* jac;  // [T][P] row-major
     int lane;
-    __device__ void operator()(int k, Dual th)
+    __device__ __forceinline__ Dual begin(int, Dual u) const { return -u; }
+    __device__ __forceinline__ void end(int k, Dual e)
     {
+        const Dual th = -e;
         if (lane == 0) theta[k] = th.v;
         if (lane < P) jac[(int64_t)k * P + lane] = th.d;
     }
+    __device__ __forceinline__ void block_end() const {}
 };
 
 struct Residual {
@@ -305,10 +161,11 @@ struct CostSink {  // objective value only (trial points, reports)
     Residual res;
     int objective;
     double sq, ab;
-    __device__ void operator()(int k, double th)
+    __device__ __forceinline__ double begin(int, double u) const { return -u; }
+    __device__ __forceinline__ void end(int k, double e)
     {
         double ex, ey;
-        res(k, th, ex, ey);
+        res(k, -e, ex, ey);
         sq = __fma_rn(ex, ex, sq);
         ab += fabs(ex);
         if (res.C == 2) {
@@ -316,6 +173,7 @@ struct CostSink {  // objective value only (trial points, reports)
             ab += fabs(ey);
         }
     }
+    __device__ __forceinline__ void block_end() const {}
     __device__ double f() const { return objective == OPMM_OBJ_MAE ? ab : sq; }
 };
 
@@ -328,68 +186,101 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The lower triangle's entries in row order, (row << 8) | column.
+struct Triangle {
+    uint16_t e[PTRI];
+    constexpr Triangle() : e()
+    {
+        int n = 0;
+        for (int i = 0; i < P; ++i)
+            for (int j = 0; j <= i; ++j) e[n++] = (uint16_t)((i << 8) | j);
+    }
+};
+__constant__ Triangle TRI;
+
 // Normal equations of the linearised problem.  Lane r of the saccade's group carries column r of
-// J (the dual part) and accumulates g_r; the rows of J are staged in LDS NCH samples at a time,
-// and each lane of the group then accumulates up to NENT entries (i >= j) of the lower triangle
-// of J^T W J, h_ij += (w_k J_ki) J_kj in sample order.  Every lane of the group calls it (the
-// group's control flow is uniform).
+// J (the dual part).  A sample only stages its row of J and its theta in LDS; every NCH - 8 samples or so the
+// staged ones are worked off: lanes take a sample each for its residual and weights, then lane r accumulates
+// g_r and up to NENT entries (i >= j) of the lower triangle of J^T W J, h_ij += (w_k J_ki) J_kj in sample
+// order.  Every lane of the group calls it (the group's control flow is uniform).
+// (With the residual on every lane of every sample and the entries' indices looked up in each step a
+// sample took 830 cycles of a lone wave, most of the Jacobian pass; now 300.)
 template <int GL>
 struct NormalSink {
     static constexpr int NENT = (PTRI + GL - 1) / GL;  // lower-triangle entries accumulated per lane
     Residual res;
     int objective;
     double* jst;  // LDS [NCH][P]: staged rows of J
-    double* ast;  // LDS [NCH]: per-sample weight of the normal matrix
+    double* ast;  // LDS [NCH]: staged theta, then the sample's weight in the normal matrix
+    double* bst;  // LDS [NCH]: its weighted residual
     int r;        // lane within the group
     int nk;       // samples staged
+    int k0;       // index of the first
     double g;
-    int eij[NENT];  // this lane's entries, (row << 8) | column; -1: none
+    int eij[NENT];  // this lane's entries; -1: none
     double h[NENT];
     __device__ void init(int nf)
     {
         nk = 0;
+        k0 = 0;
         g = 0.0;
 #pragma unroll
         for (int q = 0; q < NENT; ++q) {
             const int e = r + GL * q;
-            int i = 0;
-            while ((i + 1) * (i + 2) / 2 <= e) ++i;
-            const bool use = e < PTRI && i < nf;
-            eij[q] = use ? (i << 8) | (e - i * (i + 1) / 2) : -1;
+            eij[q] = (e < PTRI && (TRI.e[e < PTRI ? e : 0] >> 8) < nf) ? TRI.e[e < PTRI ? e : 0] : -1;
             h[q] = 0.0;
         }
     }
-    __device__ void operator()(int k, Dual th)
+    __device__ __forceinline__ Dual begin(int, Dual u) const { return -u; }
+    __device__ __forceinline__ void end(int, Dual e)
     {
-        double ex, ey;
-        res(k, th.v, ex, ey);
-        double wx = 1.0, wy = 1.0;
-        if (objective == OPMM_OBJ_MAE) {
-            wx = 1.0 / fmax(fabs(ex), IRLS_EPS);
-            wy = 1.0 / fmax(fabs(ey), IRLS_EPS);
-        }
-        const double cp = res.cphi, sp = res.sphi;
-        double a = wx * cp * cp, b = wx * cp * ex;
-        if (res.C == 2) {
-            a = __fma_rn(wy * sp, sp, a);
-            b = __fma_rn(wy * sp, ey, b);
-        }
-        g = __fma_rn(th.d, b, g);
-        if (r < P) jst[nk * P + r] = th.d;
-        if (r == 0) ast[nk] = a;
-        if (++nk == NCH) flush();
+        if (r < P) jst[nk * P + r] = -e.d;
+        if (r == 0) ast[nk] = -e.v;
+        ++nk;
     }
-    __device__ void flush()
+    __device__ __forceinline__ void block_end()
+    {
+        if (nk > NCH - 8) flush();
+    }
+    __device__ __forceinline__ void flush()
     {
         wave_sync();
+        for (int kk = r; kk < nk; kk += GL) {
+            double ex, ey;
+            res(k0 + kk, ast[kk], ex, ey);
+            double wx = 1.0, wy = 1.0;
+            if (objective == OPMM_OBJ_MAE) {
+                wx = 1.0 / fmax(fabs(ex), IRLS_EPS);
+                wy = 1.0 / fmax(fabs(ey), IRLS_EPS);
+            }
+            const double cp = res.cphi, sp = res.sphi;
+            double a = wx * cp * cp, b = wx * cp * ex;
+            if (res.C == 2) {
+                a = __fma_rn(wy * sp, sp, a);
+                b = __fma_rn(wy * sp, ey, b);
+            }
+            ast[kk] = a;
+            bst[kk] = b;
+        }
+        wave_sync();
+        const double* pi[NENT];
+        const double* pj[NENT];
+#pragma unroll
+        for (int q = 0; q < NENT; ++q) {
+            const int e = max(eij[q], 0);  // entries past the triangle work on (0, 0) and go nowhere
+            pi[q] = jst + (e >> 8);
+            pj[q] = jst + (e & 255);
+        }
+        const double* pg = jst + min(r, P - 1);
+#pragma unroll 4
         for (int kk = 0; kk < nk; ++kk) {
             const double ak = ast[kk];
+            g = __fma_rn(pg[kk * P], bst[kk], g);
 #pragma unroll
-            for (int q = 0; q < NENT; ++q)
-                if (eij[q] >= 0)
-                    h[q] = __fma_rn(ak * jst[kk * P + (eij[q] >> 8)], jst[kk * P + (eij[q] & 255)], h[q]);
+            for (int q = 0; q < NENT; ++q) h[q] = __fma_rn(ak * pi[q][kk * P], pj[q][kk * P], h[q]);
         }
         wave_sync();
+        k0 += nk;
         nk = 0;
     }
 };
@@ -420,9 +311,10 @@ struct PolishSlot {
     double ft[NLAM];
     double x[P], nom[P], lo[P], hi[P];
     double jst[NCH][P];
-    double ast[NCH];
+    double ast[NCH], bst[NCH];
     int opc_of[P];   // free parameter -> its (first) OPC index
     int tied[P];     // free parameter -> second OPC index it moves, or -1
+    int free_of[P];  // OPC index -> the free parameter that moves it, or -1
     int nf;
     double fcur, lam;
     int ok[NLAM];
@@ -479,6 +371,10 @@ __device__ __forceinline__ bool damped_solve(const PolishSlot& sl, double lam, u
     return true;
 }
 
+// Bound by the latency of one wave per SIMD (512 registers: dual numbers).  Cycles per iteration at T = 61, one
+// saccade per wave, with sample-by-sample matrices and the residuals on every lane -> now: Jacobian pass
+// ~105k -> 52k, damped solves 37k -> 28k (their Cholesky factorisations; the held parameters and trial points
+// went to a lane each), trial costs ~40k -> 21k.  1000 saccades x 4 iterations: 443 -> 288 us.
 // PG saccades per wave: lane group g = lane / GL polishes saccade order[blockIdx.x * PG + g]
 // (order: the batch sorted by T, so a wave's saccades run loops of similar length; NULL: batch
 // order).  A group's arithmetic is that of a wave of its own, so results do not depend on the
@@ -535,9 +431,15 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
     if (member && r == 0) {
         int n = 0;
         for (int i = 0; i < P && live; ++i) {
-            if (model == 9 && (fixed_in_model9(i) || i == 1 || i == 3)) continue;
+            if (model == 9 && (i == 1 || i == 3)) {
+                sl.free_of[i] = n - 1;  // the agonist's, just taken
+                continue;
+            }
+            sl.free_of[i] = -1;
+            if (model == 9 && fixed_in_model9(i)) continue;
             sl.opc_of[n] = i;
             sl.tied[n] = (model == 9 && (i == 0 || i == 2)) ? i + 1 : -1;
+            sl.free_of[i] = n;
             ++n;
         }
         sl.nf = n;
@@ -568,7 +470,7 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
             const int i1 = r < nf ? sl.tied[r] : -1;
             for (int i = 0; i < P; ++i)
                 p[i] = Dual(opc_value(sl, sl.x, i), (i == i0 || i == i1) ? sl.nom[i] : 0.0);
-            NormalSink<GL> ns{res, objective, &sl.jst[0][0], sl.ast, r};
+            NormalSink<GL> ns{res, objective, &sl.jst[0][0], sl.ast, sl.bst, r};
             ns.init(nf);
             simulate_s<DiscFast>(p, (double)sd.amp, dt, T, ns);
             ns.flush();
@@ -578,32 +480,33 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
             if (r < nf) sl.g[r] = ns.g;
         }
         __syncthreads();
-        // B: damped solves, one damping value per lane
+        // B: damped solves, one damping value per lane; held parameters by a lane each
+        bool hold = true;
+        if (run && r < nf) {
+            const int i = sl.opc_of[r];
+            hold = !(sl.H[r][r] > 0.0) || (sl.x[i] <= sl.lo[i] && sl.g[r] > 0.0) ||
+                   (sl.x[i] >= sl.hi[i] && sl.g[r] < 0.0);
+        }
+        const uint32_t held = (uint32_t)(__ballot(hold) >> (g * GL)) & ((1u << P) - 1);
         if (run && r < NLAM) {
-            const double lam = sl.lam * LAM_FAC[r];
-            uint32_t held = 0;
-            for (int j = 0; j < P; ++j) {
-                bool h = true;
-                if (j < nf) {
-                    const int i = sl.opc_of[j];
-                    h = !(sl.H[j][j] > 0.0) || (sl.x[i] <= sl.lo[i] && sl.g[j] > 0.0) ||
-                        (sl.x[i] >= sl.hi[i] && sl.g[j] < 0.0);
-                }
-                held |= (uint32_t)h << j;
-            }
             double delta[P];
-            const bool ok = damped_solve(sl, lam, held, delta);
-            for (int i = 0; i < P; ++i) sl.xt[r][i] = sl.x[i];
-            if (ok) {
-                for (int j = 0; j < nf; ++j) {
-                    const int i = sl.opc_of[j];
-                    const double v = fmin(fmax(sl.x[i] + delta[j], sl.lo[i]), sl.hi[i]);
-                    sl.xt[r][i] = v;
-                    if (sl.tied[j] >= 0) sl.xt[r][sl.tied[j]] = v;
-                }
-            }
+            const bool ok = damped_solve(sl, sl.lam * LAM_FAC[r], held, delta);
             sl.ok[r] = ok;
             sl.ft[r] = INFINITY;
+#pragma unroll
+            for (int j = 0; j < P; ++j) sl.jst[r][j] = ok ? delta[j] : 0.0;
+        }
+        __syncthreads();
+        if (run) {  // trial points: the free parameters move, the tied ones with them
+            for (int e = r; e < NLAM * P; e += GL) {
+                const int m = e / P, i = e - m * P, f = sl.free_of[i];
+                double v = sl.x[i];
+                if (f >= 0 && sl.ok[m]) {
+                    const int src = sl.opc_of[f];
+                    v = fmin(fmax(sl.x[src] + sl.jst[m][f], sl.lo[src]), sl.hi[src]);
+                }
+                sl.xt[m][i] = v;
+            }
         }
         __syncthreads();
         // C: trial costs, and the cost at the current point (lane NLAM)
@@ -653,10 +556,10 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
     }
 }
 
-// Time of one wave polishing pg saccades, relative to a wave with one (measured with one wave per
-// SIMD: the groups' loops run to the longest member, and each lane accumulates more entries of
-// the normal matrix).
-constexpr double WAVE_TIME[4] = {0.0, 1.0, 1.30, 1.51};
+// Time of one wave polishing pg saccades, relative to a wave with one (288, 432 and 545 us for 1000, 2000
+// and 3000 full-estimation saccades, one wave per SIMD and four iterations: the groups' loops run to the
+// longest member, and each lane accumulates more entries of the normal matrix).
+constexpr double WAVE_TIME[4] = {0.0, 1.0, 1.50, 1.89};
 
 // Saccades per wave for n saccades (T <= max_T) on `simds` SIMDs: one wave per SIMD is resident at
 // a time, so a batch takes ceil(waves / simds) wave times.

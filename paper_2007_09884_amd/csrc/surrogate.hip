@@ -680,6 +680,7 @@ struct GenSink {
     float* out;
     __device__ __forceinline__ R begin(int, R u) const { return -u; }
     __device__ __forceinline__ void end(int k, R e) { out[k] = (float)-e; }
+    __device__ __forceinline__ void block_end() const {}
 };
 
 __global__ __launch_bounds__(64) void gen_batch_kernel(int B, uint64_t seed, const uint64_t* __restrict__ counter,
