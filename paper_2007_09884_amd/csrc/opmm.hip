@@ -2246,8 +2246,8 @@ int opmm_fit_noalloc(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opm
     OPMM_HIP(ctx, hipMemcpyAsync(B.sacs, g.recs, sizeof(SacDev) * (size_t)S, hipMemcpyHostToDevice, st));
     OPMM_HIP(ctx, hipMemcpyAsync(B.order, g.order, sizeof(int) * 2 * (size_t)S, hipMemcpyHostToDevice, st));
     OPMM_HIP(ctx, hipStreamSynchronize(st));
-    // every part is written before it is read: records and order above, projection, energies and
-    // status by the prep kernel, the box by init, counters and keys by fill kernels
+    // every part is written before it is read: records and order above, projection, energies, status, box,
+    // keys and counters by begin_kernel
     return enqueue_fit_bufs(ctx, B, pos, S, (int)tiles, params, shape, seed_opc, opc_out, rmse_out, mae_out,
                             status_out, st, true);
 }
