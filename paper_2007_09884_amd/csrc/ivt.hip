@@ -247,6 +247,9 @@ int opmm_ivt_extract(opmm_ctx* ctx, const float* gaze, int64_t N, float dt_ms, f
         (max_out > 0 && (!sacs_out || !pos_out)))
         return opmm_rt::fail(ctx, OPMM_EINVAL, "bad I-VT arguments");
     if (N < 2 || max_out == 0) return OPMM_OK;
+    // the staging below is made once and kept: on the context's device, whichever is current now
+    const hipError_t dev = hipSetDevice(opmm_rt::ctx_device(ctx));
+    if (dev != hipSuccess) return opmm_rt::hip_fail(ctx, dev, "hipSetDevice");
     hipStream_t st = (hipStream_t)stream;
     const float v_per_sample = vel_thresh_deg_s * dt_ms * 1e-3f;  // deg per sample at the threshold
     const int64_t chunks = (N + CHUNK - 1) / CHUNK;

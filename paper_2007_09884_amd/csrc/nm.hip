@@ -519,6 +519,8 @@ int opmm_fit_nm(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_sac
         return opmm_rt::fail(ctx, OPMM_EINVAL, "bad Nelder-Mead parameters");
     if (S < 0 || (S > 0 && (!pos || !sacs || !opc_out || !rmse_out))) return opmm_rt::fail(ctx, OPMM_EINVAL, "bad arguments");
     if (S == 0) return OPMM_OK;
+    const hipError_t dev = hipSetDevice(opmm_rt::ctx_device(ctx));
+    if (dev != hipSuccess) return opmm_rt::hip_fail(ctx, dev, "hipSetDevice");
     hipStream_t st = (hipStream_t)stream;
     opmm_rt::Ordered ord(opmm_rt::ctx_order(ctx), st);
     if (ord.error() != hipSuccess) return opmm_rt::hip_fail(ctx, ord.error(), "stream ordering");

@@ -648,6 +648,8 @@ int opmm_sensitivity(opmm_ctx* ctx, const opmm_saccade* sacs, int32_t S, const f
         off[i] = acc;
         acc += sacs[i].T;
     }
+    const hipError_t dev = hipSetDevice(opmm_rt::ctx_device(ctx));
+    if (dev != hipSuccess) return opmm_rt::hip_fail(ctx, dev, "hipSetDevice");
     hipStream_t st = (hipStream_t)stream;
     SacDev* d_sacs = nullptr;
     int64_t* d_off = nullptr;
@@ -682,6 +684,8 @@ int opmm_polish(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_sac
     if (S < 0 || (S > 0 && (!pos || !sacs || !opc_inout || !rmse_out)))
         return opmm_rt::fail(ctx, OPMM_EINVAL, "bad arguments");
     if (S == 0) return OPMM_OK;
+    const hipError_t dev = hipSetDevice(opmm_rt::ctx_device(ctx));
+    if (dev != hipSuccess) return opmm_rt::hip_fail(ctx, dev, "hipSetDevice");
     hipStream_t st = (hipStream_t)stream;
     opmm_rt::Ordered ord(opmm_rt::ctx_order(ctx), st);
     if (ord.error() != hipSuccess) return opmm_rt::hip_fail(ctx, ord.error(), "stream ordering");

@@ -1,0 +1,86 @@
+"""What the library's host code asks the HIP runtime for, without a GPU: calls run in a child process on a
+stand-in runtime (fake_hip.c) that logs every allocation, device selection and launch with the device
+that was current."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, os, sys
+sys.path.insert(0, %r)
+del os.environ["LD_PRELOAD"]
+import numpy as np
+from paper_2007_09884_amd import opmm
+fake = ctypes.CDLL(None)
+fake.fake_log.restype = ctypes.c_char_p
+lib, P = opmm.lib, ctypes.c_void_p(1 << 20)       # P: a device pointer nobody reads
+
+def lines():
+    return [l.split(None, 5) for l in fake.fake_log().decode().splitlines()]
+
+def records(S, T=57, n_cand=None):
+    return opmm.saccade_records(np.full(S, T) if np.isscalar(T) else T, 2, np.full(S, 10.0), np.zeros(S),
+                                np.full(S, 43.0), np.arange(S), n_cand)
+
+def ptr(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+def check(rc):
+    assert rc == 0, (rc, lib.opmm_last_error(ctx._h))
+
+def fit_nm(recs, **kw):
+    check(lib.opmm_fit_nm(ctx._h, P, 1 << 40, ptr(recs), len(recs), ctypes.byref(opmm.nm_params(**kw)), None, P, P,
+                          None, None, None, None))
+
+def polish(recs, **kw):
+    check(lib.opmm_polish(ctx._h, P, 1 << 40, ptr(recs), len(recs), ctypes.byref(opmm.polish_params(**kw)), 18, P, P,
+                          None, None, None, None))
+
+def sensitivity(recs):
+    check(lib.opmm_sensitivity(ctx._h, ptr(recs), len(recs), P, ctypes.c_float(1.0), P, P, None))
+
+def ivt(N, max_out, min_dur=6.0):
+    recs, n = np.zeros(max_out, opmm.SACCADE_DTYPE), ctypes.c_int32()
+    check(lib.opmm_ivt_extract(ctx._h, P, N, ctypes.c_float(1.0), ctypes.c_float(30.0), ctypes.c_float(min_dur),
+                               ctypes.c_float(0.0), 2048, ctypes.c_uint64(0), max_out, ptr(recs), P, 1 << 40, None,
+                               ctypes.byref(n), None))
+
+def fit(recs, **kw):
+    check(lib.opmm_fit(ctx._h, P, 1 << 40, ptr(recs), len(recs), ctypes.byref(opmm.fit_params(**kw)), None, P, P,
+                       None, None, None, None))
+
+ctx = opmm.Context(0)
+fake.fake_clear()
+""" % ROOT
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    if os.environ.get("LD_PRELOAD"):
+        pytest.skip("a preload is already set")
+    include = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I" + include,
+                    os.path.join(HERE, "fake_hip.c"), "-o", so], check=True)
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + code], cwd=ROOT, env=dict(os.environ, LD_PRELOAD=so),
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr[-3000:]
+        return json.loads(r.stdout.splitlines()[-1])
+    return run
+
+
+@pytest.mark.parametrize("call", ["ivt(100000, 4096)", "fit_nm(records(5))", "polish(records(5))",
+                                  "sensitivity(records(5))", "fit(records(5))"])
+def test_work_goes_to_the_contexts_device(fake, call):
+    """Another device is current when the call comes: what it allocates and launches is on the context's."""
+    log = fake("fake.fake_current(1)\n%s\nprint(json.dumps(lines()))" % call)
+    work = [l for l in log if l[0] in ("malloc", "async", "launch")]
+    assert any(l[0] == "launch" for l in work) and all(l[1] == "0" for l in work), work
