@@ -112,7 +112,7 @@ struct opmm_server {
     float* d_box = nullptr;   // 4 x [slots][18]
     int32_t* d_status = nullptr;
     uint64_t* d_keys = nullptr;
-    uint32_t* d_done = nullptr;  // [slots], the one array the budget does not count (4 bytes a slot)
+    uint32_t* d_done = nullptr;  // [slots]
     float* d_proj = nullptr;  // [slots][max_T]
     double* d_qorth = nullptr;
     SacDev* d_list = nullptr;  // [slots] active / admitted / finished lists
@@ -228,7 +228,7 @@ int opmm_server_create(opmm_ctx* ctx, opmm_surrogate* sg, const opmm_serve_param
         return opmm_rt::fail(ctx, OPMM_EINVAL, "rounds_per_step must be in 1..64");
     // slots admitted by memory: what one resident request costs on the device
     const size_t per_slot = sizeof(float) * (3 * (size_t)prm->max_T + 4 * P + P + P + 2) + sizeof(int32_t) * 2 +
-                            sizeof(uint64_t) + sizeof(double) + sizeof(SacDev) +
+                            sizeof(uint32_t) + sizeof(uint64_t) + sizeof(double) + sizeof(SacDev) +
                             (prm->polish_iter > 0
                                  ? kPolishBatches * (sizeof(SacDev) + sizeof(float) * (P + 2) + sizeof(int32_t))
                                  : 0);

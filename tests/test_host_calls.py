@@ -84,3 +84,20 @@ def test_work_goes_to_the_contexts_device(fake, call):
     log = fake("fake.fake_current(1)\n%s\nprint(json.dumps(lines()))" % call)
     work = [l for l in log if l[0] in ("malloc", "async", "launch")]
     assert any(l[0] == "launch" for l in work) and all(l[1] == "0" for l in work), work
+
+
+@pytest.mark.parametrize("polish_iter", [0, 4])
+def test_server_slots_fit_their_budget(fake, polish_iter):
+    """Every per-slot array of a server counts against hbm_budget_bytes."""
+    budget = 1000000
+    log = fake("""
+prm = opmm.serve_params(max_slots=1 << 20, max_T=1, hbm_budget_bytes=%d, polish_iter=%d)
+sv = ctypes.c_void_p()
+check(lib.opmm_server_create(ctx._h, None, ctypes.byref(prm), ctypes.byref(sv)))
+print(json.dumps([lib.opmm_server_slots(sv), lines()]))""" % (budget, polish_iter))
+    slots, log = log
+    sizes = [int(l[2]) for l in log if l[0] == "malloc"]
+    staged = 2 * 4 * min(slots, 4096)      # traces admitted in one step: the server's, not a slot's
+    assert staged in sizes
+    used = sum(sizes) - staged
+    assert budget - used // slots < used <= budget
