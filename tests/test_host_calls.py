@@ -101,3 +101,10 @@ print(json.dumps([lib.opmm_server_slots(sv), lines()]))""" % (budget, polish_ite
     assert staged in sizes
     used = sum(sizes) - staged
     assert budget - used // slots < used <= budget
+
+
+@pytest.mark.parametrize("N,max_out", [(100000, 4096), (200000000, 20000000)])
+def test_extraction_allocates_for_what_it_finds(fake, N, max_out):
+    """A stream without saccades costs no memory for records, however many the caller would take."""
+    log = fake("ivt(%d, %d)\nprint(json.dumps(lines()))" % (N, max_out))
+    assert sum(int(l[2]) for l in log if l[0] in ("malloc", "async", "pinned")) <= 1 << 20
