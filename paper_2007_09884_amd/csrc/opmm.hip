@@ -918,6 +918,7 @@ struct FitLaunch {
     const double* qorth;
     float tau;
     float w0;            // round-0 half-width relative to nominal
+    double sims;         // samples of a round's simulations: candidates times trace length, over the batch
     KernelTimer* timer;  // non-null: record an event pair around each search-kernel launch
 };
 
@@ -963,13 +964,16 @@ hipError_t launch_screened(const FitLaunch& L, int round, hipStream_t st)
                            L.costs, L.tmin, L.smin);
     }
     const int max_T = L.max_T > 0 && L.max_T <= OPMM_MAX_T ? L.max_T : OPMM_MAX_T;
-    // The anchor tightens the threshold by about tau / 2 and so spares FP64 simulations: on 256 x 65536
-    // candidates 0.45 us of verify time over the round's relative half-width w (10 us at 3 %, 220 us at
-    // 0.2 %), in proportion to the candidates, against the 11 us of its own launch.
-    const double w = (double)L.w0 * std::pow((double)L.shrink, round);
-    const bool anchor = (double)L.tiles_per_round * TPB * PASSES > 4.5e8 * w;
     int per = 1;
-    while (anchor && 2 * per <= ANCHOR_MAX && per * L.simds < L.S && 2 * per * (int)sizeof(R) * max_T <= (48 << 10)) per *= 2;
+    while (2 * per <= ANCHOR_MAX && per * L.simds < L.S && 2 * per * (int)sizeof(R) * max_T <= (48 << 10)) per *= 2;
+    // The anchor tightens the threshold by about tau / 2 and so spares FP64 simulations, as many as lie between
+    // the two thresholds: with the cost quadratic around the box's centre, a share that grows with tau / w^2 (w the
+    // round's relative half-width).  Verify time spared, measured per candidate and sample: 3.3e-8 us
+    // sqrt(tau) / w on 256 x 65536 candidates (11 / 14 / 39 / 84 / 141 us at w = 3.1 / 1.6 / 0.8 / 0.4 /
+    // 0.2 % for tau = 5e-5; the same at ten times tau and three times w), up to 6e-8 on a quarter of them.
+    // Its own launch adds 7 us for one wave, 12 / 16 / 25 us for 64 / 256 / 1024.
+    const double w = (double)L.w0 * std::pow((double)L.shrink, round);
+    const bool anchor = 4.5e-8 * L.sims * std::sqrt((double)L.tau) > w * (7.0 + 0.56 * std::sqrt((L.S + per - 1) / per));
     if (anchor)
         hipLaunchKernelGGL(screen_anchor_kernel, dim3((L.S + per - 1) / per), dim3(64), sizeof(R) * (size_t)max_T * per, st,
                        L.sacs, L.S, per, L.ord, round, L.dt, L.proj, L.centre, L.hw, L.lo, L.hi, L.status, L.qorth,
@@ -1059,6 +1063,7 @@ struct FitScratch {
     DevBuf sacs, proj, qorth, box, keys, status, counters, order;
     DevBuf costs, tmin, smin, vthr;  // screened rounds (see FitBufs)
     int max_T = 0;             // longest trace of the last uploaded batch
+    double sims = 0.0;         // its candidates times their trace's length (screened fits)
     // Pinned host staging of the record upload (records, then dispatch order and tile bases), kept
     // between calls: the upload is a direct DMA and no batch pays for fresh pages.
     DevBuf stage;
@@ -1338,6 +1343,9 @@ int upload_saccades(opmm_ctx* ctx, FitScratch& sc, const opmm_saccade* sacs, int
     build_records(sacs, S, prm, tile_size, h, ob, sc.h_count.data(), &toff, &tiles);
     if (tiles > 0x7FFFFFFF / 8) return fail(ctx, OPMM_EINVAL, "too many candidate tiles in one batch");
     sc.max_T = S > 0 ? sacs[ob[0]].T : 0;  // the dispatch order is longest trace first
+    sc.sims = 0.0;
+    if (prm && prm->screen_rounds > 0)
+        for (int i = 0; i < S; ++i) sc.sims += (double)h[i].n_cand * h[i].T;
     if ((rc = ensure(ctx, sc.sacs, rec_bytes)) != OPMM_OK) return rc;
     if ((rc = ensure(ctx, sc.order, ord_bytes)) != OPMM_OK) return rc;
     OPMM_HIP(ctx, hipMemcpyAsync(sc.sacs.p, h, rec_bytes, hipMemcpyHostToDevice, st));
@@ -1367,6 +1375,7 @@ struct FitBufs {
     uint64_t* smin = nullptr;
     double* vthr = nullptr;  // verify threshold per saccade [S]
     int max_T = 0;  // longest trace (0: unknown)
+    double sims = 0.0;
 };
 
 int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, int tiles_per_round,
@@ -1410,6 +1419,7 @@ int enqueue_fit(opmm_ctx* ctx, FitScratch& sc, const float* pos, int S, int64_t 
         B.tmin = (uint32_t*)sc.tmin.p;
         B.vthr = (double*)sc.vthr.p;
         B.max_T = sc.max_T;
+        B.sims = sc.sims;
         B.smin = (uint64_t*)sc.smin.p;
     }
     return enqueue_fit_bufs(ctx, B, pos, S, tiles_per_round, prm, shape, seed_opc, opc_out, rmse_out, mae_out,
@@ -1455,6 +1465,7 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
     L.tmin = B.tmin;
     L.vthr = B.vthr;
     L.max_T = B.max_T;
+    L.sims = B.sims;
     L.smin = B.smin;
     L.qorth = qorth;
     L.tau = prm->screen_tol;

@@ -108,3 +108,31 @@ def test_extraction_allocates_for_what_it_finds(fake, N, max_out):
     """A stream without saccades costs no memory for records, however many the caller would take."""
     log = fake("ivt(%d, %d)\nprint(json.dumps(lines()))" % (N, max_out))
     assert sum(int(l[2]) for l in log if l[0] in ("malloc", "async", "pinned")) <= 1 << 20
+
+
+ANCHORED = """
+def anchored(recs, **kw):
+    fake.fake_clear()
+    fit(recs, n_rounds=10, screen_rounds=8, **kw)
+    names = ["anchor" if "anchor" in l[5] else "verify" for l in lines()
+             if l[0] == "launch" and ("anchor" in l[5] or "fit_verify" in l[5])]
+    rounds = "".join("a" if n == "anchor" else "v" for n in names).replace("av", "A")
+    assert len(rounds) == 8
+    return [r for r, c in enumerate(rounds) if c == "A"]
+"""
+
+
+def test_anchor_where_it_pays(fake):
+    """The rounds whose verify threshold comes from an anchor launch: those where it was measured to spare
+    more than it costs, by the candidates' work, the width and the tolerance; not by how the tiles pad."""
+    r = fake(ANCHORED + """
+big, few = records(256), records(2000)
+print(json.dumps(dict(
+    default=anchored(big, n_cand=65536), wide=anchored(big, n_cand=65536, screen_tol=5e-3),
+    tight=anchored(big, n_cand=65536, screen_tol=5e-6), one=anchored(records(1), n_cand=65536),
+    padded=[anchored(few, n_cand=513, tile=t) for t in (1, 7)])))""")
+    assert r["default"] in ([4, 5, 6, 7], [5, 6, 7])      # even at w = 1.6 %
+    assert r["wide"] == [1, 2, 3, 4, 5, 6, 7]
+    assert r["tight"] == [6, 7] or r["tight"] == [5, 6, 7]
+    assert r["one"] == []
+    assert r["padded"] == [[], []]
