@@ -479,7 +479,9 @@ typedef struct {
                            still iterating then stops with its best vertex
                            and OPMM_ST_DEADLINE (Section 3.3 names a time
                            limit among the exit criteria)              */
-    int32_t tasks_per_wave; /* 0 auto, 1 or 2 tasks per 64-lane wave   [0] */
+    int32_t tasks_per_wave; /* tasks per 64-lane wave: 1 or 2; 0 = auto, one
+                           or three by the batch's size and trace lengths
+                           (same results)                          [0] */
 } opmm_nm_params;
 void opmm_nm_params_default(opmm_nm_params* p);
 /* seed_opc: NULL (start at nominal) or device [S][18].  Outputs (device):

@@ -492,6 +492,25 @@ __global__ __launch_bounds__(64, 2) void nm_kernel(int S, const SacDev* __restri
     }
 }
 
+// Whether three tasks per wave (which share its instructions) finish a batch sooner than one.  While every task
+// has a SIMD to itself, one does: a wave of three takes 1.2 times as long.  Up to two waves per SIMD all
+// run at once, the S - simds shortest tasks beside a longer one, which the longest of them slows most: by
+// nothing where a task of its length takes 0.4 of the longest's time, 1.03 times at 0.5, 1.12 at 0.6, 1.2 at 0.64,
+// 1.3 at 0.73, 1.5 at 1 (an evaluation takes the time of 67 samples besides its trace's).  Past that, waves
+// queue.  Measured, 400 iterations, one / three per wave: T 26-87, 1024 saccades 2.82 / 3.42 ms, 1100 3.40 /
+// 3.39, 1500 3.66 / 3.43, 3072 5.28 / 3.45; T 20-150, 1100 3.86 / 4.60, 1500 4.37 / 4.62, 1900 4.72 / 4.68; all of
+// 26 samples, 1025 2.52 / 2.10.
+bool three_per_wave(const opmm_saccade* sacs, int S, int max_T, int simds)
+{
+    if (S <= simds) return false;
+    if (S > 2 * simds) return true;
+    int count[OPMM_MAX_T + 1] = {};
+    for (int i = 0; i < S; ++i) ++count[sacs[i].T];
+    int T = 0;  // of the longest among the S - simds shortest
+    for (int n = 0; n < S - simds;) n += count[++T];
+    return T + 67 > 0.64 * (max_T + 67);
+}
+
 }  // namespace
 
 extern "C" {
@@ -532,13 +551,10 @@ int opmm_fit_nm(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_sac
     if (rc != OPMM_OK) return rc;
     int max_T = 1;
     for (int i = 0; i < S; ++i) max_T = std::max(max_T, (int)sacs[i].T);
-    // While every task can have a SIMD to itself one task per wave is fastest (its four evaluations and
-    // nothing else); beyond that three share a wave and its instructions.  Measured, 200 iterations, one /
-    // two / three per wave: 1024 saccades 1.48 / 1.73 / 1.73 ms, 1500 1.88 / 1.75 / 1.75, 4096 3.49 / 2.33 / 2.17.
-    const int cus = opmm_rt::ctx_cu_count(ctx);
     // Three staged traces of more than 1024 samples leave room for no more tasks per CU than one does (160 KB
     // of LDS), and three of the longest would not fit a block's 64 KB.
-    const int G = prm->tasks_per_wave ? prm->tasks_per_wave : (S > 4 * cus && max_T <= 1024 ? 3 : 1);
+    const int G = prm->tasks_per_wave ? prm->tasks_per_wave
+                  : max_T <= 1024 && three_per_wave(sacs, S, max_T, 4 * opmm_rt::ctx_cu_count(ctx)) ? 3 : 1;
     uint64_t ticks = 0;
     if (prm->max_ms > 0.0f) {
         int khz = 0;

@@ -79,3 +79,11 @@ def test_long_traces_keep_one_task_per_wave():
         got.append((opc.cpu().numpy().tobytes(), rmse.cpu().numpy().tobytes()))
     assert got[0] == got[1] == got[2]
     ctx.close()
+
+
+@pytest.mark.parametrize("max_iter", [0, 60])
+def test_three_tasks_per_wave_past_two_waves_per_simd(max_iter):
+    """Beyond two waves per SIMD the automatic choice is three tasks per wave whatever the traces' lengths."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    test_three_tasks_per_wave(8 * torch.cuda.get_device_properties(0).multi_processor_count + 3, max_iter, 2e-2, 1e-2)

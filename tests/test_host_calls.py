@@ -136,3 +136,18 @@ print(json.dumps(dict(
     assert r["tight"] == [6, 7] or r["tight"] == [5, 6, 7]
     assert r["one"] == []
     assert r["padded"] == [[], []]
+
+
+def test_simplex_tasks_per_wave(fake):
+    """Saccades per wave of the simplex search (batch over grid): one while every task has a SIMD of its own or shares
+    it with a much shorter one, three where it shares it with one of like length, and beyond two per SIMD."""
+    r = fake("""
+def grid(T):
+    fake.fake_clear()
+    fit_nm(records(len(T), np.asarray(T)))
+    return [int(l[2]) for l in lines() if l[0] == "launch" and "nm_kernel" in l[5]]
+
+spread = lambda S: np.linspace(20, 150, S).astype(int)
+print(json.dumps([grid(np.full(1024, 57)), grid(np.full(1025, 57)), grid(spread(1025)), grid(spread(1500)),
+                  grid(spread(1900)), grid(spread(2049)), grid(np.full(1500, 1025)), grid([2048] + [20] * 1500)]))""")
+    assert r == [[1024], [342], [1025], [1500], [634], [683], [1500], [1501]]
