@@ -893,7 +893,17 @@ const Shape kShapes[] = {
 };
 constexpr int kOnePassShape = sizeof(kShapes) / sizeof(kShapes[0]) - 1;
 constexpr int kNumShapes = kOnePassShape;  // the shapes of opmm_fit_params.tile
-constexpr int kDefaultShape = 9;  // fastest per-round shape on the full-estimation workload (sweep)
+// Fastest shape on the full estimation: 256 x 65536 x 10, eight rounds screened, 7.85 ms, against 7.97 (128 x 8),
+// 8.04 (256 x 4, 256 x 16), 8.41 (64 x 16), 8.54 (128 x 32) and 8.61 (256 x 2); four FP64 rounds 4.66 ms, 256 x 16 4.64.
+constexpr int kDefaultShape = 9;
+
+// The lowest shape that runs shape i's kernel.
+int first_alike(int i)
+{
+    int k = 0;
+    while (kShapes[k].tpb != kShapes[i].tpb || kShapes[k].passes != kShapes[i].passes) ++k;
+    return k;
+}
 
 struct FitLaunch {
     const SacDev* sacs;
@@ -1506,8 +1516,10 @@ int enqueue_fit_bufs(opmm_ctx* ctx, const FitBufs& B, const float* pos, int S, i
 
 int shape_tile(int shape) { return kShapes[shape].tpb * kShapes[shape].passes; }
 
-// Shapes in the order of a sweep on the full-estimation workload (fastest first).
-constexpr int kShapePreference[] = {9, 10, 11, 5, 12, 4, 6, 2, 7, 3, 0, 1, 8};
+// A shape for each smaller tile, largest first, the fastest where several kernels have that tile: of 1024 candidates,
+// 2048 saccades x 1024 x 3 take 329 us screened and 496 us in FP64 with 256 x 4, 355 and 530 with 128 x 8, 382 and
+// 534 with 64 x 16.
+constexpr int kShapePreference[] = {9, 10, 1};
 
 // The tuned (else default) shape, unless its tile holds more candidates than
 // a saccade has: then the fastest shape whose tile fits (empty lanes do no
@@ -2168,6 +2180,7 @@ int opmm_autotune(opmm_ctx* ctx, const float* pos, int64_t pos_len, const opmm_s
     int best = 0;
     float best_ms = 1e30f;
     for (int sh = 0; sh < kNumShapes && rc == OPMM_OK; ++sh) {
+        if (first_alike(sh) != sh) continue;  // timed already
         pp.tile = sh;
         float ms_best = 1e30f;
         for (int rep = 0; rep < 3 && rc == OPMM_OK; ++rep) {

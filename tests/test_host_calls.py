@@ -151,3 +151,24 @@ spread = lambda S: np.linspace(20, 150, S).astype(int)
 print(json.dumps([grid(np.full(1024, 57)), grid(np.full(1025, 57)), grid(spread(1025)), grid(spread(1500)),
                   grid(spread(1900)), grid(spread(2049)), grid(np.full(1500, 1025)), grid([2048] + [20] * 1500)]))""")
     assert r == [[1024], [342], [1025], [1500], [634], [683], [1500], [1501]]
+
+
+def test_autotuner_times_each_kernel_once(fake):
+    """Shapes that run the same kernel are one candidate; the pick is the lowest index of its kernel."""
+    launches, pick, small = fake("""
+recs, prm, t = records(64), opmm.fit_params(n_cand=65536, n_rounds=2), ctypes.c_int32(-1)
+check(lib.opmm_autotune(ctx._h, P, 1 << 40, ptr(recs), len(recs), ctypes.byref(prm), ctypes.byref(t), None))
+tuned = lines()
+c2 = opmm.Context(0)
+small = []
+for n in (1 << 20, 2048, 2047, 1024, 1023, 512, 511, 1):     # the library's own choice, by candidates
+    fake.fake_clear()
+    r = records(3000)
+    assert lib.opmm_fit(c2._h, P, 1 << 40, ptr(r), 3000, ctypes.byref(opmm.fit_params(n_cand=n)), None, P, P, None, None,
+                        None, None) == 0
+    small += [l[5].split("fit_round_kernel")[1][:11] for l in lines() if l[0] == "launch" and "fit_round" in l[5]]
+print(json.dumps([tuned, t.value, small]))""")
+    kernels = [l[5] for l in launches if l[0] == "launch" and "fit_round" in l[5]]
+    assert len(set(kernels)) == 7 and all(kernels.count(k) == 2 * 3 for k in set(kernels))
+    assert pick == 0
+    assert small == ["ILi256ELi8E"] * 2 + ["ILi256ELi4E"] * 2 + ["ILi256ELi2E"] * 4
