@@ -74,3 +74,29 @@ def test_polish_alone_and_three_to_a_wave(ctx, opmm, objective):
         assert abs(rm[s] - want[1]) <= 1e-6 * want[1] + 1e-6
         if objective == 0:
             assert rm[s] <= want[0] + 1e-6
+
+
+@pytest.mark.parametrize("copies", [1, 112])
+def test_polish_lowers_the_mean_absolute_difference(ctx, opmm, copies):
+    """Objective MAE: mae_out is the oracle's mean absolute difference of the result, and no larger than the
+    start's; one saccade per wave, and three."""
+    recs, start, traces = problem(opmm)
+    S = len(LENGTHS)
+    pos = np.concatenate([t.reshape(-1) for t in traces])
+    d = torch.from_numpy(np.tile(pos, copies)).cuda()
+    many = np.concatenate([recs] * copies)
+    for c in range(copies):
+        many["pos_offset"][c * S:(c + 1) * S] += c * pos.size
+    opc = torch.from_numpy(np.tile(start, (copies, 1))).cuda()
+    rm, ma = torch.zeros(S * copies, device="cuda"), torch.zeros(S * copies, device="cuda")
+    ctx.polish(d, many, opmm.polish_params(max_iter=3, objective=opmm.OBJ_MAE), opc, rm, ma)
+    torch.cuda.synchronize()
+    opc, rm, ma = opc.cpu().numpy()[-S:], rm.cpu().numpy()[-S:], ma.cpu().numpy()[-S:]
+    for s in range(S):
+        rmse, mae = oracle.score(np.stack([start[s], opc[s]]), traces[s], 11.0, 25.0)
+        # FP32 outputs of costs of a few hundredths of a degree; the plant's truncation is far below
+        assert abs(rm[s] - rmse[1]) <= 1e-6 * rmse[1] + 1e-6, LENGTHS[s]
+        assert abs(ma[s] - mae[1]) <= 1e-6 * mae[1] + 1e-6, LENGTHS[s]
+        assert mae[1] <= mae[0] + 1e-6, LENGTHS[s]
+    assert np.mean([oracle.score(opc[s:s + 1], traces[s], 11.0, 25.0)[1][0] for s in range(S)]) < \
+        np.mean([oracle.score(start[s:s + 1], traces[s], 11.0, 25.0)[1][0] for s in range(S)])
