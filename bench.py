@@ -27,7 +27,9 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-FLOP_PER_CAND_SAMPLE = 54  # algorithmic work of one recurrence step + fused squared residual
+# work of a one-sample recurrence step + fused squared residual, per candidate and sample: the unit of the algorithmic
+# figures; the block recurrence, four samples per step, executes fewer
+FLOP_PER_CAND_SAMPLE = 54
 ALU_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12  # 256 CU x 4 SIMD x 16 lanes x FMA x 2.4 GHz: v_fma_f64 or non-packed v_fma_f32
 PUBLISHED_FP32_PEAK = 157.3
 
@@ -616,7 +618,9 @@ def main():
     fp32 = dom == "fit_screen_kernel"
     peak = PUBLISHED_FP32_PEAK if fp32 else ALU_PEAK_TFLOPS
     dom_ms = kt[dom]["avg_ms"]
-    achieved = flop_launch / (dom_ms * 1e-3) / 1e12
+    algorithmic = flop_launch / (dom_ms * 1e-3) / 1e12
+    executed = executed_fig(profiled_value("executed_flop_per_launch", dom, tile_name), dom_ms, peak)
+    achieved = executed["tflops"] if executed else algorithmic
     # the whole step against the peak of the precision each round runs in
     step_peak = R / (scr / PUBLISHED_FP32_PEAK + (R - scr) / ALU_PEAK_TFLOPS)
     step_tflops = flop / (step_ms_gpu * 1e-3) / 1e12
@@ -655,19 +659,22 @@ def main():
         "status_nonzero": int(np.count_nonzero(st)),
         "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
+                     "counted": "executed FLOP" if executed else "algorithmic FLOP (no counter summary of these "
+                                "kernel sources)",
                      "traffic": profiled_value("traffic_per_launch_bytes", dom, tile_name),
                      "kernel": kernel_text,
                      "peak_source": ("published FP32 vector peak (non-packed FMA issues at up to twice the FP64 "
                                      "rate on this chip)" if fp32 else
                                      "FP64 vector peak: 256 CU x 4 SIMD x 16 lanes x FMA x 2.4 GHz"),
                      "launch_ms": dom_ms, "launch_timing": "library event pairs around each launch, launch stream",
-                     "algorithmic_flop_per_launch": flop_launch,
-                     "executed": executed_fig(profiled_value("executed_flop_per_launch", dom, tile_name), dom_ms,
-                                              peak),
+                     "algorithmic": {"flop_per_launch": flop_launch, "tflops": algorithmic, "frac": algorithmic / peak,
+                                     "note": "%d FLOP per candidate-sample, a one-sample step each: more than the "
+                                             "block recurrence executes" % FLOP_PER_CAND_SAMPLE},
+                     "executed": executed,
                      "kernels": kt,
                      "step": {"achieved": step_tflops, "peak": step_peak, "frac": step_tflops / step_peak,
-                              "note": "whole captured step (all kernels) against the peak of each round's "
-                                      "precision: %d FP32 rounds at %.1f, %d FP64 rounds at %.1f TFLOP/s" % (
+                              "note": "whole captured step (all kernels), algorithmic FLOP, against the peak of each "
+                                      "round's precision: %d FP32 rounds at %.1f, %d FP64 rounds at %.1f TFLOP/s" % (
                                           scr, PUBLISHED_FP32_PEAK, R - scr, ALU_PEAK_TFLOPS)}},
     }
     if a.report_csv:

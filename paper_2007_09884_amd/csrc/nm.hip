@@ -65,11 +65,11 @@ __device__ __forceinline__ double pick(int i, double a, double b, double c, doub
 }
 
 // ---- one evaluation on a quad -------------------------------------------------
-// The simplex's iterates depend on every rounding of its costs, so this file keeps the sample-by-sample
-// evaluation its results are defined by: the transition by Horner's rule and squarings on matrices, one
-// step per sample (run_blocks in plant.hpp gives the same trajectories to ~1e-14 deg).  A quad only
-// spreads that evaluation's operations over four lanes; each result goes through the same operations in
-// the same order as on one.
+// The simplex's iterates depend on every rounding of its costs, so that its results stay the bits they were this
+// file keeps the sample-by-sample evaluation: the transition by Horner's rule and squarings on matrices, one
+// step per sample.  (run_blocks in plant.hpp gives the same trajectories to ~1e-14 deg, well within what the
+// decisions' comparison with the oracle allows.)  A quad only spreads that evaluation's operations over four
+// lanes; each result goes through the same operations in the same order as on one.
 
 // Column c of the one-sample transition in D-form (D = Phi - I): mechanical block m[.][c], coupling x[.][c]
 // of active state c (pulse ag, pulse ant, post ag, post ant) and that state's factor minus one e.

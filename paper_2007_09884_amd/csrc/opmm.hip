@@ -3,17 +3,19 @@
 //
 // Hot path (one fused kernel per candidate tile):
 //   candidate draw (SplitMix64 stream, in registers)
-//   -> per-candidate plant setup (D-form one-sample transition, equilibria)
-//   -> T-sample recurrence with the projected target trace in LDS and the
-//      squared residual accumulated on the fly
+//   -> per-candidate plant setup (equilibria, transitions over 1-4 samples as
+//      polynomials of the plant matrix)
+//   -> T samples, four per step, with the projected target trace in LDS and
+//      the squared residual accumulated on the fly
 //   -> wave/block argmin of a packed (SSE bits, index) key -> one 64-bit
-//      atomicMin per tile on the saccade's round slot.
+//      atomicMin per tile on the saccade's round slot; the block that posts
+//      a saccade's last tile refines its box.
 // Candidates of a tile are ordered by the sample that holds their pulse end
 // (a counting sort in LDS) before they are assigned to lanes, so the lanes of
-// a wave switch from the pulse to the step within one or two samples of each
-// other and the recurrence stays branch-free elsewhere.  The ordering changes
-// nothing in any lane's arithmetic, and the argmin key is order-independent,
-// so results are bit-identical for every tile shape and batch layout.
+// a wave end their pulse blocks within a block of each other and few are
+// masked.  The ordering changes nothing in any lane's arithmetic, and the
+// argmin key is order-independent, so results are bit-identical for every
+// tile shape and batch layout.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -543,14 +545,6 @@ __global__ __launch_bounds__(64) void screen_anchor_kernel(const SacDev* __restr
     thr[slot] = rm <= 1e300 ? rm * rm * m - q : __builtin_inf();  // a non-finite anchor verifies all
 }
 
-// Screened round, second pass, one wave per tile (a tile's survivors are often fewer than one
-// block's lanes, and a one-wave block leaves no wave of it idle).  The tile's candidates whose FP32
-// RMSE lies within tau of the saccade's FP32 best (or is NaN) are simulated again exactly as the FP64
-// round kernel simulates them, in the first pass's pulse-end order, and their FP64 keys go to
-// keys[round][slot].  The threshold comes from screen_anchor_kernel: with n = T C samples and Q the
-// orthogonal energy, RMSE = sqrt((SSE + Q) / n), so a candidate passes when its FP32 SSE <=
-// (RMSE64(b) + tau / 2)^2 n - Q.  A tile whose least FP32 SSE (tmin, 0 when one is NaN) misses that
-// is left without reading its costs.
 // Verify threshold (SSE units) without an anchor: FP32 RMSE <= RMSE32(b) + tau for the FP32 best b.  The FP64
 // argmin x* passes under the same condition eps <= tau / 2: RMSE32(x*) <= RMSE64(x*) + eps <= RMSE64(b) + eps
 // <= RMSE32(b) + 2 eps.
@@ -573,6 +567,14 @@ struct VerifySmem {
 // longest trace), so that short traces leave room for more waves per CU.
 extern __shared__ R verify_trace[];
 
+// Screened round, second pass, one wave per tile (a tile's survivors are often fewer than one
+// block's lanes, and a one-wave block leaves no wave of it idle).  The tile's candidates whose FP32
+// SSE is at most the saccade's threshold (or is NaN) are simulated again exactly as the FP64
+// round kernel simulates them, in the first pass's pulse-end order, and their FP64 keys go to
+// keys[round][slot].  The threshold: with n = T C samples and Q the orthogonal energy,
+// RMSE = sqrt((SSE + Q) / n), (RMSE64(b) + tau / 2)^2 n - Q from screen_anchor_kernel (vthr), or
+// (RMSE32(b) + tau)^2 n - Q where no anchor was launched (vthr null: best_threshold).  A tile whose
+// least FP32 SSE (tmin, 0 when one is NaN) misses it is left without reading its costs.
 template <int TILE>
 __global__ __launch_bounds__(64, OPMM_MIN_WAVES) void fit_verify_kernel(
     const SacDev* __restrict__ sacs, int S, int round, int key_stride, float dt, const float* __restrict__ proj,

@@ -606,17 +606,11 @@ __device__ __forceinline__ void split_step(const PlantT<RT>& pl, RT frac, RT d[6
     expmv<D, 1>(pl, (RT(1) - frac) * steps, d);
 }
 
-// wave-wide min / max of an int (64 lanes)
+// wave-wide min of an int (64 lanes)
 __device__ __forceinline__ int wave_min(int v)
 {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ int wave_max(int v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
     return v;
 }
 
@@ -668,7 +662,8 @@ __device__ __forceinline__ void block_step(const PlantT<RT>& pl, const ThetaRows
 }
 
 // Run the trajectory theta_k, k = 0..T-1: for each sample, t = sink.begin(k, u) and sink.end(k, t - v)
-// with theta_k = u + v; sink.block_end() after each whole block (at most 7 samples lie outside blocks).  pl's transition (m, x, e) is set to that of a block.
+// with theta_k = u + v; sink.block_end() after each whole block (at most 7 samples lie outside blocks).
+// pl's transition (m, x, e) is set to that of a block.
 //
 // Bound by VALU issue.  A block of four samples costs one step of the four-sample transition (26
 // multiply-adds) and three rows (6 each) instead of four one-sample steps: 53 operations per block with a

@@ -371,10 +371,10 @@ __device__ __forceinline__ bool damped_solve(const PolishSlot& sl, double lam, u
     return true;
 }
 
-// Bound by the latency of one wave per SIMD (512 registers: dual numbers).  Cycles per iteration at T = 61, one
-// saccade per wave, with sample-by-sample matrices and the residuals on every lane -> now: Jacobian pass
-// ~105k -> 52k, damped solves 37k -> 28k (their Cholesky factorisations; the held parameters and trial points
-// went to a lane each), trial costs ~40k -> 21k.  1000 saccades x 4 iterations: 443 -> 288 us.
+// Bound by the latency of one wave per SIMD (512 registers: dual numbers).  Cycles per iteration at T = 57, one
+// saccade per wave among 1000, with sample-by-sample matrices and the residuals on every lane -> now: Jacobian
+// pass 99k -> 57k, damped solves 39k -> 28k (their Cholesky factorisations; the held parameters and trial
+// points went to a lane each), trial costs 45k -> 25k.  1000 saccades x 4 iterations: 443 -> 288 us.
 // PG saccades per wave: lane group g = lane / GL polishes saccade order[blockIdx.x * PG + g]
 // (order: the batch sorted by T, so a wave's saccades run loops of similar length; NULL: batch
 // order).  A group's arithmetic is that of a wave of its own, so results do not depend on the
