@@ -128,3 +128,30 @@ def test_several_chunks_per_tile_and_odd_alignment():
     want = np.concatenate([g[a:a + t] - g[a] for a, t in zip(first, T)]).reshape(-1)
     assert np.array_equal(P, want)
     ctx.close()
+
+
+@pytest.mark.gpu
+def test_many_short_runs_take_no_turns():
+    """A stream that moves in every other sample takes a few times as long as a still one, not ten times (a chunk's
+    thousand runs are emitted side by side)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import time
+    from paper_2007_09884_amd import opmm
+    ctx = opmm.Context(0)
+    N = 100000
+    flags = np.zeros(N, bool)
+    pos = torch.zeros(2 * N, device="cuda")
+    best = {}
+    for name in ("still", "alternate"):
+        flags[1::2] = name == "alternate"
+        d = torch.from_numpy(stream(flags)).cuda()
+        times = []
+        for _ in range(30):
+            t = time.perf_counter()
+            recs, _src = ctx.ivt_extract(d, pos, min_dur=0.0, max_out=4096)
+            times.append(time.perf_counter() - t)
+        assert len(recs) == (4096 if name == "alternate" else 0)
+        best[name] = min(times)
+    assert best["alternate"] < 6 * best["still"], best
+    ctx.close()
