@@ -200,37 +200,32 @@ __constant__ Triangle TRI;
 
 // Normal equations of the linearised problem.  Lane r of the saccade's group carries column r of
 // J (the dual part).  A sample only stages its row of J and its theta in LDS; every NCH - 8 samples or so the
-// staged ones are worked off: lanes take a sample each for its residual and weights, then lane r accumulates
-// g_r and up to NENT entries (i >= j) of the lower triangle of J^T W J, h_ij += (w_k J_ki) J_kj in sample
+// staged ones are worked off: lanes take a sample each for its residual and weights, then lane r adds to
+// g_r and to its entries (i >= j) of the lower triangle of J^T W J, h_ij += (w_k J_ki) J_kj in sample
 // order.  Every lane of the group calls it (the group's control flow is uniform).
 // (With the residual on every lane of every sample and the entries' indices looked up in each step a
 // sample took 830 cycles of a lone wave, most of the Jacobian pass; now 300.)
+// The sums stay in LDS between flushes: held in registers they and their indices are live through the whole
+// trajectory (187 spilled registers with three saccades to a wave instead of 137; 4096 saccades x 4 iterations,
+// two to a wave: T = 7 418 -> 336 us, T 26-87 700 -> 617, with nine parameters 693 -> 560).
 template <int GL>
 struct NormalSink {
-    static constexpr int NENT = (PTRI + GL - 1) / GL;  // lower-triangle entries accumulated per lane
+    static constexpr int NENT = (PTRI + GL - 1) / GL;  // lower-triangle entries of a lane, of 18 parameters
+    static constexpr int NFEW = 3;                     // and of 9, at most
+    static_assert(9 * 10 / 2 <= NFEW * GL, "entries of nine parameters");
     Residual res;
     int objective;
-    double* jst;  // LDS [NCH][P]: staged rows of J
-    double* ast;  // LDS [NCH]: staged theta, then the sample's weight in the normal matrix
-    double* bst;  // LDS [NCH]: its weighted residual
-    int r;        // lane within the group
-    int nk;       // samples staged
-    int k0;       // index of the first
-    double g;
-    int eij[NENT];  // this lane's entries; -1: none
-    double h[NENT];
-    __device__ void init(int nf)
-    {
-        nk = 0;
-        k0 = 0;
-        g = 0.0;
-#pragma unroll
-        for (int q = 0; q < NENT; ++q) {
-            const int e = r + GL * q;
-            eij[q] = (e < PTRI && (TRI.e[e < PTRI ? e : 0] >> 8) < nf) ? TRI.e[e < PTRI ? e : 0] : -1;
-            h[q] = 0.0;
-        }
-    }
+    double* jst;          // LDS [NCH][P]: staged rows of J
+    double* ast;          // LDS [NCH]: staged theta, then the sample's weight in the normal matrix
+    double* bst;          // LDS [NCH]: its weighted residual
+    double* H;            // LDS [P][P]: lower triangle of J^T W J
+    double* g;            // LDS [P]: J^T W e
+    const uint16_t* tri;  // LDS [PTRI]: the triangle's entries
+    int nf;               // free parameters
+    bool few;             // 9 of them, the same in every group
+    int r;                // lane within the group
+    int nk;               // samples staged
+    int k0;               // index of the first
     __device__ __forceinline__ Dual begin(int, Dual u) const { return -u; }
     __device__ __forceinline__ void end(int, Dual e)
     {
@@ -263,25 +258,44 @@ struct NormalSink {
             bst[kk] = b;
         }
         wave_sync();
-        const double* pi[NENT];
-        const double* pj[NENT];
-#pragma unroll
-        for (int q = 0; q < NENT; ++q) {
-            const int e = max(eij[q], 0);  // entries past the triangle work on (0, 0) and go nowhere
-            pi[q] = jst + (e >> 8);
-            pj[q] = jst + (e & 255);
-        }
-        const double* pg = jst + min(r, P - 1);
-#pragma unroll 4
-        for (int kk = 0; kk < nk; ++kk) {
-            const double ak = ast[kk];
-            g = __fma_rn(pg[kk * P], bst[kk], g);
-#pragma unroll
-            for (int q = 0; q < NENT; ++q) h[q] = __fma_rn(ak * pi[q][kk * P], pj[q][kk * P], h[q]);
-        }
+        if (NENT > NFEW && few) add_samples<NFEW>();
+        else add_samples<NENT>();
         wave_sync();
         k0 += nk;
         nk = 0;
+    }
+    // Adds the staged samples to g_r and to the lane's entries r, r + GL, ... (NQ of them at most).
+    template <int NQ>
+    __device__ __forceinline__ void add_samples()
+    {
+        int l = r;
+        keep(l);  // what follows from it is formed here: hoisted out of the flush it is live through the trajectory
+        const int ne = nf * (nf + 1) / 2;  // entries of the free parameters: the first rows
+        int at[NQ];
+        const double *pi[NQ], *pj[NQ];
+        double h[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int n = l + GL * q;
+            const int e = n < ne ? tri[n] : 0;  // entries past the triangle work on (0, 0) and go nowhere
+            at[q] = n < ne ? (e >> 8) * P + (e & 255) : -1;
+            pi[q] = jst + (e >> 8);
+            pj[q] = jst + (e & 255);
+            h[q] = at[q] >= 0 && k0 > 0 ? H[at[q]] : 0.0;
+        }
+        const double* pg = jst + min(l, P - 1);
+        double gr = k0 > 0 && l < nf ? g[l] : 0.0;
+#pragma unroll 4
+        for (int kk = 0; kk < nk; ++kk) {
+            const double ak = ast[kk];
+            gr = __fma_rn(pg[kk * P], bst[kk], gr);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) h[q] = __fma_rn(ak * pi[q][kk * P], pj[q][kk * P], h[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (at[q] >= 0) H[at[q]] = h[q];
+        if (l < nf) g[l] = gr;
     }
 };
 
@@ -389,6 +403,7 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
                                                     int32_t* __restrict__ iters_out, int8_t* __restrict__ dec_out)
 {
     __shared__ PolishSlot slots[PG];
+    __shared__ uint16_t tri[PTRI];
     extern __shared__ float traces[];
     const int lane = threadIdx.x;
     constexpr int GL = group_lanes(PG);
@@ -404,6 +419,7 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
     const SacDev sd = has ? sacs[s] : SacDev{};
     const int T = sd.T;
     bool live = has;
+    for (int e = lane; e < PTRI; e += 64) tri[e] = TRI.e[e];
     if (has && ((status_in[sd.slot] & OPMM_ST_NONFINITE_INPUT) || T > max_T)) {
         if (r < P) opc[(int64_t)s * P + r] = __int_as_float(0x7FC00000);
         if (r == 0) {
@@ -470,14 +486,9 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
             const int i1 = r < nf ? sl.tied[r] : -1;
             for (int i = 0; i < P; ++i)
                 p[i] = Dual(opc_value(sl, sl.x, i), (i == i0 || i == i1) ? sl.nom[i] : 0.0);
-            NormalSink<GL> ns{res, objective, &sl.jst[0][0], sl.ast, sl.bst, r};
-            ns.init(nf);
+            NormalSink<GL> ns{res, objective, &sl.jst[0][0], sl.ast, sl.bst, &sl.H[0][0], sl.g, tri, nf, model == 9, r, 0, 0};
             simulate_s<DiscFast>(p, (double)sd.amp, dt, T, ns);
             ns.flush();
-#pragma unroll
-            for (int q = 0; q < NormalSink<GL>::NENT; ++q)
-                if (ns.eij[q] >= 0) sl.H[ns.eij[q] >> 8][ns.eij[q] & 255] = ns.h[q];
-            if (r < nf) sl.g[r] = ns.g;
         }
         __syncthreads();
         // B: damped solves, one damping value per lane; held parameters by a lane each
@@ -556,10 +567,11 @@ __global__ __launch_bounds__(64) void polish_kernel(int S, const SacDev* __restr
     }
 }
 
-// Time of one wave polishing pg saccades, relative to a wave with one (288, 432 and 545 us for 1000, 2000
-// and 3000 full-estimation saccades, one wave per SIMD and four iterations: the groups' loops run to the
-// longest member, and each lane accumulates more entries of the normal matrix).
-constexpr double WAVE_TIME[4] = {0.0, 1.0, 1.50, 1.89};
+// Time of one wave polishing pg saccades, relative to a wave with one (258, 360 and 448 us for 1000, 2000
+// and 3000 full-estimation saccades, one wave per SIMD and four iterations; 252, 314 and 344 with nine
+// parameters: the groups' loops run to the longest member, and each lane accumulates more entries of the
+// normal matrix).
+constexpr double WAVE_TIME[4] = {0.0, 1.0, 1.40, 1.73};
 
 // Saccades per wave for n saccades (T <= max_T) on `simds` SIMDs: one wave per SIMD is resident at
 // a time, so a batch takes ceil(waves / simds) wave times.
